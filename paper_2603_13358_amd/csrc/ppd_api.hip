@@ -20,13 +20,18 @@ namespace {
 thread_local std::string g_create_error;
 
 constexpr int kStagingSlots = 4;
+constexpr int kStagingFlagStride = 16;  // words between the slots' flags: a cache line each
+// the upload kernel reads the staged plan in place, and the host reads the flag it writes: mapped, coherent
+constexpr unsigned kStagingFlags = hipHostMallocMapped | hipHostMallocCoherent;
 constexpr size_t kMaxTimedLaunches = 4096;
 
+// A pinned buffer a plan is staged in on its way to the device.  The upload kernel writes the upload's serial number
+// to *read when it has read the buffer.
 struct Staging {
-    void* host = nullptr;  // pinned
+    void* host = nullptr;  // pinned, mapped
     size_t bytes = 0;
-    hipEvent_t done = nullptr;
-    bool in_flight = false;
+    volatile uint32_t* read = nullptr;
+    uint32_t serial = 0;
 };
 
 }  // namespace
@@ -45,6 +50,7 @@ struct ppd_ctx {
     size_t d_partials_floats = 0;
     uint32_t* d_counters = nullptr;  // kCounterWords words: error flags, finished-workgroup counts, queue cursors
     Staging staging[kStagingSlots];
+    uint32_t* staging_flags = nullptr;  // pinned: the words the slots' `read` point at
     int next_slot = 0;
     // the plan on the device stays valid while L, n and the planner options do not change (the layers of one
     // engine step call with the same lengths): such calls skip planning and upload
@@ -67,10 +73,7 @@ struct ppd_ctx {
     // debugging aids switched on by environment variables read in ppd_create
     bool log_calls = false;          // PPD_LOG=1: one line per call on stderr
     uint32_t* d_slot_seen = nullptr;  // PPD_DEBUG_SLOTS=1: one bit per pool slot, to find duplicate slots of an append
-    // pinned staging of the entry point that allocates nothing (fixed size, allocated with the context)
-    void* static_staging = nullptr;
-    hipEvent_t static_staging_done = nullptr;
-    bool static_staging_in_flight = false;
+    Staging static_staging;  // of the entry point that allocates nothing (fixed size, allocated with the context)
     // optional timing of the attention kernels alone (option "timing"): one pair of events per call since the option
     // was set or the times were last collected, up to kMaxTimedLaunches
     bool timing = false;
@@ -149,6 +152,37 @@ hipError_t static_scratch_address(int device, unsigned char** out) {
 __global__ void ppd_clear_counters_kernel(uint32_t* counters) {
     for (int i = threadIdx.x; i < ppd::kCounterWords; i += blockDim.x)
         if (i == 10 || i == 11 || i >= ppd::kCursorBase) counters[i] = 0u;
+}
+
+// Copies a staged plan from pinned host memory to the device and tells the host that the staging buffer has been read.
+// Bound by the latency of one read across PCIe (2 us) up to ~50 KB, by its bandwidth beyond (180 KB: ~6 us).  A copy
+// command does the same through the copy engine, whose hand-overs with the kernels before and after leave the stream
+// idle for ~20 us; a kernel follows and is followed like any other.
+// Measured: 13-15 us less per new plan (a decode step of 64 sequences at 1K-8K over two layers 433 -> 418 us, an
+// append-prefill of 16 and the decode step after it 816 -> 793 us).
+// One workgroup moves 16 KiB (16 B per lane, every read issued at once); the last one to finish (counted in word
+// `done_word`, which it re-arms) writes the serial number.
+constexpr int kUploadThreads = 1024;
+__global__ __launch_bounds__(kUploadThreads) void ppd_upload_kernel(const uint4* host, uint4* dev, int64_t granules, uint32_t* counters,
+                                                                    uint32_t* read, uint32_t serial) {
+    const int64_t i = (int64_t)blockIdx.x * kUploadThreads + threadIdx.x;
+    if (i < granules) dev[i] = host[i];
+    __syncthreads();  // the workgroup's reads have returned: their values are stored
+    if (threadIdx.x == 0) {
+        if (gridDim.x > 1) {
+            if (atomicAdd(&counters[ppd::kUploadWord], 1u) != gridDim.x - 1) return;
+            __hip_atomic_store(&counters[ppd::kUploadWord], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __hip_atomic_store(read, serial, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// Waits until the upload that last used a staging buffer has read it.
+ppd_status wait_staging_read(ppd_ctx* ctx, const Staging& sg) {
+    for (int spin = 0; spin < 1 << 14; ++spin)
+        if (*sg.read == sg.serial) return PPD_OK;
+    PPD_HIP(ctx, hipDeviceSynchronize());
+    return PPD_OK;
 }
 
 // Debugging aid (PPD_DEBUG_SLOTS=1): marks every slot of an append in a bitmap; a bit found set already is a
@@ -253,28 +287,17 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     void* d_plan = use_static ? static_cast<void*>(sbase + kStaticCounterBytes) : nullptr;
     if (!reuse) {
         // upload: [items][groups][units] through pinned staging
-        void* host = nullptr;
-        hipEvent_t done = nullptr;
-        if (use_static) {
-            if (ctx->static_staging_in_flight) {
-                PPD_HIP(ctx, hipEventSynchronize(ctx->static_staging_done));
-                ctx->static_staging_in_flight = false;
-            }
-            host = ctx->static_staging;
-            done = ctx->static_staging_done;
-        } else {
-            Staging& sg = ctx->staging[ctx->next_slot];
+        Staging& sg = use_static ? ctx->static_staging : ctx->staging[ctx->next_slot];
+        st = wait_staging_read(ctx, sg);
+        if (st != PPD_OK) return st;
+        if (!use_static) {
             ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
-            if (sg.in_flight) {
-                PPD_HIP(ctx, hipEventSynchronize(sg.done));
-                sg.in_flight = false;
-            }
             if (sg.bytes < total) {
                 if (sg.host) PPD_HIP(ctx, hipHostFree(sg.host));
                 sg.host = nullptr;
                 sg.bytes = 0;
                 const size_t want = total + total / 4 + 4096;
-                if (hipHostMalloc(&sg.host, want, hipHostMallocDefault) != hipSuccess) {
+                if (hipHostMalloc(&sg.host, want, kStagingFlags) != hipSuccess) {
                     (void)hipGetLastError();
                     sg.host = nullptr;
                     return fail(ctx, PPD_ERR_WORKSPACE, "pinned staging allocation failed");
@@ -291,22 +314,21 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
                 ctx->d_partials_floats = have / sizeof(float);
                 if (st != PPD_OK) return st;
             }
-            host = sg.host;
-            done = sg.done;
-            sg.in_flight = true;
         }
+        void* host = sg.host;
         std::memcpy(host, plan.items.data(), items_bytes);
         if (groups_bytes) {
             std::memcpy(static_cast<char*>(host) + items_bytes, plan.groups.data(), groups_bytes);
             std::memcpy(static_cast<char*>(host) + items_bytes + groups_bytes, plan.units.data(), units_bytes);
         }
         std::memcpy(static_cast<char*>(host) + total - bounds_bytes, plan.queue_begin, bounds_bytes);
-        PPD_HIP(ctx, hipMemcpyAsync(use_static ? d_plan : ctx->d_items, host, total, hipMemcpyHostToDevice, hs));
-        PPD_HIP(ctx, hipEventRecord(done, hs));
-        if (use_static) {
-            ctx->static_staging_in_flight = true;
-            g_scratch_owner[ctx->device] = ctx;
-        }
+        const int64_t granules = (int64_t)((total + 15) / 16);
+        hipLaunchKernelGGL(ppd_upload_kernel, dim3((unsigned)((granules + kUploadThreads - 1) / kUploadThreads)), dim3(kUploadThreads), 0, hs,
+                           static_cast<const uint4*>(host), static_cast<uint4*>(use_static ? d_plan : ctx->d_items), granules,
+                           ctx->d_counters, const_cast<uint32_t*>(sg.read), sg.serial + 1);
+        PPD_HIP(ctx, hipGetLastError());
+        sg.serial += 1;
+        if (use_static) g_scratch_owner[ctx->device] = ctx;
         ctx->plan_L.assign(L, L + B);
         ctx->plan_n.assign(n, n + B);
         ctx->plan_opts = opts;
@@ -479,8 +501,13 @@ ppd_status ppd_create(const ppd_shape* shape, int32_t device, ppd_ctx** out) {
     const size_t counter_bytes = ppd::kCounterWords * sizeof(uint32_t);
     if ((e = hipMalloc((void**)&ctx->d_counters, counter_bytes)) != hipSuccess) return bail(e, "hipMalloc(counters)");
     if ((e = hipMemset(ctx->d_counters, 0, counter_bytes)) != hipSuccess) return bail(e, "hipMemset(counters)");
-    for (auto& s : ctx->staging)
-        if ((e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
+    if ((e = hipHostMalloc((void**)&ctx->staging_flags, (kStagingSlots + 1) * kStagingFlagStride * sizeof(uint32_t), kStagingFlags)) != hipSuccess)
+        return bail(e, "hipHostMalloc(staging flags)");
+    for (int i = 0; i <= kStagingSlots; ++i) {
+        Staging& s = i < kStagingSlots ? ctx->staging[i] : ctx->static_staging;
+        s.read = ctx->staging_flags + i * kStagingFlagStride;
+        *s.read = 0;
+    }
     // the stream kernel of the co-resident pair runs on a stream of the context's own (default priority)
     if ((e = hipStreamCreateWithFlags(&ctx->side_stream, hipStreamNonBlocking)) != hipSuccess) return bail(e, "hipStreamCreate");
     if ((e = hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
@@ -491,10 +518,9 @@ ppd_status ppd_create(const ppd_shape* shape, int32_t device, ppd_ctx** out) {
         unsigned char* sp = nullptr;
         if ((e = static_scratch_address(device, &sp)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
     }
-    if ((e = hipHostMalloc(&ctx->static_staging, kStaticPlanBytes, hipHostMallocDefault)) != hipSuccess)
+    if ((e = hipHostMalloc(&ctx->static_staging.host, kStaticPlanBytes, kStagingFlags)) != hipSuccess)
         return bail(e, "hipHostMalloc(static staging)");
-    if ((e = hipEventCreateWithFlags(&ctx->static_staging_done, hipEventDisableTiming)) != hipSuccess)
-        return bail(e, "hipEventCreate");
+    ctx->static_staging.bytes = kStaticPlanBytes;
     const char* env = std::getenv("PPD_LOG");
     ctx->log_calls = env && env[0] == '1';
     env = std::getenv("PPD_DEBUG_SLOTS");
@@ -517,7 +543,6 @@ ppd_status ppd_destroy(ppd_ctx* ctx) {
     if (ctx->d_slot_seen) (void)hipFree(ctx->d_slot_seen);
     for (auto& s : ctx->staging) {
         if (s.host) (void)hipHostFree(s.host);
-        if (s.done) (void)hipEventDestroy(s.done);
     }
     for (auto& p : ctx->ev_pairs) {
         if (p.first) (void)hipEventDestroy(p.first);
@@ -526,8 +551,8 @@ ppd_status ppd_destroy(ppd_ctx* ctx) {
     if (ctx->side_stream) (void)hipStreamDestroy(ctx->side_stream);
     if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
     if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
-    if (ctx->static_staging) (void)hipHostFree(ctx->static_staging);
-    if (ctx->static_staging_done) (void)hipEventDestroy(ctx->static_staging_done);
+    if (ctx->static_staging.host) (void)hipHostFree(ctx->static_staging.host);
+    if (ctx->staging_flags) (void)hipHostFree(ctx->staging_flags);
     {
         std::lock_guard<std::mutex> lock(g_scratch_mutex);
         if (ctx->device >= 0 && ctx->device < kMaxDevices && g_scratch_owner[ctx->device] == ctx)

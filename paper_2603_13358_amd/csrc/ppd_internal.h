@@ -62,6 +62,7 @@ constexpr int kWaveTileKeys = PPD_WAVE_TILE_KEYS;  // a narrow tile of at most t
 // workgroups of the mixed / row-block kernel and of the stream kernel), then the queue cursors, each in a
 // 128-byte line of its own (claims on different queues then do not queue up behind one another at one address
 // range of the memory side, where device-scope atomics execute).
+constexpr int kUploadWord = 12;    // finished workgroups of the plan upload
 constexpr int kCursorBase = 64;    // word index of cursor 0
 constexpr int kCursorStride = 32;  // words between cursors
 constexpr int kCounterWords = kCursorBase + kCursors * kCursorStride;
