@@ -43,3 +43,43 @@ def test_plans_follow_one_another_through_the_staging_buffers():
     for b, (_, out) in zip(steps, outs):
         check_close(bits_to_f32(from_dev_u16(out).reshape(b.T, b.Hq, b.D)), oracle_out(b, pool_bits))
     ctx.close()
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("D,Hkv,T,layers", [(128, 8, 1023, 1), (128, 8, 1025, 1), (64, 8, 1021, 1), (64, 2, 1031, 4), (128, 1, 7, 1)])
+def test_append_on_both_sides_of_its_token_split(D, Hkv, T, layers, fp8):
+    """8 or 16 tokens per workgroup by T * Hkv * layers (the line is 8192): runs of every length from every offset, with
+    skipped tokens, and a batch end inside a workgroup; every byte of the pools against the oracle."""
+    import oracle
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    rng = np.random.default_rng(T + D)
+    slots, page = [], 0
+    while len(slots) < T:
+        run, off = int(rng.integers(1, 60)), int(rng.integers(0, 16))
+        s = page * 16 + off + np.arange(run)
+        s[rng.random(run) < 0.03] = -1
+        slots.extend(s.tolist())
+        page += (off + run + 15) // 16
+    slots = np.asarray(slots[:T], np.int64)
+    num_pages = page + 1
+    k, v = (si.normal_bf16(rng, (layers, T, Hkv, D)) for _ in range(2))
+    per = oracle.pool_elems(num_pages, Hkv, D, 16)
+    ref = np.full((layers, per), 0x5A, np.uint8 if fp8 else np.uint16)
+    for i in range(layers):
+        if fp8:
+            oracle.kv_append_fp8(k[i], v[i], ref[i], slots, Hkv, D, 16, num_pages, 0.02, 0.05)
+        else:
+            oracle.kv_append(k[i], v[i], ref[i], slots, Hkv, D, 16, num_pages)
+    dev = torch.device("cuda:0")
+    ctx = ppd.Context(2 * Hkv, Hkv, D, num_pages)
+    if fp8:
+        ctx.set_kv_format(ppd.PPD_KV_FP8_E4M3, 0.02, 0.05)
+    pools = torch.full((layers, per), 0x5A, dtype=torch.uint8 if fp8 else torch.int16, device=dev)
+    ctx.kv_land(to_dev_u16(k, torch, dev), to_dev_u16(v, torch, dev), pools, per, layers, torch.from_numpy(slots).to(dev))
+    torch.cuda.synchronize()
+    assert ctx.device_error_flags() == 0
+    got = pools.cpu().numpy()
+    assert np.array_equal(got if fp8 else got.view(np.uint16), ref)
+    ctx.close()
