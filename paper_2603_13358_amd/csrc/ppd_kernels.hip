@@ -71,6 +71,7 @@ __device__ __forceinline__ float sum_halves(float v) {
 #ifndef kLazyRescale
 #define kLazyRescale 8.0f
 #endif
+constexpr float kMaxLazyP = 256.0f;  // 2^kLazyRescale
 
 // Raw page-table entry of logical page `pi` of a sequence; pi is clamped so that no access leaves the page
 // table row.  The value is NOT inspected here: a caller that prefetches it must not wait for the load.
@@ -299,14 +300,15 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
     const char* const pool_k = reinterpret_cast<const char*>(P.pool) + head_off * EB;  // this KV head's K block of page 0
     const char* const pool_v = pool_k + v_off * EB;                                    // ... and its V block
     const uint32_t smem_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)smem) + (uint32_t)wave * 1024u;
-    auto load_block = [&](const TilePages& t, int lds_byte, bool is_v) {
+    auto load_round = [&](const TilePages& t, int r, int lds_byte, bool is_v) {
         if (!loader) return;
+        const uint64_t off = FP8 ? (uint64_t)t.lo[r] * page_bytes : (((uint64_t)t.hi[r] << 32) | t.lo[r]);
+        const char* base = (is_v ? pool_v : pool_k) + off;
+        lds_direct_load16_at(base, lane_off, smem_addr + (uint32_t)(lds_byte + r * (kThreads * 16)));
+    };
+    auto load_block = [&](const TilePages& t, int lds_byte, bool is_v) {
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            const uint64_t off = FP8 ? (uint64_t)t.lo[r] * page_bytes : (((uint64_t)t.hi[r] << 32) | t.lo[r]);
-            const char* base = (is_v ? pool_v : pool_k) + off;
-            lds_direct_load16_at(base, lane_off, smem_addr + (uint32_t)(lds_byte + r * (kThreads * 16)));
-        }
+        for (int r = 0; r < ROUNDS; ++r) load_round(t, r, lds_byte, is_v);
     };
     // FP8: the 16 codes this thread staged at src_byte become two bf16 granules of the operand tile at dst_byte (the
     // element order of a tile is the same in both); V rows of positions >= kv_total were never written and become 0.
@@ -447,17 +449,20 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
         const int sv_nxt = sv_cur + 1 == NSV ? 0 : sv_cur + 1;           // (ti + 1) % NSV
         const int sv_far = ring_add<NSV>(sv_cur, (NS - 1) % NSV);                       // (ti + NS - 1) % NSV
         const bool full_issue = ti + NS < ntiles;
-        if constexpr (FP8) {  // tile t of K or of V is staged in slot t % 2
-            if (ti + NS - 1 < ntiles) load_block(tp_v, STAGE_V + (ti & 1) * LBYTES, true);
-            if (full_issue) load_block(tp_k, STAGE_K + ((ti + 1) & 1) * LBYTES, false);
-        } else {
-            if (ti + NS - 1 < ntiles) load_block(tp_v, VRING + sv_far * KBYTES, true);
-            if (full_issue) load_block(tp_k, st_far * KBYTES, false);
-        }
+        const bool v_issue = ti + NS - 1 < ntiles;
+        // the iteration's loads, one round of K or of V at a time
+        auto issue_round = [&](int j) {
+            const bool is_v = j < ROUNDS;
+            const int r = is_v ? j : j - ROUNDS;
+            if (is_v ? v_issue : full_issue) {
+                const int at = is_v ? (FP8 ? STAGE_V + (ti & 1) * LBYTES : VRING + sv_far * KBYTES)
+                                    : (FP8 ? STAGE_K + ((ti + 1) & 1) * LBYTES : st_far * KBYTES);  // FP8: tile t is staged in slot t % 2
+                load_round(is_v ? tp_v : tp_k, r, at, is_v);
+            }
+        };
         // The V tile of the next iteration is this iteration's K tile; the ids of its K tile are read from LDS
         // now and turned into scalars at the end of the iteration: under the other waves' operand reads that
         // small LDS read takes hundreds of cycles, which nothing waits for this way.
-        tp_v = tp_k;
         const RawPages tp_raw = tile_pages_raw(ti + 1 + NS < ntiles ? ti + 1 + NS : ntiles - 1);
         // K(ti+2) and V(ti+1) must have landed before the barrier; with NS = 3 the loads issued in this iteration
         // may stay in flight
@@ -474,7 +479,6 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
             }
             lds_barrier();
         };
-        float mc = 0.f;
         if (wave_active) {
             const int tile_base = it.kv_begin + ti * kTileTokens;
             if (tile_base + kTileTokens - 1 > wmin_limit) {  // causal boundary crosses this tile
@@ -486,30 +490,11 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
                         if (pos > limit) s_cur[tb][i] = NEG_INF;
                     }
             }
-            float mx = s_cur[0][0];
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s_cur[tb][i]);
-            mx = max_halves(mx);
-            const float m_new = fmaxf(m_run, mx);
-            if (__any((m_new - m_run) * c > kLazyRescale)) {  // -inf -> finite counts; -inf -> -inf does not
-                const float m_use = m_new == NEG_INF ? 0.f : m_new;
-                const float alpha = fast_exp2(m_run * c - m_use * c);  // m_run = -inf gives 0
-                l_run *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
-                m_run = m_new;
-            }
-            mc = m_run == NEG_INF ? 0.f : m_run * c;
             // Vector phase: all exponentials of this tile, packed to bf16 at once.  Nothing for the matrix pipe in
             // it, and nothing for the vector pipe in the matrix phase below, so that the late waves (half an
             // iteration behind) run their matrix phase under this vector phase and the other way round.
             float psum = 0.f;
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
+            auto exponentials = [&](int s, float mc) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int i0 = (s & 1) * 8 + 2 * e;
@@ -518,24 +503,83 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
                     psum += p0 + p1;
                     pw[s][e] = pack_bf16(p0, p1);
                 }
+            };
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                for (int j = s * 2 * ROUNDS / 4; j < (s + 1) * 2 * ROUNDS / 4; ++j) issue_round(j);
+                exponentials(s, m_run * c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // The tile's maximum (17 dependent instructions and a half-wave exchange) is not looked for: the exponentials are taken against the running reference as it is,
+            // and only if a lane's sum of 32 of them is above 32 * 2^kLazyRescale (or not a number: no reference yet, m_run =
+            // -inf) is the maximum found, the accumulators rescaled and the exponentials taken again.
+            if (__any(!(psum <= 32.0f * kMaxLazyP))) {
+                float mx = s_cur[0][0];
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s_cur[tb][i]);
+                mx = max_halves(mx);
+                const float m_new = fmaxf(m_run, mx);
+                const float m_use = m_new == NEG_INF ? 0.f : m_new;
+                const float alpha = fast_exp2(m_run * c - m_use * c);  // m_run = -inf gives 0
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
+                m_run = m_new;
+                psum = 0.f;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) exponentials(s, m_use * c);
+            }
             l_run += psum;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 2 * ROUNDS; ++j) issue_round(j);
         }
+        // The V tile of the next iteration is this iteration's K tile
+        tp_v = tp_k;
         __builtin_amdgcn_sched_barrier(0);
         if (late) close_iteration();
         if (wave_active) {
-            // Matrix phase: O^T += V^T P^T of this tile, then S^T of the next one into the registers the
-            // probabilities have left.
+            // Matrix phase: O^T += V^T P^T of this tile, then S^T of the next one, as one straight run of products whose
+            // operands are read AHEAD of them (after the last tile the S^T of whatever the ring holds, not used).
+            // Clocks per 64-key tile of one unit at full clock: 3515 with a branch between the two products, one
+            // operand pair read at a time and the maximum looked for; 3200 with this run; 3050 without the maximum as well.
+            // The whole chip runs the loop at its power limit (2.0 -> 1.8 GHz), so two full prefills of 8192 went from 1077 to 1014 us.
             const uint32_t vb = lds_base(smem + sv_cur * KBYTES + v_lane_off);
+            const uint32_t kb = lds_base(smem + st_nxt * KBYTES + k_lane_off);
+            constexpr int NPV = 4 * DB, NQK = 2 * KS, NOP = NPV + NQK;
+            constexpr int AHEAD = 4;  // operands read ahead of their product
+            auto operand = [&](int j) {
+                if (j < NPV) return lds_read16(vb, (j / DB) * PB + (j % DB) * 512);
+                return lds_read16(kb, ((j - NPV) % 2) * 2 * PB + ((j - NPV) / 2) * 512);
+            };
+            u32x4 abuf[AHEAD];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const bf16x8 pb = as_bf16x8(pw[s]);
+            for (int j = 0; j < AHEAD; ++j) abuf[j] = operand(j);
 #pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    bf16x8 a = as_bf16x8(lds_read16(vb, s * PB + db * 512));
-                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb, oacc[db], 0, 0, 0);
-                }
+            for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s_cur[tb][i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < NOP; ++j) {
+                const bf16x8 a = as_bf16x8(abuf[j % AHEAD]);
+                if (j < NPV)
+                    oacc[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(pw[j / DB]), oacc[j % DB], 0, 0, 0);
+                else
+                    s_cur[(j - NPV) % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[(j - NPV) / 2], s_cur[(j - NPV) % 2], 0, 0, 0);
+                if (j + AHEAD < NOP) abuf[j % AHEAD] = operand(j + AHEAD);
             }
-            if (ti + 1 < ntiles) qk_tile(st_nxt, s_cur);
+            __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+#pragma unroll
+            for (int j = 0; j < NOP - AHEAD; ++j) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (!late) close_iteration();

@@ -83,3 +83,17 @@ def test_append_on_both_sides_of_its_token_split(D, Hkv, T, layers, fp8):
     got = pools.cpu().numpy()
     assert np.array_equal(got if fp8 else got.view(np.uint16), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,chunk", [(128, 0), (128, 64), (64, 192)])
+@pytest.mark.parametrize("q_std", [0.5, 6.0, 40.0])
+def test_row_block_reference_is_raised_and_found(D, chunk, q_std):
+    """Row-block tiles look for a maximum only when a sum of exponentials grows past a bound or no reference exists: flat
+    scores (never after the first tile), scores that grow by far more than the bound, and splits of 64 keys on the causal
+    edge, where some columns see no key of the split's first tile."""
+    b = si.make_batch("reference", L=[1000, 0, 70, 333], n=[70, 300, 130, 61], Hq=8, Hkv=2, D=D, seed=int(q_std * 10) + D,
+                      q_std=q_std, slack_pages=3)
+    _, out, stats = gpu_step(b, options={"mfma_chunk": chunk} if chunk else None)
+    assert stats["n_mfma"] > 0
+    # peaky rows give back single values: bf16 rounds a probability and the result by at most 2^-8 of their size each
+    check_close(bits_to_f32(out), oracle_out(b), max_abs=2.0 ** -7 * float(np.abs(bits_to_f32(b.v)).max()))
