@@ -701,20 +701,44 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
     }
     // epilogue: O^T register i of block db is d = db*32 + (i/4)*8 + h*4 + i%4 of column `col`
     const float l_tot = sum_halves(l_run);
-    if (col < ncols) {
-        if (it.part_off < 0) {
-            const float inv = P.v_scale / l_tot;
-            uint16_t* op = P.out + ((int64_t)(it.grow0 + jrow) * P.Hq + head) * HD + h * 4;
+    if (it.part_off < 0) {
+        // A lane holds 8-byte pieces of 32 different result rows: stored from here, every instruction would touch 32
+        // lines.  Each wave turns its 32 columns round in LDS of its own, half a row at a time, and writes
+        // whole lines.  The space is the K ring's: no load is in flight, and what the late waves may still read there
+        // (the S^T after the last tile) is not used.  2048 row blocks of one 64-key tile (8 to a workgroup, a block is 64
+        // KiB of results): 111 -> 90 us.
+        constexpr int RS = HD + 16;       // bytes of a staged half row: 16 of padding spread the columns over the banks
+        constexpr int LPR = HD / 16;      // lanes that store a half row, 16 bytes each
+        static_assert(kWaves * 32 * RS <= NSK * KBYTES, "the staged columns fit the K ring");
+        char* const stage = smem + wave * (32 * RS);
+        char* const out0 = reinterpret_cast<char*>(P.out) + ((int64_t)it.grow0 * P.Hq + it.kvh * G) * (HD * 2);
+        const float inv = P.v_scale / l_tot;
+        if (wave_active) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int half = 0; half < 2; ++half) {
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    u32x2 w;
-                    w[0] = pack_bf16(oacc[db][i4 * 4 + 0] * inv, oacc[db][i4 * 4 + 1] * inv);
-                    w[1] = pack_bf16(oacc[db][i4 * 4 + 2] * inv, oacc[db][i4 * 4 + 3] * inv);
-                    *reinterpret_cast<u32x2*>(op + db * 32 + i4 * 8) = w;
+                for (int db = half * (DB / 2); db < (half + 1) * (DB / 2); ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        u32x2 w;
+                        w[0] = pack_bf16(oacc[db][i4 * 4 + 0] * inv, oacc[db][i4 * 4 + 1] * inv);
+                        w[1] = pack_bf16(oacc[db][i4 * 4 + 2] * inv, oacc[db][i4 * 4 + 3] * inv);
+                        *reinterpret_cast<u32x2*>(stage + l32 * RS + ((db - half * (DB / 2)) * 32 + i4 * 8 + h * 4) * 2) = w;
+                    }
+                asm volatile("" ::: "memory");  // a wave's LDS operations run in order
+#pragma unroll
+                for (int r = 0; r < 32 * LPR / 64; ++r) {
+                    const int c32 = r * (64 / LPR) + lane / LPR, ocol = wave * 32 + c32;
+                    const u32x4 w = *reinterpret_cast<const u32x4*>(stage + c32 * RS + (lane % LPR) * 16);
+                    const int orow = col_row(ocol, P.invG);
+                    const uint32_t off = (uint32_t)(orow * (P.Hq - G) + ocol) * (HD * 2) + (lane % LPR) * 16;  // a block's rows span at most 2 GiB
+                    if (ocol < ncols) *reinterpret_cast<u32x4*>(out0 + half * HD + off) = w;
                 }
-        } else {
+                asm volatile("" ::: "memory");
+            }
+        }
+    } else {
+        if (col < ncols) {
             float* pp = P.partials + it.part_off;
             float* po = pp + (int64_t)col * HD + h * 4;
 #pragma unroll

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import oracle
 import synthetic_inputs as si
 from gpu_helpers import from_dev_u16, gpu_step, to_dev_u16
 from helpers import bits_to_f32, check_close, oracle_out, oracle_pool
@@ -97,3 +98,38 @@ def test_row_block_reference_is_raised_and_found(D, chunk, q_std):
     assert stats["n_mfma"] > 0
     # peaky rows give back single values: bf16 rounds a probability and the result by at most 2^-8 of their size each
     check_close(bits_to_f32(out), oracle_out(b), max_abs=2.0 ** -7 * float(np.abs(bits_to_f32(b.v)).max()))
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 8, 128), (10, 2, 128), (8, 1, 128), (6, 2, 64), (7, 1, 64)])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_row_block_results_leave_whole_lines(Hq, Hkv, D, fp8):
+    """A wave writes its 32 columns through LDS, half a row at a time: row blocks that end one column into a wave, at its
+    edge and inside it, for group sizes that divide 32 and that do not; what surrounds the result stays as it was."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    G = Hq // Hkv
+    n = [17, 32 // G + 1, 256 // G, 256 // G + 1, 2 * (256 // G) - 1, 33]
+    n = [max(x, 16 // G + 1) for x in n]
+    b = si.make_batch("lines", L=[5, 0, 100, 64, 31, 0], n=n, Hq=Hq, Hkv=Hkv, D=D, seed=Hq * D, slack_pages=3)
+    dev = torch.device("cuda:0")
+    ctx = ppd.Context(Hq, Hkv, D, b.num_pages)
+    if fp8:
+        ctx.set_kv_format(ppd.PPD_KV_FP8_E4M3, 0.0173, 0.0421)
+        pool = torch.zeros(ctx.pool_elems(), dtype=torch.uint8, device=dev)
+    else:
+        pool = torch.zeros(ctx.pool_elems(), dtype=torch.int16, device=dev)
+    for k, v, slots in (b.cached_part(), b.new_part()):
+        ctx.kv_append(to_dev_u16(k, torch, dev), to_dev_u16(v, torch, dev), pool, torch.from_numpy(slots.astype(np.int64)).to(dev))
+    rows = torch.full((b.T + 2, Hq, D), 0x7A5A, dtype=torch.int16, device=dev)
+    ctx.mixed_attention(to_dev_u16(b.q, torch, dev), pool, torch.from_numpy(b.page_tables).to(dev), b.L, b.n, b.scale, rows[1:])
+    torch.cuda.synchronize()
+    assert ctx.device_error_flags() == 0 and ctx.plan_stats().as_dict()["n_mfma"] > 0
+    got = from_dev_u16(rows)
+    assert (got[0] == 0x7A5A).all() and (got[-1] == 0x7A5A).all()
+    want = oracle_out(b)
+    if fp8:  # the oracle reads the codes the append wrote
+        want = oracle.mixed_attention_fp8(b.q, pool.cpu().numpy(), 0.0173, 0.0421, b.page_tables, b.L, b.n, Hq, Hkv, D, b.P,
+                                          b.num_pages, b.scale)
+    check_close(bits_to_f32(got[1:-1]), want)
+    ctx.close()
