@@ -133,3 +133,18 @@ def test_row_block_results_leave_whole_lines(Hq, Hkv, D, fp8):
                                           b.num_pages, b.scale)
     check_close(bits_to_f32(got[1:-1]), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("B_narrow,B_rows,wave", [(1, 1, -1), (3, 9, -1), (9, 2, -1), (30, 25, -1), (30, 25, 1), (31, 33, -1), (32, 33, -1)])
+def test_mixed_launch_with_a_workgroup_for_every_tile(B_narrow, B_rows, wave):
+    """Up to 256 tiles are taken by workgroup index (8 to 256 here), more (260) are claimed: row blocks in few and in all
+    of the eight queues, one and several per sharing group, wave tiles, and the same call with one workgroup."""
+    rng = np.random.default_rng(B_narrow * 100 + B_rows)
+    L = np.concatenate([rng.integers(0, 500, B_narrow), rng.integers(0, 300, B_rows)])
+    n = np.concatenate([np.ones(B_narrow, np.int64), rng.integers(17, 150, B_rows)])
+    b = si.make_batch("own", L=L, n=n, Hq=4, Hkv=4, D=64, seed=B_rows, slack_pages=3)
+    _, out, stats = gpu_step(b, options={"wave_tiles": wave})
+    assert stats["n_mfma"] == 4 * B_rows and stats["n_narrow"] == 4 * B_narrow
+    check_close(bits_to_f32(out), oracle_out(b))
+    _, claimed, _ = gpu_step(b, options={"wave_tiles": wave, "grid": 1})
+    assert np.array_equal(out, claimed)
