@@ -106,6 +106,14 @@ def _host_i32(a):
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
+def _host_ptr(a):
+    """Address of a contiguous host array's first element."""
+    try:
+        return ctypes.addressof(ctypes.c_char.from_buffer(a))  # a fifth of the time of a.ctypes.data
+    except (TypeError, ValueError):  # read-only or empty
+        return a.ctypes.data
+
+
 def _check(status, ctx=None):
     if status != 0:
         raise PPDError(status, ppd_last_error(ctx))
@@ -167,8 +175,8 @@ def ppd_mixed_attention(ctx, q, kv_pages, page_tables, L, n, scale, out, max_pag
         max_pages = int(page_tables.shape[1])
     lib = load_library()
     fn = lib.ppd_mixed_attention_static if static else lib.ppd_mixed_attention
-    _check(fn(ctx, _dev_ptr(q), _dev_ptr(kv_pages), _dev_ptr(page_tables), int(max_pages), L.ctypes.data,
-              n.ctypes.data, int(L.shape[0]), float(scale), _dev_ptr(out), stream), ctx)
+    _check(fn(ctx, _dev_ptr(q), _dev_ptr(kv_pages), _dev_ptr(page_tables), int(max_pages), _host_ptr(L),
+              _host_ptr(n), int(L.shape[0]), float(scale), _dev_ptr(out), stream), ctx)
 
 
 def ppd_mixed_attention_static(ctx, q, kv_pages, page_tables, L, n, scale, out, max_pages=None, stream=None):
