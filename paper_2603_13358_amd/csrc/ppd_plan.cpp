@@ -62,8 +62,11 @@ struct RowBlock { int64_t vis_end; int32_t nrows; };
 
 // Compute units (of the 32 of an XCD) whose workgroups take narrow tiles first.  A workgroup of the mixed kernel
 // fills a compute unit (8 waves of up to 256 registers), so the two kinds are split by physical unit.  Narrow tiles are bound by the bytes a unit keeps in flight (about 45 GB/s each), MFMA tiles
-// by compute (about 2.3 us per 64 keys of a row block): the split is sized so that both kinds finish together;
-// whoever finishes first steals from the other anyway.
+// by compute (about 1.5 us per 64 keys of a row block, 2.3 on FP8 pages, which are converted on the way): the split is sized so
+// that both kinds finish together; whoever finishes first steals from the other anyway.  Swept over seven mixed steps on
+// bf16 pages the best split lay within two units of this one and 2.3 us cost 1-4 % (60 decodes beside 4 turns, 64 query heads,
+// 16 -> 18 units: 358 -> 346 us; 128 long decodes beside 4 long turns, 14 -> 18: 3249 -> 3133 us a layer pair); on FP8 pages
+// 2.3 is within 1 % of the best.
 // A unit streams FP8 pages at about 38 GB/s: its loads are 8 bytes per lane instead of 16 and 8, and a unit's memory
 // pipeline moves fewer bytes per second with narrower loads (about 58 GB/s at best, with contiguous 16-byte loads).
 static double unit_bytes_per_us(int elem_bytes) { return elem_bytes == 1 ? 38e3 : 45e3; }
@@ -72,7 +75,7 @@ static int narrow_units(double narrow_bytes, double mfma_iters, int elem_bytes) 
     if (narrow_bytes == 0) return 0;
     if (mfma_iters == 0) return 32;
     const double narrow_cu_us = narrow_bytes / unit_bytes_per_us(elem_bytes);  // CU-microseconds
-    const double mfma_us = mfma_iters * 2.3 / kWgPerCu;
+    const double mfma_us = mfma_iters * (elem_bytes == 1 ? 2.3 : 1.5) / kWgPerCu;
     const int cus = (int)std::lround(32.0 * narrow_cu_us / (narrow_cu_us + mfma_us));
     return std::min(std::max(cus, 2), 20);            // HBM saturates well before all units stream
 }
