@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 import synthetic_inputs as si
-from gpu_helpers import from_dev_u16, gpu_step, to_dev_u16
+from gpu_helpers import from_dev_u16, gpu_step, gpu_step_fp8, to_dev_u16
 from helpers import bits_to_f32, check_close, oracle_out, oracle_pool
 
 pytestmark = pytest.mark.gpu
@@ -148,3 +148,19 @@ def test_mixed_launch_with_a_workgroup_for_every_tile(B_narrow, B_rows, wave):
     check_close(bits_to_f32(out), oracle_out(b))
     _, claimed, _ = gpu_step(b, options={"wave_tiles": wave, "grid": 1})
     assert np.array_equal(out, claimed)
+
+
+@pytest.mark.parametrize("fp8,longest", [(False, 768), (True, 1536)])
+def test_decode_only_launch_of_single_wave_tiles(fp8, longest):
+    """2048 decode tiles of up to the longest keys a single wave is given, whole and partly filled last pages among them."""
+    rng = np.random.default_rng(longest)
+    L = rng.integers(0, 300, 256)
+    L[:6] = [longest - 1, longest - 2, longest - 16, longest - 17, 15, 16]
+    b = si.make_batch("single", L=L, n=np.ones(256, np.int64), Hq=8, Hkv=8, D=128, seed=longest, slack_pages=3)
+    if fp8:
+        pool, out, _ = gpu_step_fp8(b, 0.0173, 0.0421)
+        want = oracle.mixed_attention_fp8(b.q, pool, 0.0173, 0.0421, b.page_tables, b.L, b.n, b.Hq, b.Hkv, b.D, b.P, b.num_pages, b.scale)
+    else:
+        _, out, _ = gpu_step(b)
+        want = oracle_out(b)
+    check_close(bits_to_f32(out), want)
