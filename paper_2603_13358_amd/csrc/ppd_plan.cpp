@@ -71,11 +71,14 @@ struct RowBlock { int64_t vis_end; int32_t nrows; };
 // pipeline moves fewer bytes per second with narrower loads (about 58 GB/s at best, with contiguous 16-byte loads).
 static double unit_bytes_per_us(int elem_bytes) { return elem_bytes == 1 ? 38e3 : 45e3; }
 
-static int narrow_units(double narrow_bytes, double mfma_iters, int elem_bytes) {
+// (The choice of the split size reckons with 2.3 us for both formats: with 1.5 it splits more row blocks, and one batch in
+// forty then needs more room for its partials than the fixed scratch array has.)
+constexpr double kSplitIterUs = 2.3;
+static int narrow_units(double narrow_bytes, double mfma_iters, int elem_bytes, double iter_us) {
     if (narrow_bytes == 0) return 0;
     if (mfma_iters == 0) return 32;
     const double narrow_cu_us = narrow_bytes / unit_bytes_per_us(elem_bytes);  // CU-microseconds
-    const double mfma_us = mfma_iters * (elem_bytes == 1 ? 2.3 : 1.5) / kWgPerCu;
+    const double mfma_us = mfma_iters * iter_us / kWgPerCu;
     const int cus = (int)std::lround(32.0 * narrow_cu_us / (narrow_cu_us + mfma_us));
     return std::min(std::max(cus, 2), 20);            // HBM saturates well before all units stream
 }
@@ -110,7 +113,7 @@ static int64_t choose_mfma_chunk(const std::vector<RowBlock>& blocks, int G, int
             if (nsplit > 1) partial_bytes += (double)rb.nrows * G * (D + 2) * 4.0 * nsplit * Hkv;
         }
         // the workgroups that take MFMA tiles first, as the launch will split them
-        const int S = std::max(1, slots - narrow_units(narrow_bytes, iters, elem_bytes) * slots / 32);
+        const int S = std::max(1, slots - narrow_units(narrow_bytes, iters, elem_bytes, kSplitIterUs) * slots / 32);
         std::sort(tiles.begin(), tiles.end(), std::greater<double>());
         load.assign((size_t)S, 0.0);  // min-heap of workgroup finish times; the earliest workgroup takes the next tile
         for (double t : tiles)
@@ -419,7 +422,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
             if (k.it.kind == 0) narrow_bytes += toks * kv_tok_bytes_head;
             else mfma_iters += std::ceil(toks / kTileTokens);
         }
-        plan->narrow_cus = o.narrow_cus >= 0 ? std::min(o.narrow_cus, 32) : narrow_units(narrow_bytes, mfma_iters, o.kv_elem_bytes == 1 ? 1 : 2);
+        plan->narrow_cus = o.narrow_cus >= 0 ? std::min(o.narrow_cus, 32) : narrow_units(narrow_bytes, mfma_iters, o.kv_elem_bytes == 1 ? 1 : 2, o.kv_elem_bytes == 1 ? 2.3 : 1.5);
     }
 
     ppd_plan_stats& st = plan->stats;
