@@ -50,7 +50,7 @@ struct ppd_ctx {
     size_t d_partials_floats = 0;
     uint32_t* d_counters = nullptr;  // kCounterWords words: error flags, finished-workgroup counts, queue cursors
     Staging staging[kStagingSlots];
-    uint32_t* staging_flags = nullptr;  // pinned: the words the slots' `read` point at
+    uint32_t* staging_flags = nullptr;  // pinned, behind static_staging: the words the slots' `read` point at
     int next_slot = 0;
     // the plan on the device stays valid while L, n and the planner options do not change (the layers of one
     // engine step call with the same lengths): such calls skip planning and upload
@@ -501,8 +501,11 @@ ppd_status ppd_create(const ppd_shape* shape, int32_t device, ppd_ctx** out) {
     const size_t counter_bytes = ppd::kCounterWords * sizeof(uint32_t);
     if ((e = hipMalloc((void**)&ctx->d_counters, counter_bytes)) != hipSuccess) return bail(e, "hipMalloc(counters)");
     if ((e = hipMemset(ctx->d_counters, 0, counter_bytes)) != hipSuccess) return bail(e, "hipMemset(counters)");
-    if ((e = hipHostMalloc((void**)&ctx->staging_flags, (kStagingSlots + 1) * kStagingFlagStride * sizeof(uint32_t), kStagingFlags)) != hipSuccess)
-        return bail(e, "hipHostMalloc(staging flags)");
+    // the staging buffer of the entry point that allocates nothing, and behind it the flags of all staging buffers
+    if ((e = hipHostMalloc(&ctx->static_staging.host, kStaticPlanBytes + (kStagingSlots + 1) * kStagingFlagStride * sizeof(uint32_t), kStagingFlags)) != hipSuccess)
+        return bail(e, "hipHostMalloc(static staging)");
+    ctx->static_staging.bytes = kStaticPlanBytes;
+    ctx->staging_flags = reinterpret_cast<uint32_t*>(static_cast<char*>(ctx->static_staging.host) + kStaticPlanBytes);
     for (int i = 0; i <= kStagingSlots; ++i) {
         Staging& s = i < kStagingSlots ? ctx->staging[i] : ctx->static_staging;
         s.read = ctx->staging_flags + i * kStagingFlagStride;
@@ -513,14 +516,11 @@ ppd_status ppd_create(const ppd_shape* shape, int32_t device, ppd_ctx** out) {
     if ((e = hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
     if ((e = hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
     // everything ppd_mixed_attention_static needs is set up here, so that the call itself allocates nothing: the
-    // device address of this GPU's scratch array and a pinned staging buffer for the plan upload
+    // device address of this GPU's scratch array and (above) a pinned staging buffer for the plan upload
     {
         unsigned char* sp = nullptr;
         if ((e = static_scratch_address(device, &sp)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
     }
-    if ((e = hipHostMalloc(&ctx->static_staging.host, kStaticPlanBytes, kStagingFlags)) != hipSuccess)
-        return bail(e, "hipHostMalloc(static staging)");
-    ctx->static_staging.bytes = kStaticPlanBytes;
     const char* env = std::getenv("PPD_LOG");
     ctx->log_calls = env && env[0] == '1';
     env = std::getenv("PPD_DEBUG_SLOTS");
@@ -551,8 +551,7 @@ ppd_status ppd_destroy(ppd_ctx* ctx) {
     if (ctx->side_stream) (void)hipStreamDestroy(ctx->side_stream);
     if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
     if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
-    if (ctx->static_staging.host) (void)hipHostFree(ctx->static_staging.host);
-    if (ctx->staging_flags) (void)hipHostFree(ctx->staging_flags);
+    if (ctx->static_staging.host) (void)hipHostFree(ctx->static_staging.host);  // and the flags behind it
     {
         std::lock_guard<std::mutex> lock(g_scratch_mutex);
         if (ctx->device >= 0 && ctx->device < kMaxDevices && g_scratch_owner[ctx->device] == ctx)
