@@ -322,12 +322,21 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
             std::memcpy(static_cast<char*>(host) + items_bytes + groups_bytes, plan.units.data(), units_bytes);
         }
         std::memcpy(static_cast<char*>(host) + total - bounds_bytes, plan.queue_begin, bounds_bytes);
-        const int64_t granules = (int64_t)((total + 15) / 16);
-        hipLaunchKernelGGL(ppd_upload_kernel, dim3((unsigned)((granules + kUploadThreads - 1) / kUploadThreads)), dim3(kUploadThreads), 0, hs,
-                           static_cast<const uint4*>(host), static_cast<uint4*>(use_static ? d_plan : ctx->d_items), granules,
-                           ctx->d_counters, const_cast<uint32_t*>(sg.read), sg.serial + 1);
-        PPD_HIP(ctx, hipGetLastError());
-        sg.serial += 1;
+        // What the upload overwrites stops counting as resident before it is launched, and the launch's own status decides: an
+        // error that an earlier call left pending does not undo an upload that is under way.
+        const uint4* src = static_cast<const uint4*>(host);
+        uint4* dst = static_cast<uint4*>(use_static ? d_plan : ctx->d_items);
+        int64_t granules = (int64_t)((total + 15) / 16);
+        uint32_t* read = const_cast<uint32_t*>(sg.read);
+        uint32_t serial = ++sg.serial;
+        if (use_static) g_scratch_owner[ctx->device] = nullptr;
+        void* args[] = {&src, &dst, &granules, &ctx->d_counters, &read, &serial};
+        const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&ppd_upload_kernel),
+                                             dim3((unsigned)((granules + kUploadThreads - 1) / kUploadThreads)), dim3(kUploadThreads), args, 0, hs);
+        if (e != hipSuccess) {
+            sg.serial -= 1;  // nothing was enqueued: the buffer is free
+            return hip_fail(ctx, e, "launch plan upload");
+        }
         if (use_static) g_scratch_owner[ctx->device] = ctx;
         ctx->plan_L.assign(L, L + B);
         ctx->plan_n.assign(n, n + B);
