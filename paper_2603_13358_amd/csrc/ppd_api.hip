@@ -124,6 +124,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // it is only a stand-in): the device address is asked for once per device and kept in g_scratch_ptr.
 constexpr size_t kStaticCounterBytes = 4096;
 constexpr size_t kStaticPlanBytes = (size_t(2) << 20) - kStaticCounterBytes;
+static_assert(kStaticPlanBytes % 16 == 0, "a plan's last 16 bytes fit");
 constexpr size_t kStaticPartialBytes = PPD_STATIC_SCRATCH_BYTES - (size_t(2) << 20);
 static_assert(ppd::kCounterWords * sizeof(uint32_t) <= kStaticCounterBytes, "counters fit their slot");
 static __device__ __align__(256) unsigned char scratch[PPD_STATIC_SCRATCH_BYTES];
@@ -274,10 +275,11 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     const size_t units_bytes = plan.units.size() * sizeof(ppd::MergeUnit);
     const size_t bounds_bytes = sizeof plan.queue_begin;  // the queues' bounds travel behind the tables
     const size_t total = items_bytes + groups_bytes + units_bytes + bounds_bytes;
+    const size_t upload_bytes = (total + 15) / 16 * 16;  // the upload moves 16 bytes per lane: both buffers hold this much
     unsigned char* sbase = nullptr;
     if (use_static) {
         PPD_HIP(ctx, static_scratch_address(ctx->device, &sbase));
-        if (total > kStaticPlanBytes || (size_t)plan.stats.partial_floats * sizeof(float) > kStaticPartialBytes)
+        if (upload_bytes > kStaticPlanBytes || (size_t)plan.stats.partial_floats * sizeof(float) > kStaticPartialBytes)
             return fail(ctx, PPD_ERR_WORKSPACE,
                         "batch too large for the static scratch array: plan " + std::to_string(total) + " of " +
                             std::to_string(kStaticPlanBytes) + " bytes, split partials " +
@@ -292,11 +294,11 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         if (st != PPD_OK) return st;
         if (!use_static) {
             ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
-            if (sg.bytes < total) {
+            if (sg.bytes < upload_bytes) {
                 if (sg.host) PPD_HIP(ctx, hipHostFree(sg.host));
                 sg.host = nullptr;
                 sg.bytes = 0;
-                const size_t want = total + total / 4 + 4096;
+                const size_t want = upload_bytes + upload_bytes / 4 + 4096;
                 if (hipHostMalloc(&sg.host, want, kStagingFlags) != hipSuccess) {
                     (void)hipGetLastError();
                     sg.host = nullptr;
@@ -304,7 +306,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
                 }
                 sg.bytes = want;
             }
-            st = grow_device(ctx, &ctx->d_items, &ctx->d_items_bytes, total, hs);
+            st = grow_device(ctx, &ctx->d_items, &ctx->d_items_bytes, upload_bytes, hs);
             if (st != PPD_OK) return st;
             {
                 void* p = ctx->d_partials;
@@ -322,11 +324,12 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
             std::memcpy(static_cast<char*>(host) + items_bytes + groups_bytes, plan.units.data(), units_bytes);
         }
         std::memcpy(static_cast<char*>(host) + total - bounds_bytes, plan.queue_begin, bounds_bytes);
+        std::memset(static_cast<char*>(host) + total, 0, upload_bytes - total);
         // What the upload overwrites stops counting as resident before it is launched, and the launch's own status decides: an
         // error that an earlier call left pending does not undo an upload that is under way.
         const uint4* src = static_cast<const uint4*>(host);
         uint4* dst = static_cast<uint4*>(use_static ? d_plan : ctx->d_items);
-        int64_t granules = (int64_t)((total + 15) / 16);
+        int64_t granules = (int64_t)(upload_bytes / 16);
         uint32_t* read = const_cast<uint32_t*>(sg.read);
         uint32_t serial = ++sg.serial;
         if (use_static) g_scratch_owner[ctx->device] = nullptr;

@@ -131,6 +131,38 @@ static void failed_launch(bool use_static) {
     finish(ctx);
 }
 
+// Plans that just fit the buffers of an earlier one: the upload moves 16 bytes per lane and a plan is any multiple of 4.
+static void sizes_that_just_fit() {
+    for (int first : {3, 50, 292}) {
+        const int bytes = first * (int)sizeof(ppd_work_item) + (int)sizeof(ppd::Plan::queue_begin);
+        const int fits = (bytes + bytes / 4 + 4096 - (int)sizeof(ppd::Plan::queue_begin)) / (int)sizeof(ppd_work_item);
+        // on the device: the second plan fills what the first one allocated
+        ppd_ctx* ctx = make_ctx();
+        CHECK(step(ctx, first, 40) == PPD_OK);
+        for (int tiles = fits - 1; tiles <= fits + 1; ++tiles) {
+            CHECK(step(ctx, tiles, 41) == PPD_OK);
+            sim.null_stream.run();
+        }
+        finish(ctx);
+        // in the staging buffer: the device buffer has grown in between, then the first staging buffer is used again
+        for (int tiles = fits - 1; tiles <= fits + 1; ++tiles) {
+            ctx = make_ctx();
+            CHECK(step(ctx, first, 40) == PPD_OK);
+            for (int k = 1; k < kStagingSlots; ++k) CHECK(step(ctx, 4 * fits, 50 + k) == PPD_OK);
+            sim.null_stream.run();
+            CHECK(step(ctx, tiles, 60) == PPD_OK);
+            finish(ctx);
+        }
+    }
+    std::mt19937 rng(5);
+    ppd_ctx* ctx = make_ctx();
+    for (int k = 0; k < 400; ++k) {
+        CHECK(step(ctx, 1 + (int)(rng() % (1 + 2 * k)), k) == PPD_OK);
+        sim.null_stream.run();
+    }
+    finish(ctx);
+}
+
 int main(int argc, char** argv) {
     (void)argc;
     const std::string what = argv[1];
@@ -139,6 +171,7 @@ int main(int argc, char** argv) {
         pending_error(true);
     }
     if (what == "two_contexts") pending_error_and_two_contexts();
+    if (what == "sizes") sizes_that_just_fit();
     if (what == "failed_launch") {
         failed_launch(false);
         failed_launch(true);
