@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -30,7 +31,7 @@ constexpr size_t kMaxTimedLaunches = 4096;
 struct Staging {
     void* host = nullptr;  // pinned, mapped
     size_t bytes = 0;
-    volatile uint32_t* read = nullptr;
+    uint32_t* read = nullptr;  // written by the device
     uint32_t serial = 0;
 };
 
@@ -162,7 +163,7 @@ __global__ void ppd_clear_counters_kernel(uint32_t* counters) {
 // Measured: 13-15 us less per new plan (a decode step of 64 sequences at 1K-8K over two layers 433 -> 418 us, an
 // append-prefill of 16 and the decode step after it 816 -> 793 us).
 // One workgroup moves 16 KiB (16 B per lane, every read issued at once); the last one to finish (counted in word
-// `done_word`, which it re-arms) writes the serial number.
+// kUploadWord of the counters, which it re-arms) writes the serial number.
 constexpr int kUploadThreads = 1024;
 __global__ __launch_bounds__(kUploadThreads) void ppd_upload_kernel(const uint4* host, uint4* dev, int64_t granules, uint32_t* counters,
                                                                     uint32_t* read, uint32_t serial) {
@@ -178,12 +179,16 @@ __global__ __launch_bounds__(kUploadThreads) void ppd_upload_kernel(const uint4*
     }
 }
 
-// Waits until the upload that last used a staging buffer has read it.
-ppd_status wait_staging_read(ppd_ctx* ctx, const Staging& sg) {
-    for (int spin = 0; spin < 1 << 14; ++spin)
-        if (*sg.read == sg.serial) return PPD_OK;
-    PPD_HIP(ctx, hipDeviceSynchronize());
-    return PPD_OK;
+// Waits until the upload that last used a staging buffer has read it.  That upload alone: a host that runs ahead of the
+// device must neither wait for the layers enqueued behind it nor for other streams, and synchronising is not allowed while
+// a stream of the process is being captured.  An upload is always launched before its serial number counts here, so the
+// flag arrives as soon as the work in front of it on its stream is done.
+void wait_staging_read(const Staging& sg) {
+    int spins = 0;
+    while (__atomic_load_n(sg.read, __ATOMIC_ACQUIRE) != sg.serial) {
+        if (spins < 1 << 10) ++spins;
+        else std::this_thread::yield();
+    }
 }
 
 // Debugging aid (PPD_DEBUG_SLOTS=1): marks every slot of an append in a bitmap; a bit found set already is a
@@ -290,8 +295,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     if (!reuse) {
         // upload: [items][groups][units] through pinned staging
         Staging& sg = use_static ? ctx->static_staging : ctx->staging[ctx->next_slot];
-        st = wait_staging_read(ctx, sg);
-        if (st != PPD_OK) return st;
+        wait_staging_read(sg);
         if (!use_static) {
             ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
             if (sg.bytes < upload_bytes) {
@@ -330,10 +334,9 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         const uint4* src = static_cast<const uint4*>(host);
         uint4* dst = static_cast<uint4*>(use_static ? d_plan : ctx->d_items);
         int64_t granules = (int64_t)(upload_bytes / 16);
-        uint32_t* read = const_cast<uint32_t*>(sg.read);
         uint32_t serial = ++sg.serial;
         if (use_static) g_scratch_owner[ctx->device] = nullptr;
-        void* args[] = {&src, &dst, &granules, &ctx->d_counters, &read, &serial};
+        void* args[] = {&src, &dst, &granules, &ctx->d_counters, &sg.read, &serial};
         const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&ppd_upload_kernel),
                                              dim3((unsigned)((granules + kUploadThreads - 1) / kUploadThreads)), dim3(kUploadThreads), args, 0, hs);
         if (e != hipSuccess) {

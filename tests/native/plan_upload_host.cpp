@@ -163,6 +163,23 @@ static void sizes_that_just_fit() {
     finish(ctx);
 }
 
+// A host that runs ahead of the device waits for the one upload whose buffer it needs: not for the layers enqueued after
+// it, nor for work on streams of others.
+static void run_ahead(bool use_static) {
+    ppd_ctx* ctx = make_ctx();
+    const int slots = use_static ? 1 : kStagingSlots;
+    sim.device_syncs = 0;
+    for (int k = 0; k < slots; ++k)
+        for (int layer = 0; layer < 3; ++layer) CHECK(step(ctx, 6, 100 + k, use_static) == PPD_OK);
+    const size_t before = sim.null_stream.waiting();
+    std::thread device = device_after(100, 1);  // the oldest upload, and nothing after it
+    CHECK(step(ctx, 6, 200, use_static) == PPD_OK);
+    device.join();
+    CHECK(sim.device_syncs == 0);
+    CHECK(sim.null_stream.waiting() > before - 1);  // what was enqueued is still there, and the new plan's work behind it
+    finish(ctx);
+}
+
 int main(int argc, char** argv) {
     (void)argc;
     const std::string what = argv[1];
@@ -171,6 +188,10 @@ int main(int argc, char** argv) {
         pending_error(true);
     }
     if (what == "two_contexts") pending_error_and_two_contexts();
+    if (what == "run_ahead") {
+        run_ahead(false);
+        run_ahead(true);
+    }
     if (what == "sizes") sizes_that_just_fit();
     if (what == "failed_launch") {
         failed_launch(false);

@@ -46,6 +46,46 @@ def test_plans_follow_one_another_through_the_staging_buffers():
     ctx.close()
 
 
+@pytest.mark.parametrize("static", [False, True])
+def test_a_host_that_runs_ahead_waits_for_its_own_uploads_only(static):
+    """More plans in flight than staging buffers (the entry point that allocates nothing has one), three layers each, while
+    another stream is busy for long: the calls return before that stream is done, and every step has read its own plan."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(9)
+    full = si.make_batch("ahead", L=rng.integers(40, 300, 24), n=np.ones(24, np.int32), Hq=8, Hkv=2, D=64, seed=9)
+    pool_bits = oracle_pool(full)
+    ctx = ppd.Context(full.Hq, full.Hkv, full.D, full.num_pages)
+    pool, pt = to_dev_u16(pool_bits, torch, dev), torch.from_numpy(full.page_tables).to(dev)
+    call = ctx.mixed_attention_static if static else ctx.mixed_attention
+    steps = []
+    for k in range(10):
+        b = si.make_batch("ahead", L=np.maximum(full.L - 3 * k, 0), n=full.n, Hq=8, Hkv=2, D=64, seed=70 + k,
+                          page_tables=full.page_tables, num_pages=full.num_pages)
+        steps.append((b, to_dev_u16(b.q, torch, dev), torch.zeros((b.T, b.Hq, b.D), dtype=torch.int16, device=dev)))
+    for k in range(5):  # every buffer has its size, every kernel has been loaded
+        call(steps[k][1], pool, pt, steps[k][0].L, steps[k][0].n, steps[k][0].scale, steps[k][2])
+    x = torch.randn(8192, 8192, device=dev, dtype=torch.bfloat16)
+    y = torch.empty_like(x)
+    torch.mm(x, x, out=y)
+    torch.cuda.synchronize()
+    other, busy = torch.cuda.Stream(), torch.cuda.Event()
+    with torch.cuda.stream(other):
+        for _ in range(400):
+            torch.mm(x, x, out=y)
+        busy.record()
+    for b, q, out in steps:
+        for _ in range(3):
+            call(q, pool, pt, b.L, b.n, b.scale, out)
+    assert not busy.query()
+    torch.cuda.synchronize()
+    for b, _, out in steps:
+        check_close(bits_to_f32(from_dev_u16(out).reshape(b.T, b.Hq, b.D)), oracle_out(b, pool_bits))
+    ctx.close()
+
+
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("D,Hkv,T,layers", [(128, 8, 1023, 1), (128, 8, 1025, 1), (64, 8, 1021, 1), (64, 2, 1031, 4), (128, 1, 7, 1)])
 def test_append_on_both_sides_of_its_token_split(D, Hkv, T, layers, fp8):

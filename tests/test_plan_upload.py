@@ -18,7 +18,7 @@ def exe(tmp_path_factory):
     return path
 
 
-@pytest.mark.parametrize("what", ["pending_error", "two_contexts", "failed_launch", "sizes"])
+@pytest.mark.parametrize("what", ["pending_error", "two_contexts", "failed_launch", "sizes", "run_ahead"])
 def test_plan_upload_host_side(exe, what):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0")
     env.pop("LD_PRELOAD", None)
