@@ -68,10 +68,13 @@ __device__ __forceinline__ float sum_halves(float v) {
 
 // The running maximum is only raised (and the accumulators rescaled) when it would grow by more than this many
 // powers of two; until then probabilities may exceed 1, by at most 2^kLazyRescale.  The final o / l is unchanged.
+// (Row-block tiles do not look for the maximum: there the bound is on the sum of a lane's 32 probabilities.)
 #ifndef kLazyRescale
 #define kLazyRescale 8.0f
 #endif
-constexpr float kMaxLazyP = 256.0f;  // 2^kLazyRescale
+constexpr float power_of_two(float e) { return e >= 1.0f ? 2.0f * power_of_two(e - 1.0f) : 1.0f; }
+constexpr float kMaxLazyP = power_of_two(kLazyRescale);
+static_assert((int)kLazyRescale == kLazyRescale, "a whole number of powers of two");
 
 // Raw page-table entry of logical page `pi` of a sequence; pi is clamped so that no access leaves the page
 // table row.  The value is NOT inspected here: a caller that prefetches it must not wait for the load.
@@ -511,10 +514,11 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
                 exponentials(s, m_run * c);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // The tile's maximum (17 dependent instructions and a half-wave exchange) is not looked for: the exponentials are taken against the running reference as it is,
-            // and only if a lane's sum of 32 of them is above 32 * 2^kLazyRescale (or not a number: no reference yet, m_run =
-            // -inf) is the maximum found, the accumulators rescaled and the exponentials taken again.
-            if (__any(!(psum <= 32.0f * kMaxLazyP))) {
+            // The tile's maximum (17 dependent instructions and a half-wave exchange) is not looked for: the exponentials
+            // are taken against the running reference as it is, and only if a lane's sum of 32 of them is above
+            // 2^kLazyRescale (or not a number: no reference yet, m_run = -inf) is the maximum found, the accumulators
+            // rescaled and the exponentials taken again.  A single probability is then never above 2^kLazyRescale.
+            if (__any(!(psum <= kMaxLazyP))) {
                 float mx = s_cur[0][0];
 #pragma unroll
                 for (int tb = 0; tb < 2; ++tb)

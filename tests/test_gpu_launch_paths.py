@@ -140,6 +140,22 @@ def test_row_block_reference_is_raised_and_found(D, chunk, q_std):
     check_close(bits_to_f32(out), oracle_out(b), max_abs=2.0 ** -7 * float(np.abs(bits_to_f32(b.v)).max()))
 
 
+@pytest.mark.parametrize("bits_above", [7.0, 9.0, 12.0])
+def test_row_block_probabilities_stay_below_their_bound(bits_above):
+    """A key whose score lies `bits_above` powers of two over the running reference, with V of 1.5e35: a probability of more
+    than 2^8 against an old reference would leave binary32 in the sum, although the result is an ordinary number."""
+    b = si.make_batch("large_v", L=[200], n=[70], Hq=8, Hkv=1, D=128, seed=5)
+    b.q[:] = 0
+    b.q[..., 0] = 0x3F80
+    b.k[:] = 0
+    b.k[150, 0, :1] = si.f32_to_bf16_bits(np.array([bits_above * np.log(2.0) / b.scale]))
+    rng = np.random.default_rng(5)
+    b.v[:] = si.f32_to_bf16_bits(rng.choice([-1.0, 1.0], b.v.shape).astype(np.float32) * np.float32(1.5e35))
+    _, out, stats = gpu_step(b)
+    assert stats["n_mfma"] == 3 and stats["n_groups"] == 0
+    check_close(bits_to_f32(out) / 1.5e35, oracle_out(b) / 1.5e35)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(8, 8, 128), (10, 2, 128), (8, 1, 128), (6, 2, 64), (7, 1, 64)])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_row_block_results_leave_whole_lines(Hq, Hkv, D, fp8):
