@@ -91,7 +91,7 @@ typedef struct {
     int32_t kv_end;
     int32_t group;    /* merge group, or -1 when the tile covers the whole key range and writes `out` */
     int32_t queue;    /* work queue: 0..7 = MFMA tiles preferred by the workgroups of XCD `queue`, 8 = narrow tiles run by a
-                         whole workgroup, 9 = narrow tiles run one per wave, eight to a claim */
+                         whole workgroup, 9 = short narrow tiles run one per wave, eight to a claim */
     int64_t part_off; /* float offset of this tile's partial (o, m, l) in the workspace, or -1 */
 } ppd_work_item;
 
@@ -125,8 +125,7 @@ const char *ppd_last_error(const ppd_ctx *ctx);
  * 2 split by physical compute unit (default), 3 narrow tiles for all), "narrow_cus" (pref_mode 2: how many of
  * the 32 compute units of an XCD take narrow tiles first; -1 = sized by the planner's cost model so that both
  * kinds finish together), "wave_tiles" (-1 = narrow tiles of at most 384 keys run one per wave, eight to a claim, when the launch has at
- * least six such tiles per workgroup; a decode-only launch of very many tiles takes longer ones as well, up to 1536 keys, 3072 on FP8
- * pages; 0 = never; 1 = tiles of at most 384 keys, however many there are), "launch_mode" (0 = one kernel runs both kinds of tiles on separate compute units,
+ * least six such tiles per workgroup; 0 = never; 1 = whenever there is such a tile), "launch_mode" (0 = one kernel runs both kinds of tiles on separate compute units,
  * 1 = a step that holds both kinds runs as two kernels resident side by side on every compute unit -- row-block
  * tiles on the caller's stream, narrow tiles on a stream of the context's own, joined before the call's work ends
  * -- 2 = the two specialised kernels also for steps of one kind), "narrow_kernel" (1, the default = with launch_mode 0 a step

@@ -50,15 +50,15 @@ constexpr int kNarrowQueue = kXcds;  // index of the narrow-tile queue
 // Very short narrow tiles of a launch that has very many of them are handed out kWaves at a time (one claim), each
 // wave running one tile on its own: no combine through LDS, no barrier, and the fixed costs of a tile (claim, work
 // item, page ids, first loads) overlap across the eight tiles instead of adding up.  Only worth it while a tile is
-// far shorter than the launch: a wave alone streams slowly, so long tiles would stretch the end of the launch (the
-// planner says how long a tile may be).
+// far shorter than the launch: a wave alone streams slowly, so long tiles would stretch the end of the launch; and its
+// probabilities have one running reference where eight waves have eight, which costs a tenth more rounding error.
 constexpr int kWaveQueue = kXcds + 1;       // index of that queue; a claim covers kWaves consecutive tiles
 constexpr int kQueues = kXcds + 2;
 constexpr int kCursors = kQueues;           // one cursor per queue
 #ifndef PPD_WAVE_TILE_KEYS
 #define PPD_WAVE_TILE_KEYS 384
 #endif
-constexpr int kWaveTileKeys = PPD_WAVE_TILE_KEYS;  // that length where other tiles are in the launch
+constexpr int kWaveTileKeys = PPD_WAVE_TILE_KEYS;  // a narrow tile of at most this many keys may run on one wave
 // Device counters of a context: 64 words of flags (word 9: sticky error flags; words 10 and 11: finished
 // workgroups of the mixed / row-block kernel and of the stream kernel), then the queue cursors, each in a
 // 128-byte line of its own (claims on different queues then do not queue up behind one another at one address

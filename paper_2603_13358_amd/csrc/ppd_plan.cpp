@@ -374,36 +374,13 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     // fewer, eight waves per tile keep more compute units streaming.
     size_t wave_from = narrow_items.size();
     if (o.wave_tiles != 0 && o.force_kind != 1) {
-        const size_t device_slots = (size_t)(kWgPerCu * o.num_cus);  // not a grid override: that option must stay scheduling only
-        auto tile_keys = [&](size_t k) { return narrow_items[k].it.kv_end - narrow_items[k].it.kv_begin; };
-        auto first_within = [&](int keys) {
-            size_t k = 0;
-            while (k < narrow_items.size() && tile_keys(k) > keys) ++k;
-            return k;
-        };
-        size_t first_short = first_within(kWaveTileKeys);
-        bool enough = o.wave_tiles == 1 || narrow_items.size() - first_short >= 6 * device_slots;
-        // A launch of nothing else takes longer tiles as well, if nearly all of it can go that way.  Eight tiles in a row
-        // are the KV heads of one sequence: the waves of a workgroup then read whole pages between them, 6.0 TB/s on bf16 pages
-        // where tiles of 400 keys on eight waves each reach 4.8 (FP8 pages gain more: their tiles are shorter in bytes and
-        // the combine is not).  A workgroup is busy for as long as its longest tile, so the limit grows with
-        // the number of tiles a wave gets.  Measured (us a layer; 64-700 keys: 256, 320, 512 sequences 99 -> 97, 121 -> 112, 175 ->
-        // 155; FP8 200, 256: 67 -> 56, 82 -> 61; 64-1500 keys, 512: 300 -> 283; FP8 256: 106 -> 103; 64-3000, FP8 512: 307 -> 270).
-        // Beyond it: 256 of 400-1000 keys 142 -> 147, 512 of 64-3000 498 -> 516, FP8 200 of 64-1500 85 -> 97.
-        if (o.wave_tiles < 0 && row_blocks.empty()) {
-            const size_t rounds = std::min<size_t>(narrow_items.size() / (kWaves * device_slots), 2);
-            const bool fp8 = o.kv_elem_bytes == 1;
-            const int limit = (int)rounds * (fp8 ? 1536 : 768);
-            const int keys = fp8 && rounds == 0 && narrow_items.size() >= 6 * device_slots ? 768 : limit;
-            const size_t from = first_within(keys);
-            int64_t longer = 0;
-            for (size_t k = 0; k < from; ++k) longer += tile_keys(k);
-            if (keys > kWaveTileKeys && longer <= (int64_t)(narrow_tokens / 8)) {
-                first_short = from;
-                enough = true;
-            }
-        }
-        if (enough && first_short < narrow_items.size()) wave_from = first_short;
+        size_t first_short = 0;
+        while (first_short < narrow_items.size() &&
+               narrow_items[first_short].it.kv_end - narrow_items[first_short].it.kv_begin > kWaveTileKeys)
+            ++first_short;
+        const size_t n_short = narrow_items.size() - first_short;
+        // (by the chip's workgroup slots, not by a grid override: that option must stay scheduling only)
+        if (n_short > 0 && (o.wave_tiles == 1 || n_short >= (size_t)6 * (size_t)(kWgPerCu * o.num_cus))) wave_from = first_short;
     }
     plan->queue_begin[kNarrowQueue] = (int32_t)plan->items.size();
     for (size_t k = 0; k < narrow_items.size(); ++k) {
