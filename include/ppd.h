@@ -26,10 +26,11 @@
  *    never dereference an out-of-range id (the token or key is skipped) and raise a sticky flag that
  *    ppd_device_error_flags reads back.
  *  - ppd_kv_append enqueues one kernel launch.  ppd_mixed_attention plans on the host and uploads the plan when L, n
- *    or the options differ from the previous call on the context (pinned staging buffer, one asynchronous copy);
- *    otherwise -- the other layers of the same engine step -- it enqueues kernel launches only.  Such a step can be
- *    captured into a HIP graph and replayed (the kernels reset their own queue cursors; no memset nodes); with the
- *    option "timing" set, events are recorded as well, so leave it off under capture.
+ *    or the options differ from the previous call on the context (one small kernel reads the pinned staging buffer in
+ *    place; a call that finds every staging buffer still unread -- there are four, one for ppd_mixed_attention_static --
+ *    waits for the oldest upload); otherwise -- the other layers of the same engine step -- it enqueues kernel launches
+ *    only.  Such a step can be captured into a HIP graph and replayed (the kernels reset their own queue cursors; no
+ *    memset nodes); with the option "timing" set, events are recorded as well, so leave it off under capture.
  *  - One context serves one stream at a time.  Calls on a context are not thread-safe.
  *  - Debugging aids, read from the environment by ppd_create: PPD_LOG=1 prints one line per call on stderr (batch
  *    size, tiles of each kind, split sizes, grid, whether the plan was reused); PPD_DEBUG_SLOTS=1 makes every append

@@ -61,19 +61,24 @@ static void split_range(int64_t len, int64_t chunk, std::vector<int32_t>* bounds
 struct RowBlock { int64_t vis_end; int32_t nrows; };
 
 // Compute units (of the 32 of an XCD) whose workgroups take narrow tiles first.  A workgroup of the mixed kernel
-// fills a compute unit (8 waves of up to 256 registers), so the two kinds are split by physical unit.  Narrow tiles are bound by the bytes a unit keeps in flight (about 45 GB/s each), MFMA tiles
-// by compute (about 1.5 us per 64 keys of a row block, 2.3 on FP8 pages, which are converted on the way): the split is sized so
-// that both kinds finish together; whoever finishes first steals from the other anyway.  Swept over seven mixed steps on
-// bf16 pages the best split lay within two units of this one and 2.3 us cost 1-4 % (60 decodes beside 4 turns, 64 query heads,
-// 16 -> 18 units: 358 -> 346 us; 128 long decodes beside 4 long turns, 14 -> 18: 3249 -> 3133 us a layer pair); on FP8 pages
-// 2.3 is within 1 % of the best.
+// fills a compute unit (8 waves of up to 256 registers), so the two kinds are split by physical unit: narrow tiles are
+// bound by the bytes a unit keeps in flight (about 45 GB/s each), MFMA tiles by compute, and the split is sized so that
+// both kinds finish together; whoever finishes first steals from the other anyway.
 // A unit streams FP8 pages at about 38 GB/s: its loads are 8 bytes per lane instead of 16 and 8, and a unit's memory
 // pipeline moves fewer bytes per second with narrower loads (about 58 GB/s at best, with contiguous 16-byte loads).
 static double unit_bytes_per_us(int elem_bytes) { return elem_bytes == 1 ? 38e3 : 45e3; }
 
-// (The choice of the split size reckons with 2.3 us for both formats: with 1.5 it splits more row blocks, and one batch in
-// forty then needs more room for its partials than the fixed scratch array has.)
-constexpr double kSplitIterUs = 2.3;
+// What 64 keys of a row block are priced at.  The loop itself takes 1.9 us on either format while every unit runs it (the
+// chip is then at its power limit) and less beside streaming units; the three prices below are fits of three
+// different estimates, not measurements of it.
+//  - the split of the units: swept over seven mixed steps on bf16 pages the best split lay within two units of what 1.5 gives, and
+//    2.3 cost 1-4 % (60 decodes beside 4 turns, 64 query heads, 16 -> 18 units: 358 -> 346 us; 128 long decodes beside 4 long
+//    turns, 14 -> 18: 3249 -> 3133 us a layer pair); on FP8 pages 2.3 is within 1 % of the best.
+//  - the units left to row blocks while their split size is chosen: with 1.5 it splits more row blocks, and one batch in
+//    forty then needs more room for its partials than the fixed scratch array has.
+//  - the tiles of that choice: kTileIterUs there, with the cost of a tile's start beside it.
+static double split_of_units_iter_us(int elem_bytes) { return elem_bytes == 1 ? 2.3 : 1.5; }
+constexpr double kChunkChoiceIterUs = 2.3;
 static int narrow_units(double narrow_bytes, double mfma_iters, int elem_bytes, double iter_us) {
     if (narrow_bytes == 0) return 0;
     if (mfma_iters == 0) return 32;
@@ -113,7 +118,7 @@ static int64_t choose_mfma_chunk(const std::vector<RowBlock>& blocks, int G, int
             if (nsplit > 1) partial_bytes += (double)rb.nrows * G * (D + 2) * 4.0 * nsplit * Hkv;
         }
         // the workgroups that take MFMA tiles first, as the launch will split them
-        const int S = std::max(1, slots - narrow_units(narrow_bytes, iters, elem_bytes, kSplitIterUs) * slots / 32);
+        const int S = std::max(1, slots - narrow_units(narrow_bytes, iters, elem_bytes, kChunkChoiceIterUs) * slots / 32);
         std::sort(tiles.begin(), tiles.end(), std::greater<double>());
         load.assign((size_t)S, 0.0);  // min-heap of workgroup finish times; the earliest workgroup takes the next tile
         for (double t : tiles)
@@ -399,7 +404,9 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
             if (k.it.kind == 0) narrow_bytes += toks * kv_tok_bytes_head;
             else mfma_iters += std::ceil(toks / kTileTokens);
         }
-        plan->narrow_cus = o.narrow_cus >= 0 ? std::min(o.narrow_cus, 32) : narrow_units(narrow_bytes, mfma_iters, o.kv_elem_bytes == 1 ? 1 : 2, o.kv_elem_bytes == 1 ? 2.3 : 1.5);
+        const int elem_bytes = o.kv_elem_bytes == 1 ? 1 : 2;
+        plan->narrow_cus = o.narrow_cus >= 0 ? std::min(o.narrow_cus, 32)
+                                             : narrow_units(narrow_bytes, mfma_iters, elem_bytes, split_of_units_iter_us(elem_bytes));
     }
 
     ppd_plan_stats& st = plan->stats;
