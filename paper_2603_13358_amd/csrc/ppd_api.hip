@@ -295,7 +295,9 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     if (!reuse) {
         // upload: [items][groups][units] through pinned staging
         Staging& sg = use_static ? ctx->static_staging : ctx->staging[ctx->next_slot];
+        const auto t_wait0 = std::chrono::steady_clock::now();
         wait_staging_read(sg);
+        const auto waited = std::chrono::steady_clock::now() - t_wait0;
         if (!use_static) {
             ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
             if (sg.bytes < upload_bytes) {
@@ -350,7 +352,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         ctx->plan_on_device = true;
         ctx->plan_where = where;
         ctx->plan.stats.plan_host_us = (int32_t)std::chrono::duration_cast<std::chrono::microseconds>(
-                                           std::chrono::steady_clock::now() - t_plan0).count();
+                                           std::chrono::steady_clock::now() - t_plan0 - waited).count();
     }
     if (!use_static) d_plan = ctx->d_items;
     if (!in_capture) {

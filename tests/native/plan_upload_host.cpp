@@ -176,6 +176,8 @@ static void run_ahead(bool use_static) {
     CHECK(step(ctx, 6, 200, use_static) == PPD_OK);
     device.join();
     CHECK(sim.device_syncs == 0);
+    ppd_plan_stats stats;
+    CHECK(ppd_get_plan_stats(ctx, &stats) == PPD_OK && stats.plan_host_us < 50000);  // the plan's own time, not the wait
     CHECK(sim.null_stream.waiting() > before - 1);  // what was enqueued is still there, and the new plan's work behind it
     finish(ctx);
 }
