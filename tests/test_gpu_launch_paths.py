@@ -210,9 +210,13 @@ def test_mixed_launch_with_a_workgroup_for_every_tile(B_narrow, B_rows, wave):
 def test_decode_only_launch_of_many_short_tiles(fp8, longest):
     """2048 decode tiles, most of them of at most 300 keys (which run one per wave), a few of up to 768 or 1536 (which do
     not), whole and partly filled last pages among them."""
+    import paper_2603_13358_amd as ppd
+
     rng = np.random.default_rng(longest)
     L = rng.integers(0, 300, 256)
     L[:6] = [longest - 1, longest - 2, longest - 16, longest - 17, 15, 16]
+    items, _ = ppd.ppd_plan_build(8, 8, 128, 16, 1 << 20, L, np.ones(256, np.int64))
+    assert sorted({t.queue for t in items}) == [8, 9] and sum(t.queue == 9 for t in items) == 8 * 252
     b = si.make_batch("single", L=L, n=np.ones(256, np.int64), Hq=8, Hkv=8, D=128, seed=longest, slack_pages=3)
     if fp8:
         pool, out, _ = gpu_step_fp8(b, 0.0173, 0.0421)
