@@ -210,6 +210,7 @@ def test_mixed_launch_with_a_workgroup_for_every_tile(B_narrow, B_rows, wave):
 def test_decode_only_launch_of_many_short_tiles(fp8, longest):
     """2048 decode tiles, most of them of at most 300 keys (which run one per wave), a few of up to 768 or 1536 (which do
     not), whole and partly filled last pages among them."""
+    import torch  # noqa: F401 -- before the library: both load a HIP runtime, and torch has to find its own
     import paper_2603_13358_amd as ppd
 
     rng = np.random.default_rng(longest)
