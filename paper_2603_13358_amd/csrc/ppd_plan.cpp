@@ -368,7 +368,14 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
                 queues[q].push_back(it);
             }
     }
-    std::stable_sort(narrow_items.begin(), narrow_items.end(), [](const Keyed& a, const Keyed& b) { return a.cost > b.cost; });
+    // Longest first; among equals the KV heads of one key range side by side.  Workgroups that start together then read the
+    // heads' 4 KiB pieces of the same 64 KiB pages instead of pieces of as many pages as there are splits: one decode over 32000
+    // keys 47 -> 42 us a layer, 11 decodes of 300-6500 keys (64 query heads) 36.8 -> 34.9.
+    std::stable_sort(narrow_items.begin(), narrow_items.end(), [](const Keyed& a, const Keyed& b) {
+        if (a.cost != b.cost) return a.cost > b.cost;
+        if (a.it.seq != b.it.seq) return a.it.seq < b.it.seq;
+        return a.it.kv_begin < b.it.kv_begin;
+    });
     plan->items.reserve(keyed.size());
     for (int q = 0; q < kXcds; ++q) {
         plan->queue_begin[q] = (int32_t)plan->items.size();

@@ -222,6 +222,17 @@ def test_narrow_split_size_of_small_decode_batches():
     assert st.narrow_chunk == 1024 and st.n_items == 4 * 8 * 17
 
 
+@pytest.mark.parametrize("L,n,Hkv", [([32000], [1], 8), ([300, 6500, 1023, 4095], [1, 1, 1, 2], 8), ([700, 700, 701], [1, 1, 1], 5)])
+def test_heads_of_a_key_range_are_neighbours_in_the_narrow_list(L, n, Hkv):
+    """Narrow tiles of equal length: the KV heads of one key range sit side by side, because they read the same pages."""
+    items, _ = ppd.ppd_plan_build(4 * Hkv, Hkv, 128, 16, 1 << 20, L, n)
+    assert len(items) % Hkv == 0
+    for i in range(0, len(items), Hkv):
+        run = items[i:i + Hkv]
+        assert [t.kvh for t in run] == list(range(Hkv))
+        assert len({(t.seq, t.kv_begin, t.kv_end) for t in run}) == 1
+
+
 def test_plan_refuses_a_batch_that_needs_millions_of_tiles():
     # 2^29 new tokens in one sequence: 8.4M row blocks x 8 KV heads, far beyond one launch's work list
     with pytest.raises(ppd.PPDError) as e:
