@@ -38,10 +38,17 @@ constexpr int kStreamThreads = 64 * kStreamWaves;
 #endif
 constexpr int kStreamKSets = PPD_STREAM_KSETS;
 constexpr int kStreamVSets = PPD_STREAM_VSETS;
+// Rotating register sets of a wave that streams bf16 pages, one page each: in the mixed kernel, and in the decode-only kernel
+// for long and for short tiles (launch_narrow has the figures).  In the mixed kernel four sets left its row-block loop no
+// register to spare and streamed less: 128 long decodes beside 4 turns 2804 -> 2755 us with three.
+constexpr int kMixedSets = 3, kLongSets = 3, kShortSets = 2;
 #ifndef PPD_FP8_SETS
-#define PPD_FP8_SETS 2
+#define PPD_FP8_SETS 1
 #endif
-constexpr int kFp8StreamSets = PPD_FP8_SETS;  // rotating register sets (one page pair each) of a streaming wave on FP8 pages
+// The same on FP8 pages, one page pair each.  One: a wave asks for a pair and works it, and the other seven keep the unit's
+// loads going.  A second set gained nothing on long ranges (128 decodes of 1K-32K 1353 -> 1346 us without it) and its spilled
+// scalars cost short ones 7 % (one decode of 4000 keys 20.5 -> 19.1 us a layer).
+constexpr int kFp8StreamSets = PPD_FP8_SETS;
 // Waves per workgroup of ppd_narrow_kernel.  Two workgroups of four waves per unit (two tiles in flight there) measured
 // the same on short tiles and 10 % slower on cfg2, so it runs its tiles exactly as ppd_mixed_kernel does.
 constexpr int kNarrowKernelWaves = kWaves;
@@ -123,6 +130,7 @@ struct KParams {
     const int32_t* queue_begin;  // device: kQueues + 1 bounds, uploaded behind the plan's tables
     int64_t num_pages;
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
+    int64_t mean_tile_keys;  // keys of the work list's tiles, on average
     int32_t n_items;
     int32_t pref_mode;    // how a workgroup picks its preferred queue (see ppd_mixed_kernel)
     int32_t narrow_cus;   // pref_mode 2: compute units per XCD (of 32) that take narrow tiles first

@@ -912,7 +912,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
     };
 
     // K of NK - 1 pages and V of NV - 1 pages (4 KiB each at D = 128) are in flight per wave while one page is being
-    // computed; the register sets rotate (period = NK * NV steps, unrolled).  The loads sit under conditions, so at
+    // computed; the register sets rotate (period = NK steps if NK = NV, else NK * NV, unrolled).  The loads sit under conditions, so at
     // the points where paths meet the compiler's waits on the memory counter assume the path with the fewest loads
     // issued and mostly drain what was just issued.  That costs nothing here: a loop without any conditional load
     // (waits of 36..47 outstanding loads in its steady state) was built and measured the same -- a compute unit
@@ -1029,7 +1029,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
 //   S^T rows: MFMA row r is key (page r >> 4 of the pair, token 8*bit2(r) + 4*bit3(r) + (r & 3)), so that accumulator
 //   registers 0..7 of a lane are tokens 8h..8h+7 of the first page and 8..15 those of the second (h = lane / 32):
 //   the octet the lane's V granules hold.
-// NS register sets of one page pair each rotate: NS - 1 pairs are in flight per wave.
+// NS register sets of one page pair each rotate: NS - 1 pairs are in flight per wave besides the one being computed.
 // ---------------------------------------------------------------------------------------------------
 template <int HD, int NW, int NS, bool SOLO, bool FP8>
 __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_work_item& it, char* smem) {
@@ -1333,7 +1333,6 @@ __device__ __forceinline__ int own_entry(const KParams& P) {
 
 template <int HD, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P) {
-    constexpr int NSETS = 4;  // rotating register sets (one page each) of a streaming wave on bf16 pages
     // Dynamic LDS: rings of kStages + 1 stages of 4 pages of K and as many of V, then the page ids of a tile's key
     // range, for the MFMA path (136 KiB at HD = 128); the narrow path's combine buffer (kWaves * 16 * (HD+2)
     // floats) uses the front of it.
@@ -1426,7 +1425,7 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
             if (mine < P.queue_begin[kQueues]) {
                 const ppd_work_item it = P.items[mine];
                 if constexpr (FP8) narrow_item_wide<HD, 1, kFp8StreamSets, true, true>(P, it, smem);
-                else narrow_item<HD, 1, NSETS, NSETS, true>(P, it, smem);
+                else narrow_item<HD, 1, kMixedSets, kMixedSets, true>(P, it, smem);
             }
             if (own >= 0) return;
             continue;
@@ -1434,7 +1433,7 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
         const ppd_work_item it = P.items[idx];
         if (it.kind == 0) {
             if constexpr (FP8) narrow_item_wide<HD, kWaves, kFp8StreamSets, false, true>(P, it, smem);
-            else narrow_item<HD, kWaves, NSETS, NSETS, false>(P, it, smem);
+            else narrow_item<HD, kWaves, kMixedSets, kMixedSets, false>(P, it, smem);
         } else {
             mfma_item<HD, false, FP8>(P, it, smem);
         }
@@ -1454,10 +1453,11 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
 // trip but holds a slot that an idle workgroup could have run: cfg2 186 -> 206 us), and handing out all slots by
 // index, rounds running alternately up and down the workgroups (no atomics at all: same step time on short tiles,
 // +3 % on long ones).
+// NSETS: rotating register sets (one page each) of a streaming wave on bf16 pages, kLongSets where the tiles are long and
+// kShortSets where they are short (see launch_narrow).
 // ---------------------------------------------------------------------------------------------------
-template <int HD, bool FP8, int NW>
+template <int HD, bool FP8, int NW, int NSETS>
 __global__ __launch_bounds__(64 * NW, 2) void ppd_narrow_kernel(const KParams P) {
-    constexpr int NSETS = 4;  // rotating register sets (one page each) of a streaming wave on bf16 pages
     extern __shared__ __attribute__((aligned(16))) char smem[];  // the combine buffer
     __shared__ int s_next_slot;
     volatile int* s_next = &s_next_slot;
@@ -1819,10 +1819,12 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, false>), mixed_lds_bytes(64));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<128, true>), mixed_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, true>), mixed_lds_bytes(64));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, kNarrowKernelWaves>), NarrowCombine<kNarrowKernelWaves>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, false, kNarrowKernelWaves>), NarrowCombine<kNarrowKernelWaves>::bytes(64));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, true, kNarrowKernelWaves>), NarrowCombine<kNarrowKernelWaves>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, kNarrowKernelWaves>), NarrowCombine<kNarrowKernelWaves>::bytes(64));
+    constexpr int NW = kNarrowKernelWaves;
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kLongSets>), NarrowCombine<NW>::bytes(128));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kShortSets>), NarrowCombine<NW>::bytes(128));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, false, NW, kShortSets>), NarrowCombine<NW>::bytes(64));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, true, NW, kShortSets>), NarrowCombine<NW>::bytes(128));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, NW, kShortSets>), NarrowCombine<NW>::bytes(64));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<128>), ring_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<64>), ring_lds_bytes(64));
     return (int)e;
@@ -1845,14 +1847,23 @@ int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool f
     hipStream_t st = static_cast<hipStream_t>(stream);
     constexpr int NW = kNarrowKernelWaves;
     const size_t lds128 = NarrowCombine<NW>::bytes(128), lds64 = NarrowCombine<NW>::bytes(64);
-    if (head_dim == 128 && !fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW>), dim3(grid), dim3(64 * NW), lds128, st, p);
+    // Register sets on bf16 pages.  Two make a loop of half the instructions, which short tiles never get to stream from a warm
+    // instruction cache; long tiles want K and V of two pages in flight.  Two and three sets, us a layer with its append: 64
+    // decodes of 200-400 keys 22.8 and 24.0, of 400-800 33.2 and 34.1, of 800-1600 (8 KV heads, tiles of 1200 on average) 54.7
+    // and 55.2; 64 of 1600-3200 99.9 and 98.8, of 6400-9000 306 and 303; 8 of 6400-9000 (tiles of 2000) 59.3 and 58.3.  The four
+    // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
+    // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
+    const bool long_tiles = p.mean_tile_keys >= 1536;
+    if (head_dim == 128 && fp8_pages)
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
+    else if (head_dim == 128 && long_tiles)
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kLongSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
     else if (head_dim == 128)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW>), dim3(grid), dim3(64 * NW), lds128, st, p);
-    else if (!fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, false, NW>), dim3(grid), dim3(64 * NW), lds64, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
+    else if (fp8_pages)
+        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p);
     else
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW>), dim3(grid), dim3(64 * NW), lds64, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<64, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p);
     return (int)hipGetLastError();
 }
 

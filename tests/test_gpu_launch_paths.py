@@ -246,3 +246,17 @@ def test_short_decode_batch_is_as_exact_as_on_whole_workgroups(Hq, Hkv, D, fp8):
         d = bits_to_f32(out).astype(np.float64) - want
         errors.append(np.sqrt((d * d).sum() / (np.asarray(want, np.float64) ** 2).sum()))
     assert errors[0] <= 1.01 * errors[1], errors
+
+
+@pytest.mark.parametrize("D,G,L", [(128, 4, [1534] * 3), (128, 4, [1535] * 3), (128, 8, [3000, 61, 47, 3049]), (128, 1, [0, 15, 16, 6000]),
+                                   (64, 4, [1535, 4000, 1])])
+def test_decode_only_kernel_for_short_and_for_long_tiles(D, G, L):
+    """Tiles of 1535, of 1536 and of mixed lengths on average (the decode-only kernel takes other register sets from 1536
+    on): the oracle's result, and bit for bit the mixed kernel's."""
+    b = si.make_batch("sets", L=L, n=np.ones(len(L), np.int64), Hq=8 * G, Hkv=8, D=D, seed=D + G + len(L), slack_pages=2)
+    options = {"narrow_chunk": 8192}
+    _, out, stats = gpu_step(b, options=options)
+    assert stats["n_narrow"] == 8 * len(L)
+    check_close(bits_to_f32(out), oracle_out(b))
+    _, mixed, _ = gpu_step(b, options=dict(options, narrow_kernel=0))
+    assert np.array_equal(out, mixed)
