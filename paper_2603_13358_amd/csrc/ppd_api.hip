@@ -404,6 +404,8 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         PPD_HIP(ctx, hipEventRecord(ctx->ev_pairs[ctx->ev_used].first, hs));
     }
     const int D = ctx->shape.head_dim;
+    ppd::MergeGroup* const d_groups = plan.groups.empty() ? nullptr : reinterpret_cast<ppd::MergeGroup*>(static_cast<char*>(d_plan) + items_bytes);
+    kp.merge_groups = nullptr;
     const bool has_narrow = plan.stats.n_narrow > 0, has_mfma = plan.stats.n_mfma > 0;
     const int mode = ctx->launch_mode;
     int rc = 0;
@@ -413,6 +415,12 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         constexpr int NW = ppd::kNarrowKernelWaves;
         const int64_t slots = (plan.queue_begin[ppd::kWaveQueue] - plan.queue_begin[ppd::kNarrowQueue]) + (n_wave + NW - 1) / NW;
         const int64_t wgs = (int64_t)plan.stats.grid * (ppd::kWaves / NW);  // as many waves on a unit as the planned grid has
+        // Split ranges are merged in the launch where it has one round of tiles: what its last tile waits for is then what the
+        // step waits for, and a second launch is longer (4 decodes of 8K keys 35.7 -> 32.9 us a layer, one of 4000 keys of FP8
+        // pages 18.2 -> 16.6, 11 decodes of 300-6500 keys 34.4 -> 33.4).  With more rounds every tile but the last ones would
+        // stop for its count while its unit could stream (66 decodes of 1K-32K, FP8 pages, 1576 tiles: +3 us of 440).  Tiles that
+        // run on single waves leave their partials to the merge launch as well.
+        if (n_wave == 0 && slots <= wgs) kp.merge_groups = d_groups;
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {
@@ -447,9 +455,9 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         PPD_HIP(ctx, hipEventRecord(ctx->ev_pairs[ctx->ev_used].second, hs));
         ctx->ev_used += 1;
     }
-    if (!plan.groups.empty()) {
+    if (d_groups && !kp.merge_groups) {
         ppd::MergeParams mp;
-        mp.groups = reinterpret_cast<const ppd::MergeGroup*>(static_cast<const char*>(d_plan) + items_bytes);
+        mp.groups = d_groups;
         mp.partials = kp.partials;
         mp.out = static_cast<uint16_t*>(out);
         mp.n_groups = (int32_t)plan.groups.size();

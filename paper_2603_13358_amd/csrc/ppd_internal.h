@@ -79,9 +79,10 @@ constexpr int kMergeCols = 16;     // columns of a merge group one block of the 
 // One merge group: a row block whose key range was split over `nsplit` tiles with consecutive partials.
 struct MergeGroup {
     int32_t grow0;
-    int32_t nrows;
-    int32_t kvh;
+    int16_t nrows;        // at most 256
+    int16_t kvh;          // below 1024
     int32_t nsplit;
+    uint32_t arrived;     // decode-only launches: tiles of the group that have written their partial; 0 between launches
     int64_t part_off;     // float offset of split 0
     int64_t part_stride;  // floats per split = cols * (D + 2)
 };
@@ -128,6 +129,7 @@ struct KParams {
     float* partials;
     uint32_t* counters;   // [9] sticky error flags, [10], [11] finished workgroups; queue cursors from kCursorBase on
     const int32_t* queue_begin;  // device: kQueues + 1 bounds, uploaded behind the plan's tables
+    MergeGroup* merge_groups;    // not NULL: the last tile of a group merges it (ppd_narrow_kernel only)
     int64_t num_pages;
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average

@@ -768,6 +768,13 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
 // K and NV <= NK for V rotate, so that K of NK - 1 and V of NV - 1 pages per wave are in flight while one page is
 // computed), then the waves' (o, m, l) are combined through LDS, CB columns per pass.
 // ---------------------------------------------------------------------------------------------------
+// A narrow tile's partial may be read by another workgroup of the same launch (merge_last): it goes past the caches of this
+// XCD, which the other XCDs do not see.
+__device__ __forceinline__ void store_partial(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ f32x2 load_partial2(const float* p) {
+    return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 template <int NW>
 struct NarrowCombine {
     static constexpr int CB = NW >= 8 ? kNarrowCols : 8;  // columns per combine pass
@@ -1008,10 +1015,10 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
                 if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
             } else {
                 float* pp = P.partials + it.part_off;
-                pp[(int64_t)col * HD + d] = o;
+                store_partial(pp + (int64_t)col * HD + d, o);
                 if (d == 0) {
-                    pp[(int64_t)ncols * HD + col * 2] = mm;
-                    pp[(int64_t)ncols * HD + col * 2 + 1] = l;
+                    store_partial(pp + (int64_t)ncols * HD + col * 2, mm);
+                    store_partial(pp + (int64_t)ncols * HD + col * 2 + 1, l);
                 }
             }
         }
@@ -1278,10 +1285,10 @@ __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_wor
                 if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
             } else {
                 float* pp = P.partials + it.part_off;
-                pp[(int64_t)col * HD + d] = o;
+                store_partial(pp + (int64_t)col * HD + d, o);
                 if (d == 0) {
-                    pp[(int64_t)ncols * HD + col * 2] = mm;
-                    pp[(int64_t)ncols * HD + col * 2 + 1] = l;
+                    store_partial(pp + (int64_t)ncols * HD + col * 2, mm);
+                    store_partial(pp + (int64_t)ncols * HD + col * 2 + 1, l);
                 }
             }
         }
@@ -1442,6 +1449,73 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
     if (tid == 0) rearm_cursors(P, 0, kCursors, 10);
 }
 
+// Merge of a split range by the last of its tiles, in the launch that made them: every tile of the group has counted itself in
+// once its partial had reached the memory side, and the one that finds all others there does what ppd_merge_kernel does, splits
+// in index order (bit for bit the same results).  Bound by latency: the count (one trip) and the partials (one trip for up to
+// eight splits: the (m, l) pairs of all splits go to LDS while the first values are on their way).  A second launch costs
+// 5.5 us for 4 splits and 10 for 12, this about 3.
+// An arriving partial is ordered before its count by the wait below and needs no cache-wide write-back, because its stores go
+// past the L2 (store_partial); the reads do so as well.
+template <int HD, int NW>
+__device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item* item, char* smem, volatile int* s_arrived) {
+    constexpr int NT = NW * 64, LANES = HD / 2;  // lanes of a column, two d each
+    constexpr int kStagedPairs = 4096;           // (m, l) pairs that fit the combine buffer
+    static_assert(kStagedPairs * sizeof(f32x2) <= (size_t)NW * NarrowCombine<NW>::CB * (HD + 2) * sizeof(float), "staged in the combine buffer");
+    const int tid = threadIdx.x;
+    asm volatile("s_waitcnt vmcnt(0)" : "+s"(item) : : "memory");  // this wave's part of the partial has arrived
+    const ppd_work_item it = *item;                   // read again: kept over the tile's loop it would cost that scalar registers
+    __syncthreads();                                  // every wave's part has arrived; the combine buffer is free
+    MergeGroup* const g = P.merge_groups + it.group;
+    const int nsplit = g->nsplit;
+    const int64_t stride = g->part_stride;
+    const float* const base = P.partials + g->part_off;
+    if (tid == 0) *s_arrived = (int)atomicAdd(&g->arrived, 1u);
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(*s_arrived) != nsplit - 1) return;
+    if (tid == 0) __hip_atomic_store(&g->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    const int ncols = it.nrows * P.G;
+    const float c = P.scale_log2e;
+    f32x2* const ml = reinterpret_cast<f32x2*>(smem);  // [split][column]
+    const bool staged = nsplit * ncols <= kStagedPairs;
+    constexpr int AT_ONCE = 8;
+    auto load_values = [&](int idx, int j0, f32x2 (&v)[AT_ONCE]) {
+        const float* p = base + (int64_t)(idx / LANES) * HD + (idx % LANES) * 2;
+#pragma unroll
+        for (int t = 0; t < AT_ONCE; ++t) v[t] = load_partial2(p + stride * (j0 + t < nsplit ? j0 + t : j0));
+    };
+    auto pair = [&](int j, int col) { return staged ? ml[j * ncols + col] : load_partial2(base + stride * j + (int64_t)ncols * HD + col * 2); };
+    f32x2 v[AT_ONCE];
+    if (tid < ncols * LANES) load_values(tid, 0, v);
+    if (staged) {
+        const int col = tid & (kNarrowCols - 1);
+        for (int j = tid / kNarrowCols; j < nsplit; j += NT / kNarrowCols)
+            if (col < ncols) ml[j * ncols + col] = load_partial2(base + stride * j + (int64_t)ncols * HD + col * 2);
+    }
+    __syncthreads();
+    for (int idx = tid; idx < ncols * LANES; idx += NT) {
+        const int col = idx / LANES, d = (idx % LANES) * 2;
+        float mm = NEG_INF;
+        for (int j = 0; j < nsplit; ++j) mm = fmaxf(mm, pair(j, col)[0]);
+        float o0 = 0.f, o1 = 0.f, l = 0.f;
+        for (int j0 = 0; j0 < nsplit; j0 += AT_ONCE) {
+            if (idx != tid || j0 > 0) load_values(idx, j0, v);
+#pragma unroll
+            for (int t = 0; t < AT_ONCE; ++t) {
+                if (j0 + t < nsplit) {
+                    const f32x2 w = pair(j0 + t, col);
+                    const float f = w[0] == NEG_INF ? 0.f : fast_exp2((w[0] - mm) * c);
+                    l += f * w[1];
+                    o0 += f * v[t][0];
+                    o1 += f * v[t][1];
+                }
+            }
+        }
+        const int crow = col_row(col, P.invG);
+        const int64_t orow = (int64_t)(it.grow0 + crow) * P.Hq + it.kvh * P.G + (col - crow * P.G);
+        *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16((o0 / l) * P.v_scale, (o1 / l) * P.v_scale);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------------
 // A launch that holds narrow tiles only (a decode-only step).  Same tile code as in ppd_mixed_kernel, handed out
 // differently: a small launch of the mixed kernel spends 1.7 us on its first claim and ~5 us finding out, claim by
@@ -1459,7 +1533,7 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
 template <int HD, bool FP8, int NW, int NSETS>
 __global__ __launch_bounds__(64 * NW, 2) void ppd_narrow_kernel(const KParams P) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // the combine buffer
-    __shared__ int s_next_slot;
+    __shared__ int s_next_slot, s_arrived;
     volatile int* s_next = &s_next_slot;
     const int tid = threadIdx.x;
     const int wg_begin = P.queue_begin[kNarrowQueue], wave_begin = P.queue_begin[kWaveQueue], end = P.queue_begin[kQueues];
@@ -1472,6 +1546,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ppd_narrow_kernel(const KParams P)
             const ppd_work_item it = P.items[wg_begin + slot];
             if constexpr (FP8) narrow_item_wide<HD, NW, kFp8StreamSets, false, true>(P, it, smem);
             else narrow_item<HD, NW, NSETS, NSETS, false>(P, it, smem);
+            if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, P.items + wg_begin + slot, smem, &s_arrived);
         } else {
             const int mine = wave_begin + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
             if (mine < end) {

@@ -286,7 +286,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
                 if (nsplit > 1) {
                     group = (int)plan->groups.size();
                     base = part_floats;
-                    plan->groups.push_back(MergeGroup{(int32_t)(grow + r0), nrows, h, nsplit, base, stride});
+                    plan->groups.push_back(MergeGroup{(int32_t)(grow + r0), (int16_t)nrows, (int16_t)h, nsplit, 0u, base, stride});
                     for (int c0 = 0; c0 < nrows * G; c0 += kMergeCols) plan->units.push_back(MergeUnit{group, c0});
                     part_floats += stride * nsplit;
                 }

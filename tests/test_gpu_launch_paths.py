@@ -260,3 +260,46 @@ def test_decode_only_kernel_for_short_and_for_long_tiles(D, G, L):
     check_close(bits_to_f32(out), oracle_out(b))
     _, mixed, _ = gpu_step(b, options=dict(options, narrow_kernel=0))
     assert np.array_equal(out, mixed)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,L,n,chunk", [
+    (32, 8, 128, [900, 17, 4000, 0, 2047], [1, 1, 1, 4, 1], 256),   # 1..16 splits, whole ranges beside them
+    (8, 8, 128, [8191], [1], 64),                                   # one column, 128 splits
+    (16, 2, 64, [3000, 129], [2, 1], 64),                           # 16 columns: two passes of the merging workgroup
+    (40, 8, 128, [577, 511, 512], [3, 1, 1], 64),                   # 15 and 5 columns
+    (16, 2, 128, [17000], [2], 64),                                 # 16 columns x 266 splits: more pairs than are staged
+])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_split_ranges_are_merged_by_their_last_tile(Hq, Hkv, D, L, n, chunk, fp8):
+    """Decode-only launches of one round merge split ranges themselves: the oracle's result, bit for bit that of the mixed
+    kernel and the merge launch behind it, and again on the same plan (the counts are back at zero)."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    b = si.make_batch("last", L=L, n=n, Hq=Hq, Hkv=Hkv, D=D, seed=D + len(L), slack_pages=2)
+    options = {"narrow_chunk": chunk, "grid": 1 << 12}  # a workgroup for every tile
+    if fp8:
+        pool, out, stats = gpu_step_fp8(b, 0.0173, 0.0421, options=options)
+        want = oracle.mixed_attention_fp8(b.q, pool, 0.0173, 0.0421, b.page_tables, b.L, b.n, Hq, Hkv, D, b.P, b.num_pages, b.scale)
+        _, mixed, _ = gpu_step_fp8(b, 0.0173, 0.0421, options=dict(options, narrow_kernel=0))
+    else:
+        pool, out, stats = gpu_step(b, options=options)
+        want = oracle_out(b)
+        _, mixed, _ = gpu_step(b, options=dict(options, narrow_kernel=0))
+    assert stats["n_groups"] > 0 and stats["n_mfma"] == 0 and stats["n_items"] <= stats["grid"]
+    check_close(bits_to_f32(out), want)
+    assert np.array_equal(out, mixed)
+    dev = torch.device("cuda:0")
+    ctx = ppd.Context(Hq, Hkv, D, b.num_pages)
+    if fp8:
+        ctx.set_kv_format(ppd.PPD_KV_FP8_E4M3, 0.0173, 0.0421)
+    for key, value in options.items():
+        ctx.set_option(key, value)
+    dpool = torch.from_numpy(pool if fp8 else pool.view(np.int16)).to(dev)
+    q, pt = to_dev_u16(b.q, torch, dev), torch.from_numpy(b.page_tables).to(dev)
+    for call in (ctx.mixed_attention, ctx.mixed_attention, ctx.mixed_attention_static, ctx.mixed_attention_static):
+        got = torch.zeros((b.T, b.Hq, b.D), dtype=torch.int16, device=dev)
+        call(q, dpool, pt, b.L, b.n, b.scale, got)
+        torch.cuda.synchronize()
+        assert np.array_equal(from_dev_u16(got).reshape(out.shape), out)
+    ctx.close()
