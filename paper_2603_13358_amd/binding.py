@@ -1,12 +1,17 @@
 """ctypes binding of libppd.so: argument marshalling only."""
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libppd.so")
+_CALL_PATH = os.path.join(_HERE, "ppd_call.so")
 _lib = None
+_call = None       # the call module
+_fn_append = _fn_land = _fn_mixed = _fn_mixed_static = None  # addresses of the entry points it calls
 
 STATUS_NAMES = {0: "PPD_OK", -1: "PPD_ERR_NULL", -2: "PPD_ERR_SHAPE", -3: "PPD_ERR_RANGE",
                 -4: "PPD_ERR_PAGETABLE", -5: "PPD_ERR_WORKSPACE", -6: "PPD_ERR_HIP"}
@@ -51,11 +56,11 @@ def lib_path():
 
 def load_library():
     """Loads libppd.so; raises if it has not been built (no fallback of any kind)."""
-    global _lib
+    global _lib, _call, _fn_append, _fn_land, _fn_mixed, _fn_mixed_static
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError("libppd.so is not built: run `python -m paper_2603_13358_amd.build` "
+    if not os.path.exists(_LIB_PATH) or not os.path.exists(_CALL_PATH):
+        raise ImportError("libppd.so or ppd_call.so is not built: run `python -m paper_2603_13358_amd.build` "
                           "(or __graft_entry__.build()); there is no CPU path")
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
@@ -89,29 +94,17 @@ def load_library():
     for name in EXPORTS:
         if name not in ("ppd_last_error", "ppd_version", "ppd_transfer_delay_s", "ppd_route_score"):
             getattr(lib, name).restype = i32
+    loader = importlib.machinery.ExtensionFileLoader("ppd_call", _CALL_PATH)
+    _call = importlib.util.module_from_spec(importlib.util.spec_from_loader("ppd_call", loader))
+    loader.exec_module(_call)
+    _fn_append, _fn_land, _fn_mixed, _fn_mixed_static = (ctypes.cast(f, vp).value for f in (
+        lib.ppd_kv_append, lib.ppd_kv_land, lib.ppd_mixed_attention, lib.ppd_mixed_attention_static))
     _lib = lib
     return lib
 
 
-def _dev_ptr(x):
-    """Device address of a torch tensor (or an int that already is one)."""
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return x
-    return x.data_ptr()
-
-
 def _host_i32(a):
     return np.ascontiguousarray(a, dtype=np.int32)
-
-
-def _host_ptr(a):
-    """Address of a contiguous host array's first element."""
-    try:
-        return ctypes.addressof(ctypes.c_char.from_buffer(a))  # a fifth of the time of a.ctypes.data
-    except (TypeError, ValueError):  # read-only or empty
-        return a.ctypes.data
 
 
 def _check(status, ctx=None):
@@ -150,17 +143,19 @@ def ppd_set_kv_format(ctx, fmt, k_scale=1.0, v_scale=1.0):
 
 
 def ppd_kv_append(ctx, k, v, kv_pages, slot_mapping, T=None, stream=None):
-    if T is None:
-        T = int(slot_mapping.shape[0])
-    _check(load_library().ppd_kv_append(ctx, _dev_ptr(k), _dev_ptr(v), _dev_ptr(kv_pages), _dev_ptr(slot_mapping),
-                                        int(T), stream), ctx)
+    if _lib is None:
+        load_library()
+    status = _call.kv_append(_fn_append, ctx, k, v, kv_pages, slot_mapping, T, stream)
+    if status != 0:
+        _check(status, ctx)
 
 
 def ppd_kv_land(ctx, k, v, kv_pages, layer_stride_elems, num_layers, slot_mapping, T=None, stream=None):
-    if T is None:
-        T = int(slot_mapping.shape[0])
-    _check(load_library().ppd_kv_land(ctx, _dev_ptr(k), _dev_ptr(v), _dev_ptr(kv_pages), int(layer_stride_elems),
-                                      int(num_layers), _dev_ptr(slot_mapping), int(T), stream), ctx)
+    if _lib is None:
+        load_library()
+    status = _call.kv_land(_fn_land, ctx, k, v, kv_pages, layer_stride_elems, num_layers, slot_mapping, T, stream)
+    if status != 0:
+        _check(status, ctx)
 
 
 def ppd_transfer_delay_s(n_tokens, kv_bytes_per_token, beta_target_bytes_per_s, t_fast_s):
@@ -169,14 +164,15 @@ def ppd_transfer_delay_s(n_tokens, kv_bytes_per_token, beta_target_bytes_per_s, 
 
 
 def ppd_mixed_attention(ctx, q, kv_pages, page_tables, L, n, scale, out, max_pages=None, stream=None, static=False):
-    L = _host_i32(L)
-    n = _host_i32(n)
-    if max_pages is None:
-        max_pages = int(page_tables.shape[1])
-    lib = load_library()
-    fn = lib.ppd_mixed_attention_static if static else lib.ppd_mixed_attention
-    _check(fn(ctx, _dev_ptr(q), _dev_ptr(kv_pages), _dev_ptr(page_tables), int(max_pages), _host_ptr(L),
-              _host_ptr(n), int(L.shape[0]), float(scale), _dev_ptr(out), stream), ctx)
+    if _lib is None:
+        load_library()
+    fn = _fn_mixed_static if static else _fn_mixed
+    status = _call.mixed_attention(fn, ctx, q, kv_pages, page_tables, max_pages, L, n, scale, out, stream)
+    if status is None:  # lengths in another type, layout or container
+        L, n = _host_i32(L), _host_i32(n)
+        status = _call.mixed_attention(fn, ctx, q, kv_pages, page_tables, max_pages, L.reshape(-1)[:L.shape[0]], n.reshape(-1), scale, out, stream)
+    if status != 0:
+        _check(status, ctx)
 
 
 def ppd_mixed_attention_static(ctx, q, kv_pages, page_tables, L, n, scale, out, max_pages=None, stream=None):

@@ -1,11 +1,14 @@
-"""Builds libppd.so (hand-written HIP for gfx950) in-tree with hipcc.  `python -m paper_2603_13358_amd.build`."""
+"""Builds libppd.so (hand-written HIP for gfx950, with hipcc) and the call module ppd_call.so (host C) in-tree.  `python -m paper_2603_13358_amd.build`."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libppd.so")
+CALL = os.path.join(HERE, "ppd_call.so")
+CALL_SOURCE = os.path.join(CSRC, "ppd_call.c")
 SOURCES = ["ppd_api.hip", "ppd_kernels.hip", "ppd_plan.cpp", "ppd_route.cpp"]
 HEADERS = ["ppd_internal.h", os.path.join("..", "..", "include", "ppd.h")]
 
@@ -16,16 +19,28 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wal
 
 
 def is_stale():
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
+    return os.path.getmtime(CALL_SOURCE) > os.path.getmtime(CALL) or any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
+
+
+def build_call(verbose=False):
+    """Compiles the call module (CPython extension, no device code)."""
+    cc = os.environ.get("CC", "gcc")
+    cmd = [cc, "-O2", "-Wall", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"], CALL_SOURCE, "-o", CALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(cc + " failed:\n" + res.stdout)
 
 
 def build_lib(force=True, verbose=False):
-    """Compiles the library.  force=False skips the compile when the built library is newer than its sources."""
+    """Compiles the library and the call module.  force=False skips the compile when the built library is newer than its sources."""
     if not force and not is_stale():
         return LIB
+    build_call(verbose)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     # PPD_EXTRA_HIPCC_FLAGS: tuning macros of the kernels, e.g. "-DPPD_STAGES=2 -DPPD_STREAM_KSETS=2"
     extra = os.environ.get("PPD_EXTRA_HIPCC_FLAGS", "").split()

@@ -304,3 +304,51 @@ def test_bench_refuses_more_than_one_gpu_and_reads_its_traffic_file():
         b = bench.make_shapes(w, 0)
         assert t is not None and 0.9 * b.kv_read_bytes() < t < 3.0 * b.kv_read_bytes()
     assert bench.measured_traffic("no_such_workload") is None
+
+
+def test_calls_marshal_their_arguments(monkeypatch):
+    """The call module hands on what it is given: addresses of tensors, ints and None, sizes taken from shapes, lengths in any
+    container or type; a status other than 0 becomes the library's error."""
+    import ctypes
+    import torch
+    from paper_2603_13358_amd import binding
+
+    ppd.load_library()
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+    seen, status = [], [0]
+
+    def mixed(ctx, q, pages, tables, max_pages, L, n, B, scale, out, stream):
+        lengths = [list((ctypes.c_int32 * B).from_address(p)) if B else [] for p in (L, n)]
+        seen.append((ctx, q, pages, tables, max_pages, lengths, B, scale, out, stream))
+        return status[0]
+
+    def append(*args):
+        seen.append(args)
+        return status[0]
+
+    c_mixed = ctypes.CFUNCTYPE(i32, vp, vp, vp, vp, i32, vp, vp, i32, ctypes.c_float, vp, vp)(mixed)
+    c_append = ctypes.CFUNCTYPE(i32, vp, vp, vp, vp, vp, i64, vp)(append)
+    c_land = ctypes.CFUNCTYPE(i32, vp, vp, vp, vp, i64, i32, vp, i64, vp)(append)
+    for name, f in (("_fn_mixed", c_mixed), ("_fn_append", c_append), ("_fn_land", c_land)):
+        monkeypatch.setattr(binding, name, ctypes.cast(f, vp).value)
+    t, table = torch.zeros(8), torch.zeros((2, 7), dtype=torch.int32)
+    L = [5, 6]
+    for form in (np.array(L, np.int32), np.array(L), L, np.array([5, 0, 6, 0], np.int32)[::2], torch.tensor(L), np.array([[5], [6]])):
+        ppd.ppd_mixed_attention(vp(11), t, 1 << 40, table, form, np.ones(2, np.int32), 0.5, None, stream=13)
+        assert seen.pop() == (11, t.data_ptr(), 1 << 40, table.data_ptr(), 7, [[5, 6], [1, 1]], 2, 0.5, None, 13)
+    ppd.ppd_mixed_attention(11, t, t, table, [], [], 1, t, max_pages=3)
+    assert seen.pop() == (11, t.data_ptr(), t.data_ptr(), table.data_ptr(), 3, [[], []], 0, 1.0, t.data_ptr(), None)
+    slots = torch.zeros(9, dtype=torch.int64)
+    ppd.ppd_kv_append(vp(11), t, t, t, slots)
+    assert seen.pop() == (11,) + (t.data_ptr(),) * 3 + (slots.data_ptr(), 9, None)
+    ppd.ppd_kv_land(vp(11), t, None, t, 1 << 40, 32, slots, T=4, stream=vp(17))
+    assert seen.pop() == (11, t.data_ptr(), None, t.data_ptr(), 1 << 40, 32, slots.data_ptr(), 4, 17)
+    status[0] = -3
+    for call in (lambda: ppd.ppd_kv_append(None, t, t, t, slots), lambda: ppd.ppd_mixed_attention(None, t, t, table, L, L, 1.0, t)):
+        with pytest.raises(ppd.PPDError) as e:
+            call()
+        assert e.value.status == -3
+    with pytest.raises(TypeError):
+        ppd.ppd_mixed_attention(11, t, t, table, L, L, None, t)
+    with pytest.raises(AttributeError):
+        ppd.ppd_kv_append(11, "k", t, t, slots)
