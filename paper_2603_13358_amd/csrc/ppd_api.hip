@@ -379,6 +379,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.n_items = (int32_t)plan.items.size();
     kp.mean_tile_keys = plan.stats.kv_bytes_tiles / (2LL * ctx->shape.head_dim * (ctx->fp8_pages ? 1 : 2)) / plan.stats.n_items;
     kp.queue_begin = reinterpret_cast<const int32_t*>(static_cast<const char*>(d_plan) + total - bounds_bytes);
+    kp.rounds = 0;
     kp.pref_mode = ctx->opts.pref_mode;
     kp.narrow_cus = plan.narrow_cus;
     kp.max_pages = max_pages;
@@ -421,6 +422,8 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         // stop for its count while its unit could stream (66 decodes of 1K-32K, FP8 pages, 1576 tiles: +3 us of 440).  Tiles that
         // run on single waves leave their partials to the merge launch as well.
         if (n_wave == 0 && slots <= wgs) kp.merge_groups = d_groups;
+        // (by the device's workgroups: the grid option stays scheduling only, and this choice changes the rounding)
+        kp.rounds = n_wave == 0 ? (int32_t)(slots / (ppd::kWgPerCu * ctx->num_cus)) : 0;
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {

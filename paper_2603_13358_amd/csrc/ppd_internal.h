@@ -42,6 +42,8 @@ constexpr int kStreamVSets = PPD_STREAM_VSETS;
 // for long and for short tiles (launch_narrow has the figures).  In the mixed kernel four sets left its row-block loop no
 // register to spare and streamed less: 128 long decodes beside 4 turns 2804 -> 2755 us with three.
 constexpr int kMixedSets = 3, kLongSets = 3, kShortSets = 2;
+// Waves and register sets of the decode-only kernel's tiles where they are long and many (launch_narrow): one wave per SIMD.
+constexpr int kStreamingWaves = 4, kStreamingSets = 4;
 #ifndef PPD_FP8_SETS
 #define PPD_FP8_SETS 1
 #endif
@@ -133,6 +135,7 @@ struct KParams {
     int64_t num_pages;
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average
+    int32_t rounds;          // ppd_narrow_kernel: whole rounds of the device's workgroups, 0 if tiles run on single waves as well
     int32_t n_items;
     int32_t pref_mode;    // how a workgroup picks its preferred queue (see ppd_mixed_kernel)
     int32_t narrow_cus;   // pref_mode 2: compute units per XCD (of 32) that take narrow tiles first

@@ -784,7 +784,10 @@ struct NarrowCombine {
 // SOLO: the calling wave runs the whole tile on its own (NW = 1): no LDS, no barrier, the result is written from the
 // accumulator registers; the other waves of the workgroup run other tiles at the same time.
 // (bf16 pages; FP8 pages are read by narrow_item_wide.)
-template <int HD, int NW, int NK, int NV, bool SOLO = false>
+// SPLIT_P: a probability enters the second product as two bf16 numbers, its rounding and the rounding of what that left out.
+// The probabilities of a wave are rounded relative to the wave's own running reference, and fewer waves have fewer of them:
+// four waves without it would have more rounding error than eight.
+template <int HD, int NW, int NK, int NV, bool SOLO = false, bool SPLIT_P = false>
 __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
     constexpr int EB = 2;  // bytes per pool element
@@ -916,6 +919,16 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
 #pragma unroll
         for (int db = 0; db < DBN; ++db)
             oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), pb4, oacc[db], 0, 0, 0);
+        if constexpr (SPLIT_P) {
+            float rest[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rest[i] = p[i] - __builtin_bit_cast(float, (i & 1) ? pw[i >> 1] & 0xFFFF0000u : pw[i >> 1] << 16);
+            const u32x2 rp = {pack_bf16(rest[0], rest[1]), pack_bf16(rest[2], rest[3])};
+            const s16x4 rb4 = __builtin_bit_cast(s16x4, rp);
+#pragma unroll
+            for (int db = 0; db < DBN; ++db)
+                oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), rb4, oacc[db], 0, 0, 0);
+        }
     };
 
     // K of NK - 1 pages and V of NV - 1 pages (4 KiB each at D = 128) are in flight per wave while one page is being
@@ -1528,10 +1541,11 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // index, rounds running alternately up and down the workgroups (no atomics at all: same step time on short tiles,
 // +3 % on long ones).
 // NSETS: rotating register sets (one page each) of a streaming wave on bf16 pages, kLongSets where the tiles are long and
-// kShortSets where they are short (see launch_narrow).
+// kShortSets where they are short.  NW: eight waves, or four of twice the registers where the tiles are long and there are many
+// (see launch_narrow for both).
 // ---------------------------------------------------------------------------------------------------
 template <int HD, bool FP8, int NW, int NSETS>
-__global__ __launch_bounds__(64 * NW, 2) void ppd_narrow_kernel(const KParams P) {
+__global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const KParams P) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // the combine buffer
     __shared__ int s_next_slot, s_arrived;
     volatile int* s_next = &s_next_slot;
@@ -1545,9 +1559,10 @@ __global__ __launch_bounds__(64 * NW, 2) void ppd_narrow_kernel(const KParams P)
         if (slot < n_wg) {
             const ppd_work_item it = P.items[wg_begin + slot];
             if constexpr (FP8) narrow_item_wide<HD, NW, kFp8StreamSets, false, true>(P, it, smem);
-            else narrow_item<HD, NW, NSETS, NSETS, false>(P, it, smem);
-            if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, P.items + wg_begin + slot, smem, &s_arrived);
-        } else {
+            else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves>(P, it, smem);
+            if constexpr (NW == kWaves)  // four waves run launches of several rounds only
+                if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, P.items + wg_begin + slot, smem, &s_arrived);
+        } else if constexpr (NW == kWaves) {
             const int mine = wave_begin + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
             if (mine < end) {
                 const ppd_work_item it = P.items[mine];
@@ -1895,6 +1910,7 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<128, true>), mixed_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, true>), mixed_lds_bytes(64));
     constexpr int NW = kNarrowKernelWaves;
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), NarrowCombine<kStreamingWaves>::bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kLongSets>), NarrowCombine<NW>::bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kShortSets>), NarrowCombine<NW>::bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, false, NW, kShortSets>), NarrowCombine<NW>::bytes(64));
@@ -1929,8 +1945,17 @@ int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool f
     // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
     // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
     const bool long_tiles = p.mean_tile_keys >= 1536;
+    // Where every unit streams long tiles one after the other, HBM is the bound, and it delivers more to half the waves, each with
+    // one more page in flight: us of 128 sequences of 7000-8000 keys by 8 heads 597 -> 574 (6.6 -> 6.9 TB/s), 64 of 3200-6400
+    // 192.8 -> 187.0, 128 of 1000-8000 345 -> 339, 256 of them 697 -> 687.  A unit alone streams less that way (42 against 52
+    // GB/s), so launches of less than two rounds stay on eight waves (16 sequences of 3200-6400 keys 70 -> 83), and so do tiles
+    // below 3072 keys, where the gain ends: 256 of 1600-2000 297 -> 298, 32 of 3200-6400 (512 tiles of 2400) 103.9 -> 107.2.
+    const bool streaming = p.mean_tile_keys >= 3072 && p.rounds >= 2;
     if (head_dim == 128 && fp8_pages)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
+    else if (head_dim == 128 && streaming)
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), dim3(grid), dim3(64 * kStreamingWaves),
+                           NarrowCombine<kStreamingWaves>::bytes(128), st, p);
     else if (head_dim == 128 && long_tiles)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kLongSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
     else if (head_dim == 128)

@@ -303,3 +303,43 @@ def test_split_ranges_are_merged_by_their_last_tile(Hq, Hkv, D, L, n, chunk, fp8
         torch.cuda.synchronize()
         assert np.array_equal(from_dev_u16(got).reshape(out.shape), out)
     ctx.close()
+
+
+@pytest.mark.parametrize("G,rows,chunk", [(4, 1, 8192), (1, 16, 8192), (8, 2, 8192), (5, 3, 4096)])
+def test_rounds_of_long_tiles_run_on_four_waves(G, rows, chunk):
+    """Decode-only launches of at least two rounds of tiles of 3072 keys and more (64 sequences that share two sequences' pages, 8 KV
+    heads; with split ranges in the last case): the oracle's result, with less error than eight waves have, whose probabilities
+    are rounded once (0.71 of it was measured)."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    B, longest = 64, 8192 if chunk < 8192 else 4400
+    rng = np.random.default_rng(G)
+    base = si.make_batch("four", L=[longest - 1, longest - 9], n=[1, 1], Hq=8, Hkv=8, D=128, seed=G, slack_pages=2)
+    pool, _, _ = gpu_step(base)
+    low = 6400 if chunk < 8192 else 3100
+    n = np.where(np.arange(B) % 5 == 0, rows, 1).astype(np.int32)
+    L = (rng.integers(low, longest - 30, B)).astype(np.int32)
+    L[:4] = [low, longest - 30, (longest - 30) // 16 * 16 - 1, (longest - 30) // 16 * 16]
+    tables = base.page_tables[np.arange(B) % 2]
+    q = (rng.standard_normal((int(n.sum()), 8 * G, 128)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    scale = 1.0 / np.sqrt(128.0)
+    want = oracle.mixed_attention(q, pool, tables, L, n, 8 * G, 8, 128, 16, base.num_pages, scale)
+    dev = torch.device("cuda:0")
+    dpool, dq, dt = to_dev_u16(pool, torch, dev), to_dev_u16(q, torch, dev), torch.from_numpy(np.ascontiguousarray(tables)).to(dev)
+    errors = []
+    for narrow_kernel in (1, 0):
+        ctx = ppd.Context(8 * G, 8, 128, base.num_pages)
+        ctx.set_option("narrow_chunk", chunk)
+        ctx.set_option("narrow_kernel", narrow_kernel)
+        out = torch.zeros((len(q), 8 * G, 128), dtype=torch.int16, device=dev)
+        ctx.mixed_attention(dq, dpool, dt, L, n, scale, out)
+        torch.cuda.synchronize()
+        stats = ctx.plan_stats()
+        assert stats.n_mfma == 0 and stats.n_narrow >= 512 and stats.kv_bytes_tiles >= stats.n_narrow * 512 * 3072
+        assert (stats.n_groups > 0) == (chunk < 8192) and ctx.device_error_flags() == 0
+        got = bits_to_f32(from_dev_u16(out)).reshape(want.shape)
+        check_close(got, want)
+        errors.append(np.linalg.norm(got.astype(np.float64) - want))
+        ctx.close()
+    assert errors[0] <= 0.875 * errors[1], errors
