@@ -380,6 +380,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.mean_tile_keys = plan.stats.kv_bytes_tiles / (2LL * ctx->shape.head_dim * (ctx->fp8_pages ? 1 : 2)) / plan.stats.n_items;
     kp.queue_begin = reinterpret_cast<const int32_t*>(static_cast<const char*>(d_plan) + total - bounds_bytes);
     kp.rounds = 0;
+    kp.by_index = 0;
     kp.pref_mode = ctx->opts.pref_mode;
     kp.narrow_cus = plan.narrow_cus;
     kp.max_pages = max_pages;
@@ -423,6 +424,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         // run on single waves leave their partials to the merge launch as well.
         if (n_wave == 0 && slots <= wgs) kp.merge_groups = d_groups;
         // (by the device's workgroups: the grid option stays scheduling only, and this choice changes the rounding)
+        kp.by_index = slots <= 2 * wgs && kp.mean_tile_keys * (ctx->fp8_pages ? 1 : 2) < 3072;  // (1536 keys of bf16 pages)
         kp.rounds = n_wave == 0 ? (int32_t)(slots / (ppd::kWgPerCu * ctx->num_cus)) : 0;
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");

@@ -1536,10 +1536,13 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // (longest first) and then the one-wave tiles, NW to a slot, form one row of slots; workgroup b takes slot b
 // without asking, and only a launch with more slots than workgroups claims further ones (from gridDim.x on) with the
 // cursor of the narrow queue, which the last workgroup to finish re-arms.  The host launches no more workgroups than
-// there are slots.  Measured and not kept: claiming the next slot before running the current one (hides the round
-// trip but holds a slot that an idle workgroup could have run: cfg2 186 -> 206 us), and handing out all slots by
-// index, rounds running alternately up and down the workgroups (no atomics at all: same step time on short tiles,
-// +3 % on long ones).
+// there are slots.  Where two rounds are enough and the tiles are short, the second is handed out by index as well, from the
+// end of the list: the claims (a trip to the memory side for every slot, and one more for each workgroup to learn that nothing is
+// left) take as long as a fifth of such a launch.  us of 64 sequences with the append, claimed and by index: D = 128, 64-380 keys
+// 19.9 and 18.6, 400-800 33.0 and 31.9, FP8 pages 25.3 and 23.8; D = 64, 64-380 16.0 and 13.1, 400-800 21.6 and 18.9.  Longer tiles
+// and more rounds are claimed, because they do not take the time that their length says (48 of 2000-6000 keys 129.8 and 133.7, 100
+// of 800-1600 88.0 and 90.8, 400 of 800-1600 314 and 327).  Measured and not kept: claiming the next slot before running the
+// current one (hides the round trip but holds a slot that an idle workgroup could have run: cfg2 186 -> 206 us).
 // NSETS: rotating register sets (one page each) of a streaming wave on bf16 pages, kLongSets where the tiles are long and
 // kShortSets where they are short.  NW: eight waves, or four of twice the registers where the tiles are long and there are many
 // (see launch_narrow for both).
@@ -1553,7 +1556,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const KPara
     const int wg_begin = P.queue_begin[kNarrowQueue], wave_begin = P.queue_begin[kWaveQueue], end = P.queue_begin[kQueues];
     const int n_wg = wave_begin - wg_begin;
     const int slots = n_wg + (end - wave_begin + NW - 1) / NW;
-    const bool claims = slots > (int)gridDim.x;  // the same for every workgroup of the launch
+    const bool claims = slots > (int)gridDim.x && !P.by_index;  // the same for every workgroup of the launch
     int slot = blockIdx.x;
     while (slot < slots) {
         if (slot < n_wg) {
@@ -1570,7 +1573,12 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const KPara
                 else narrow_item<HD, 1, NSETS, NSETS, true>(P, it, smem);
             }
         }
-        if (!claims) break;
+        if (!claims) {
+            // by index: a second slot from the end of the list, so that the longest and the shortest tiles meet
+            slot = slot < (int)gridDim.x ? 2 * (int)gridDim.x - 1 - slot : slots;
+            if (slot < slots) __syncthreads();  // the tile's combine is over
+            continue;
+        }
         if (tid == 0) *s_next = (int)gridDim.x + (int)atomicAdd(&P.counters[kCursorBase + kNarrowQueue * kCursorStride], 1u);
         __syncthreads();
         slot = __builtin_amdgcn_readfirstlane(*s_next);

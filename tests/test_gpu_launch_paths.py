@@ -343,3 +343,27 @@ def test_rounds_of_long_tiles_run_on_four_waves(G, rows, chunk):
         errors.append(np.linalg.norm(got.astype(np.float64) - want))
         ctx.close()
     assert errors[0] <= 0.875 * errors[1], errors
+
+
+@pytest.mark.parametrize("B", [8, 9, 15, 16, 17, 25])
+@pytest.mark.parametrize("fp8,wave", [(False, 0), (True, 0), (False, 1)])
+def test_two_rounds_of_short_tiles_are_handed_out_by_index(B, fp8, wave):
+    """Around one and two slots for each of 8 workgroups (from the 17th on they are claimed): the oracle's result, bit for bit the
+    mixed kernel's, twice."""
+    rng = np.random.default_rng(B)
+    L = rng.integers(0, 900, B)
+    L[:2] = [1535, 0]
+    b = si.make_batch("index", L=L, n=np.ones(B, np.int64), Hq=4, Hkv=1, D=128, seed=B, slack_pages=2)
+    options = {"grid": 8, "wave_tiles": wave, "narrow_chunk": 2048}
+
+    def step(extra):
+        if fp8:
+            return gpu_step_fp8(b, 0.0173, 0.0421, options=dict(options, **extra))
+        return gpu_step(b, options=dict(options, **extra))
+
+    pool, out, stats = step({})
+    assert stats["n_items"] == B
+    want = oracle.mixed_attention_fp8(b.q, pool, 0.0173, 0.0421, b.page_tables, b.L, b.n, 4, 1, 128, b.P, b.num_pages, b.scale) if fp8 else oracle_out(b)
+    check_close(bits_to_f32(out), want)
+    for extra in ({}, {"narrow_kernel": 0}):
+        assert np.array_equal(step(extra)[1], out)
