@@ -652,7 +652,7 @@ def main():
     roofline["traffic"] = None if args.kv_fp8 else measured_traffic(args.workload)
     fp8_s = "true" if args.kv_fp8 else "false"
     if main_res["plan"]["n_mfma"] == 0 and options.get("narrow_kernel", 1) and not options.get("launch_mode", 0):
-        roofline["kernel"] = "ppd_narrow_kernel<128, %s, 8>" % fp8_s  # a step without row-block tiles: <head_dim, FP8 pages, waves>
+        roofline["kernel"] = "ppd_narrow_kernel<128, %s>" % fp8_s  # a step without row-block tiles: <head_dim, FP8 pages>; waves and sets go by its sizes
     else:
         roofline["kernel"] = "ppd_mixed_kernel<128, %s>" % fp8_s  # <head_dim, FP8 pages>
     roofline["kernel_ms"] = main_res["mixed_kernel_ms"]

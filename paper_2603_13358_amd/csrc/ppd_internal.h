@@ -51,8 +51,8 @@ constexpr int kStreamingWaves = 4, kStreamingSets = 4;
 // loads going.  A second set gained nothing on long ranges (128 decodes of 1K-32K 1353 -> 1346 us without it) and its spilled
 // scalars cost short ones 7 % (one decode of 4000 keys 20.5 -> 19.1 us a layer).
 constexpr int kFp8StreamSets = PPD_FP8_SETS;
-// Waves per workgroup of ppd_narrow_kernel.  Two workgroups of four waves per unit (two tiles in flight there) measured
-// the same on short tiles and 10 % slower on cfg2, so it runs its tiles exactly as ppd_mixed_kernel does.
+// Waves per workgroup of ppd_narrow_kernel, but for rounds of long tiles (kStreamingWaves).  Two workgroups of four waves per
+// unit (two tiles in flight there) measured the same on short tiles and 10 % slower on cfg2.
 constexpr int kNarrowKernelWaves = kWaves;
 constexpr int kXcds = 8;             // MFMA tile queues, one per XCD (each XCD has its own L2)
 constexpr int kNarrowQueue = kXcds;  // index of the narrow-tile queue
