@@ -379,6 +379,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.n_items = (int32_t)plan.items.size();
     kp.mean_tile_keys = plan.stats.kv_bytes_tiles / (2LL * ctx->shape.head_dim * (ctx->fp8_pages ? 1 : 2)) / plan.stats.n_items;
     kp.queue_begin = reinterpret_cast<const int32_t*>(static_cast<const char*>(d_plan) + total - bounds_bytes);
+    kp.n_wg = plan.queue_begin[ppd::kWaveQueue];
     kp.rounds = 0;
     kp.by_index = 0;
     kp.pref_mode = ctx->opts.pref_mode;

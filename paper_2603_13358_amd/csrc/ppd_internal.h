@@ -136,6 +136,7 @@ struct KParams {
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average
     int32_t rounds;          // ppd_narrow_kernel: whole rounds of the device's workgroups, 0 if tiles run on single waves as well
+    int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed
     int32_t n_items;
     int32_t pref_mode;    // how a workgroup picks its preferred queue (see ppd_mixed_kernel)

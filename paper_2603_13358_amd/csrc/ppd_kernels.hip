@@ -1543,32 +1543,33 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // and more rounds are claimed, because they do not take the time that their length says (48 of 2000-6000 keys 129.8 and 133.7, 100
 // of 800-1600 88.0 and 90.8, 400 of 800-1600 314 and 327).  Measured and not kept: claiming the next slot before running the
 // current one (hides the round trip but holds a slot that an idle workgroup could have run: cfg2 186 -> 206 us).
+// The list and its bounds (n_wg whole-workgroup tiles, `end` tiles in all) are arguments of their own, which arrive in scalar registers:
+// a workgroup's first read is its work item, where it used to be the arguments, then the bounds, then the item (6 decodes of
+// 1K-3K keys 20.0 -> 19.7 us a layer, 11 of 300-6500 33.4 -> 33.1).
 // NSETS: rotating register sets (one page each) of a streaming wave on bf16 pages, kLongSets where the tiles are long and
 // kShortSets where they are short.  NW: eight waves, or four of twice the registers where the tiles are long and there are many
 // (see launch_narrow for both).
 // ---------------------------------------------------------------------------------------------------
 template <int HD, bool FP8, int NW, int NSETS>
-__global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const KParams P) {
+__global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_work_item* items, int n_wg, int end, const KParams P) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // the combine buffer
     __shared__ int s_next_slot, s_arrived;
     volatile int* s_next = &s_next_slot;
     const int tid = threadIdx.x;
-    const int wg_begin = P.queue_begin[kNarrowQueue], wave_begin = P.queue_begin[kWaveQueue], end = P.queue_begin[kQueues];
-    const int n_wg = wave_begin - wg_begin;
-    const int slots = n_wg + (end - wave_begin + NW - 1) / NW;
+    const int slots = n_wg + (end - n_wg + NW - 1) / NW;
     const bool claims = slots > (int)gridDim.x && !P.by_index;  // the same for every workgroup of the launch
     int slot = blockIdx.x;
     while (slot < slots) {
         if (slot < n_wg) {
-            const ppd_work_item it = P.items[wg_begin + slot];
+            const ppd_work_item it = items[slot];
             if constexpr (FP8) narrow_item_wide<HD, NW, kFp8StreamSets, false, true>(P, it, smem);
             else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves>(P, it, smem);
             if constexpr (NW == kWaves)  // four waves run launches of several rounds only
-                if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, P.items + wg_begin + slot, smem, &s_arrived);
+                if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, &s_arrived);
         } else if constexpr (NW == kWaves) {
-            const int mine = wave_begin + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
+            const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
             if (mine < end) {
-                const ppd_work_item it = P.items[mine];
+                const ppd_work_item it = items[mine];
                 if constexpr (FP8) narrow_item_wide<HD, 1, kFp8StreamSets, true, true>(P, it, smem);
                 else narrow_item<HD, 1, NSETS, NSETS, true>(P, it, smem);
             }
@@ -1960,18 +1961,18 @@ int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool f
     // below 3072 keys, where the gain ends: 256 of 1600-2000 297 -> 298, 32 of 3200-6400 (512 tiles of 2400) 103.9 -> 107.2.
     const bool streaming = p.mean_tile_keys >= 3072 && p.rounds >= 2;
     if (head_dim == 128 && fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
     else if (head_dim == 128 && streaming)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), dim3(grid), dim3(64 * kStreamingWaves),
-                           NarrowCombine<kStreamingWaves>::bytes(128), st, p);
+                           NarrowCombine<kStreamingWaves>::bytes(128), st, p.items, p.n_wg, p.n_items, p);
     else if (head_dim == 128 && long_tiles)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kLongSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kLongSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
     else if (head_dim == 128)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
     else if (fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
     else
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<64, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
     return (int)hipGetLastError();
 }
 
