@@ -380,7 +380,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.mean_tile_keys = plan.stats.kv_bytes_tiles / (2LL * ctx->shape.head_dim * (ctx->fp8_pages ? 1 : 2)) / plan.stats.n_items;
     kp.queue_begin = reinterpret_cast<const int32_t*>(static_cast<const char*>(d_plan) + total - bounds_bytes);
     kp.n_wg = plan.queue_begin[ppd::kWaveQueue];
-    kp.rounds = 0;
+    kp.four_waves = 0;
     kp.by_index = 0;
     kp.pref_mode = ctx->opts.pref_mode;
     kp.narrow_cus = plan.narrow_cus;
@@ -423,10 +423,12 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         // pages 18.2 -> 16.6, 11 decodes of 300-6500 keys 34.4 -> 33.4).  With more rounds every tile but the last ones would
         // stop for its count while its unit could stream (66 decodes of 1K-32K, FP8 pages, 1576 tiles: +3 us of 440).  Tiles that
         // run on single waves leave their partials to the merge launch as well.
-        if (n_wave == 0 && slots <= wgs) kp.merge_groups = d_groups;
-        // (by the device's workgroups: the grid option stays scheduling only, and this choice changes the rounding)
+        // Nor do the four-wave tiles merge; they are chosen by the device's workgroups and not by the launch's, because they round
+        // differently and the grid option stays scheduling only.
+        const int64_t rounds = n_wave == 0 ? slots / (ppd::kWgPerCu * ctx->num_cus) : 0;
+        kp.four_waves = ppd::runs_on_four_waves(D, ctx->fp8_pages, kp.mean_tile_keys, rounds);
+        if (n_wave == 0 && slots <= wgs && !kp.four_waves) kp.merge_groups = d_groups;
         kp.by_index = slots <= 2 * wgs && kp.mean_tile_keys * (ctx->fp8_pages ? 1 : 2) < 3072;  // (1536 keys of bf16 pages)
-        kp.rounds = n_wave == 0 ? (int32_t)(slots / (ppd::kWgPerCu * ctx->num_cus)) : 0;
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {

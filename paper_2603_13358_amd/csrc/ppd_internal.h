@@ -42,8 +42,16 @@ constexpr int kStreamVSets = PPD_STREAM_VSETS;
 // for long and for short tiles (launch_narrow has the figures).  In the mixed kernel four sets left its row-block loop no
 // register to spare and streamed less: 128 long decodes beside 4 turns 2804 -> 2755 us with three.
 constexpr int kMixedSets = 3, kLongSets = 3, kShortSets = 2;
-// Waves and register sets of the decode-only kernel's tiles where they are long and many (launch_narrow): one wave per SIMD.
+// Waves and register sets of the decode-only kernel's tiles where they are long and many: one wave per SIMD.
 constexpr int kStreamingWaves = 4, kStreamingSets = 4;
+// Where every unit streams long tiles one after the other, HBM is the bound, and it delivers more to half the waves, each with
+// one more page in flight: us of 128 sequences of 7000-8000 keys by 8 heads 597 -> 574 (6.6 -> 6.9 TB/s), 64 of 3200-6400
+// 192.8 -> 187.0, 128 of 1000-8000 345 -> 339, 256 of them 697 -> 687.  A unit alone streams less that way (42 against 52
+// GB/s), so launches of less than two rounds stay on eight waves (16 sequences of 3200-6400 keys 70 -> 83), and so do tiles
+// below 3072 keys, where the gain ends: 256 of 1600-2000 297 -> 298, 32 of 3200-6400 (512 tiles of 2400) 103.9 -> 107.2.
+inline bool runs_on_four_waves(int head_dim, bool fp8_pages, int64_t mean_tile_keys, int64_t rounds) {
+    return head_dim == 128 && !fp8_pages && mean_tile_keys >= 3072 && rounds >= 2;
+}
 #ifndef PPD_FP8_SETS
 #define PPD_FP8_SETS 1
 #endif
@@ -135,7 +143,7 @@ struct KParams {
     int64_t num_pages;
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average
-    int32_t rounds;          // ppd_narrow_kernel: whole rounds of the device's workgroups, 0 if tiles run on single waves as well
+    int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (runs_on_four_waves), which leaves split ranges to ppd_merge_kernel
     int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed
     int32_t n_items;

@@ -1548,7 +1548,7 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // 1K-3K keys 20.0 -> 19.7 us a layer, 11 of 300-6500 33.4 -> 33.1).
 // NSETS: rotating register sets (one page each) of a streaming wave on bf16 pages, kLongSets where the tiles are long and
 // kShortSets where they are short.  NW: eight waves, or four of twice the registers where the tiles are long and there are many
-// (see launch_narrow for both).
+// (runs_on_four_waves); launch_narrow has the figures of the former.
 // ---------------------------------------------------------------------------------------------------
 template <int HD, bool FP8, int NW, int NSETS>
 __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_work_item* items, int n_wg, int end, const KParams P) {
@@ -1564,7 +1564,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
             const ppd_work_item it = items[slot];
             if constexpr (FP8) narrow_item_wide<HD, NW, kFp8StreamSets, false, true>(P, it, smem);
             else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves>(P, it, smem);
-            if constexpr (NW == kWaves)  // four waves run launches of several rounds only
+            if constexpr (NW == kWaves)  // the host gives the four-wave form no merge_groups
                 if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, &s_arrived);
         } else if constexpr (NW == kWaves) {
             const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1954,15 +1954,9 @@ int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool f
     // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
     // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
     const bool long_tiles = p.mean_tile_keys >= 1536;
-    // Where every unit streams long tiles one after the other, HBM is the bound, and it delivers more to half the waves, each with
-    // one more page in flight: us of 128 sequences of 7000-8000 keys by 8 heads 597 -> 574 (6.6 -> 6.9 TB/s), 64 of 3200-6400
-    // 192.8 -> 187.0, 128 of 1000-8000 345 -> 339, 256 of them 697 -> 687.  A unit alone streams less that way (42 against 52
-    // GB/s), so launches of less than two rounds stay on eight waves (16 sequences of 3200-6400 keys 70 -> 83), and so do tiles
-    // below 3072 keys, where the gain ends: 256 of 1600-2000 297 -> 298, 32 of 3200-6400 (512 tiles of 2400) 103.9 -> 107.2.
-    const bool streaming = p.mean_tile_keys >= 3072 && p.rounds >= 2;
     if (head_dim == 128 && fp8_pages)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
-    else if (head_dim == 128 && streaming)
+    else if (head_dim == 128 && p.four_waves)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), dim3(grid), dim3(64 * kStreamingWaves),
                            NarrowCombine<kStreamingWaves>::bytes(128), st, p.items, p.n_wg, p.n_items, p);
     else if (head_dim == 128 && long_tiles)

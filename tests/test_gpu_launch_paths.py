@@ -367,3 +367,45 @@ def test_two_rounds_of_short_tiles_are_handed_out_by_index(B, fp8, wave):
     check_close(bits_to_f32(out), want)
     for extra in ({}, {"narrow_kernel": 0}):
         assert np.array_equal(step(extra)[1], out)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("G,grid", [(4, 0), (4, 1024), (1, 600), (8, 512)])
+def test_long_split_tiles_are_merged_whatever_the_grid(G, grid, static):
+    """Decode-only launches of at least two rounds of long tiles with split ranges, whole ones and ranges of one to three
+    pages beside them, with fewer workgroups than tiles (grid 0) and with one for each (the sequences share two sequences'
+    pages): the oracle's result, bit for bit that of the automatic grid."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    B, longest = 40, 13000
+    rng = np.random.default_rng(G)
+    base = si.make_batch("grid", L=[longest - 1, longest - 9], n=[1, 1], Hq=8, Hkv=8, D=128, seed=G, slack_pages=2)
+    pool, _, _ = gpu_step(base)
+    L = rng.integers(8200, longest - 30, B).astype(np.int32)
+    L[:8] = [0, 15, 40, 47, 5000, 8191, 8192, longest - 30]
+    n = np.ones(B, np.int32)
+    tables = np.ascontiguousarray(base.page_tables[np.arange(B) % 2])
+    q = (rng.standard_normal((B, 8 * G, 128)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    scale = 1.0 / np.sqrt(128.0)
+    want = oracle.mixed_attention(q, pool, tables, L, n, 8 * G, 8, 128, 16, base.num_pages, scale)
+    dev = torch.device("cuda:0")
+    dpool, dq, dt = to_dev_u16(pool, torch, dev), to_dev_u16(q, torch, dev), torch.from_numpy(tables).to(dev)
+    outs = []
+    for g in (grid, 0):
+        ctx = ppd.Context(8 * G, 8, 128, base.num_pages)
+        ctx.set_option("narrow_chunk", 8192)
+        ctx.set_option("grid", g)
+        call = ctx.mixed_attention_static if static else ctx.mixed_attention
+        for _ in range(2):
+            out = torch.zeros((B, 8 * G, 128), dtype=torch.int16, device=dev)
+            call(dq, dpool, dt, L, n, scale, out)
+            torch.cuda.synchronize()
+            outs.append(from_dev_u16(out))
+        stats = ctx.plan_stats()
+        assert stats.n_mfma == 0 and stats.n_groups > 0 and stats.n_items >= 512 and ctx.device_error_flags() == 0
+        assert stats.kv_bytes_tiles >= stats.n_items * 512 * 3072 and (g == 0 or stats.n_items <= stats.grid or g == 512)
+        ctx.close()
+    check_close(bits_to_f32(outs[0]).reshape(want.shape), want)
+    for other in outs[1:]:
+        assert np.array_equal(outs[0], other)
