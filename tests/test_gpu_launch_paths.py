@@ -409,3 +409,54 @@ def test_long_split_tiles_are_merged_whatever_the_grid(G, grid, static):
     check_close(bits_to_f32(outs[0]).reshape(want.shape), want)
     for other in outs[1:]:
         assert np.array_equal(outs[0], other)
+
+
+@pytest.mark.parametrize("options", [{}, {"narrow_chunk": 4096}])
+def test_infinite_values_stay_infinite_on_four_waves(options):
+    """Decode-only launches of at least two rounds of long tiles over V elements of +inf and of -inf, of one key and of
+    several (the keys of a wave's largest probability among them): those columns of every row that sees them are infinite, as
+    they are on eight waves, and the other columns do not notice."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    B, Hq, D, longest = 64, 16, 128, 8192
+    rng = np.random.default_rng(7)
+    base = si.make_batch("inf", L=[longest - 1] * 2, n=[1, 1], Hq=8, Hkv=8, D=D, seed=7, slack_pages=2)
+    pool, _, _ = gpu_step(base)
+    finite = pool.copy()
+    v = pool.reshape(base.num_pages, 2, 8, 2, D, 8)[:, 1]  # page, head, token octet, d, token of the octet (a view)
+    columns = np.arange(0, D, 3)
+    sign = np.where(columns % 2, -1.0, 1.0)
+    for s in range(2):
+        for i, d in enumerate(columns):
+            # one key for some columns, every key of the first 4096 for others
+            keys = rng.integers(0, 4096, 1) if i % 3 else np.arange(4096)
+            v[base.page_tables[s, keys // 16], :, keys % 16 // 8, d, keys % 8] = 0x7F80 if sign[i] > 0 else 0xFF80
+    L = rng.integers(6200, longest - 30, B).astype(np.int32)
+    n = np.ones(B, np.int32)
+    tables = np.ascontiguousarray(base.page_tables[np.arange(B) % 2])
+    q = (rng.standard_normal((B, Hq, D)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    scale = 1.0 / np.sqrt(D)
+    dev = torch.device("cuda:0")
+    dq, dt = to_dev_u16(q, torch, dev), torch.from_numpy(tables).to(dev)
+
+    def run(bits, narrow_kernel):
+        ctx = ppd.Context(Hq, 8, D, base.num_pages)
+        for key, value in dict({"narrow_chunk": 8192}, **options).items():
+            ctx.set_option(key, value)
+        ctx.set_option("narrow_kernel", narrow_kernel)
+        out = torch.zeros((B, Hq, D), dtype=torch.int16, device=dev)
+        ctx.mixed_attention(dq, to_dev_u16(bits, torch, dev), dt, L, n, scale, out)
+        torch.cuda.synchronize()
+        stats = ctx.plan_stats()
+        assert stats.n_mfma == 0 and stats.n_items >= 512 and stats.kv_bytes_tiles >= stats.n_items * 512 * 3072
+        ctx.close()
+        return bits_to_f32(from_dev_u16(out)).reshape(B, Hq, D)
+
+    plain = run(finite, 1)
+    for narrow_kernel in (0, 1):
+        got = run(pool, narrow_kernel)
+        assert np.array_equal(got[:, :, columns], np.broadcast_to(sign * np.inf, (B, Hq, len(columns)))), narrow_kernel
+        rest = np.setdiff1d(np.arange(D), columns)
+        if narrow_kernel:
+            assert np.array_equal(got[:, :, rest], plain[:, :, rest])
