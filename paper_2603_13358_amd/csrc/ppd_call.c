@@ -8,24 +8,32 @@
 #include <stdint.h>
 
 static PyObject *s_data_ptr, *s_value, *s_shape;
+static PyObject *t_void_p, *f_cast;  // ctypes.c_void_p and ctypes.cast
 
-// None, an int, a handle with `value` (ctypes.c_void_p) or a tensor with data_ptr() -> address
-static int to_address(PyObject* o, PyObject* attribute, void** out) {
+// What a ctypes parameter of type c_void_p takes: None, an int and a c_void_p (a context's handle) here, anything else --
+// objects with _as_parameter_ (torch.cuda.Stream is one), pointers, arrays -- by ctypes itself, which also refuses the rest
+static int to_handle(PyObject* o, void** out) {
     *out = NULL;
     if (o == Py_None) return 1;
     if (PyLong_Check(o)) {
         *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
         return !PyErr_Occurred();
     }
-    PyObject* v = attribute == s_value ? PyObject_GetAttr(o, attribute) : PyObject_CallMethodNoArgs(o, attribute);
+    PyObject* p = (PyObject*)Py_TYPE(o) == t_void_p ? Py_NewRef(o) : PyObject_CallFunctionObjArgs(f_cast, o, t_void_p, NULL);
+    if (!p) return 0;
+    PyObject* v = PyObject_GetAttr(p, s_value);
+    Py_DECREF(p);
     if (!v) return 0;
-    int ok = v == Py_None;
-    if (!ok && PyLong_Check(v)) {
-        *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
-        ok = !PyErr_Occurred();
-    } else if (!ok) {
-        PyErr_SetString(PyExc_TypeError, "an address must be an int");
-    }
+    if (v != Py_None) *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
+    Py_DECREF(v);
+    return !PyErr_Occurred();
+}
+// a tensor's data_ptr(), or None or an int that already is an address
+static int to_address(PyObject* o, void** out) {
+    if (o == Py_None || PyLong_Check(o)) return to_handle(o, out);
+    PyObject* v = PyObject_CallMethodNoArgs(o, s_data_ptr);
+    if (!v) return 0;
+    const int ok = to_handle(v, out);
     Py_DECREF(v);
     return ok;
 }
@@ -63,9 +71,9 @@ static PyObject* call_append(PyObject* self, PyObject* const* a, Py_ssize_t n) {
     void *fn, *ctx, *k, *v, *pages, *slots, *stream;
     int64_t T;
     (void)self;
-    if (!expect(n, 8) || !to_address(a[0], s_value, &fn) || !to_address(a[1], s_value, &ctx) || !to_int_or_shape(a[6], a[5], 0, &T) ||
-        !to_address(a[2], s_data_ptr, &k) || !to_address(a[3], s_data_ptr, &v) || !to_address(a[4], s_data_ptr, &pages) ||
-        !to_address(a[5], s_data_ptr, &slots) || !to_address(a[7], s_value, &stream))
+    if (!expect(n, 8) || !to_handle(a[0], &fn) || !to_handle(a[1], &ctx) || !to_int_or_shape(a[6], a[5], 0, &T) ||
+        !to_address(a[2], &k) || !to_address(a[3], &v) || !to_address(a[4], &pages) ||
+        !to_address(a[5], &slots) || !to_handle(a[7], &stream))
         return NULL;
     int32_t status;
     Py_BEGIN_ALLOW_THREADS
@@ -79,9 +87,9 @@ static PyObject* call_land(PyObject* self, PyObject* const* a, Py_ssize_t n) {
     void *fn, *ctx, *k, *v, *pages, *slots, *stream;
     int64_t stride, layers, T;
     (void)self;
-    if (!expect(n, 10) || !to_address(a[0], s_value, &fn) || !to_address(a[1], s_value, &ctx) || !to_int_or_shape(a[8], a[7], 0, &T) ||
-        !to_address(a[2], s_data_ptr, &k) || !to_address(a[3], s_data_ptr, &v) || !to_address(a[4], s_data_ptr, &pages) ||
-        !to_int(a[5], &stride) || !to_int(a[6], &layers) || !to_address(a[7], s_data_ptr, &slots) || !to_address(a[9], s_value, &stream))
+    if (!expect(n, 10) || !to_handle(a[0], &fn) || !to_handle(a[1], &ctx) || !to_int_or_shape(a[8], a[7], 0, &T) ||
+        !to_address(a[2], &k) || !to_address(a[3], &v) || !to_address(a[4], &pages) ||
+        !to_int(a[5], &stride) || !to_int(a[6], &layers) || !to_address(a[7], &slots) || !to_handle(a[9], &stream))
         return NULL;
     int32_t status;
     Py_BEGIN_ALLOW_THREADS
@@ -117,9 +125,9 @@ static PyObject* call_mixed(PyObject* self, PyObject* const* a, Py_ssize_t n) {
     }
     PyObject* result = NULL;
     PyObject* scale = NULL;
-    if (to_address(a[0], s_value, &fn) && to_address(a[1], s_value, &ctx) && to_int_or_shape(a[5], a[4], 1, &max_pages) &&
-        to_address(a[2], s_data_ptr, &q) && to_address(a[3], s_data_ptr, &pages) && to_address(a[4], s_data_ptr, &tables) &&
-        (scale = PyNumber_Float(a[8])) && to_address(a[9], s_data_ptr, &out) && to_address(a[10], s_value, &stream)) {
+    if (to_handle(a[0], &fn) && to_handle(a[1], &ctx) && to_int_or_shape(a[5], a[4], 1, &max_pages) &&
+        to_address(a[2], &q) && to_address(a[3], &pages) && to_address(a[4], &tables) &&
+        (scale = PyNumber_Float(a[8])) && to_address(a[9], &out) && to_handle(a[10], &stream)) {
         const float s = (float)PyFloat_AS_DOUBLE(scale);
         int32_t status;
         Py_BEGIN_ALLOW_THREADS
@@ -146,6 +154,11 @@ PyMODINIT_FUNC PyInit_ppd_call(void) {
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_value = PyUnicode_InternFromString("value");
     s_shape = PyUnicode_InternFromString("shape");
-    if (!s_data_ptr || !s_value || !s_shape) return NULL;
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    if (!ctypes) return NULL;
+    t_void_p = PyObject_GetAttrString(ctypes, "c_void_p");
+    f_cast = PyObject_GetAttrString(ctypes, "cast");
+    Py_DECREF(ctypes);
+    if (!s_data_ptr || !s_value || !s_shape || !t_void_p || !f_cast) return NULL;
     return PyModule_Create(&kModule);
 }

@@ -352,3 +352,67 @@ def test_calls_marshal_their_arguments(monkeypatch):
         ppd.ppd_mixed_attention(11, t, t, table, L, L, None, t)
     with pytest.raises(AttributeError):
         ppd.ppd_kv_append(11, "k", t, t, slots)
+
+
+def test_handles_are_taken_in_every_form_that_ctypes_takes(monkeypatch):
+    """Contexts and streams reach the per-layer entry points in any form that the other entry points' ctypes parameters take
+    (torch.cuda.Stream passes itself by _as_parameter_), and what those refuse is refused."""
+    import ctypes
+    import torch
+    from paper_2603_13358_amd import binding
+
+    ppd.load_library()
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+    assert hasattr(torch.cuda.Stream, "_as_parameter_")
+
+    class Handle(ctypes.c_void_p):
+        pass
+
+    class Carrier:
+        def __init__(self, parameter):
+            self._as_parameter_ = parameter
+
+    class Valued:
+        value = 5
+
+    class Tensor:
+        def __init__(self, address):
+            self.address = address
+
+        def data_ptr(self):
+            return self.address
+
+    seen = []
+    attention = (vp, vp, vp, vp, i32, vp, vp, i32, ctypes.c_float, vp, vp)
+    kinds = {"mixed": attention, "mixed_static": attention, "append": (vp,) * 5 + (i64, vp), "land": (vp,) * 4 + (i64, i32, vp, i64, vp)}
+    kept = []
+    for name, argtypes in kinds.items():
+        def entry(*args):
+            seen.append((args[0], args[1], args[-1]))
+            return 0
+        kept.append(ctypes.CFUNCTYPE(i32, *argtypes)(entry))
+        monkeypatch.setattr(binding, "_fn_" + name, ctypes.cast(kept[-1], vp).value)
+    by_ctypes = ctypes.CFUNCTYPE(ctypes.c_uint64, vp)(lambda address: address or 0)
+    by_ctypes.argtypes = [vp]
+    one = np.ones(1, np.int32)
+    calls = (lambda c, t, s: ppd.ppd_mixed_attention(c, t, 1, 1, one, one, 1.0, 1, max_pages=1, stream=s),
+             lambda c, t, s: ppd.ppd_mixed_attention_static(c, t, 1, 1, one, one, 1.0, 1, max_pages=1, stream=s),
+             lambda c, t, s: ppd.ppd_kv_append(c, t, 1, 1, 1, T=1, stream=s), lambda c, t, s: ppd.ppd_kv_land(c, t, 1, 1, 1, 1, 1, T=1, stream=s))
+    target = ctypes.c_int64(3)
+    forms = [None, 0, 17, (1 << 63) + 5, True, vp(19), vp(), Handle(23), Carrier(vp(29)), Carrier(31), Carrier(Carrier(Handle(37))), Carrier(None),
+             ctypes.pointer(target), ctypes.byref(target), (ctypes.c_int32 * 2)(), Carrier(ctypes.byref(target))]
+    for form in forms:
+        want = by_ctypes(form) or None
+        for call in calls:
+            call(form, 41, form)
+            assert seen.pop() == (want, 41, want), form
+            call(43, Tensor(form), None)
+            assert seen.pop() == (43, want, None), form
+    for form in (2.5, np.int64(7), ctypes.c_int64(7), Valued(), object(), Carrier(2.5), [1]):
+        with pytest.raises(ctypes.ArgumentError):
+            by_ctypes(form)
+        for call in calls:
+            for args in ((form, 41, None), (43, 41, form), (43, Tensor(form), None)):
+                with pytest.raises(ctypes.ArgumentError):
+                    call(*args)
+    assert not seen
