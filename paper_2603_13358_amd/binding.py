@@ -3,12 +3,13 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sysconfig
 
 import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libppd.so")
-_CALL_PATH = os.path.join(_HERE, "ppd_call.so")
+_CALL_PATH = os.path.join(_HERE, "ppd_call" + sysconfig.get_config_var("EXT_SUFFIX"))  # built for this interpreter's ABI
 _lib = None
 _call = None       # the call module
 _fn_append = _fn_land = _fn_mixed = _fn_mixed_static = None  # addresses of the entry points it calls
@@ -60,7 +61,7 @@ def load_library():
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH) or not os.path.exists(_CALL_PATH):
-        raise ImportError("libppd.so or ppd_call.so is not built: run `python -m paper_2603_13358_amd.build` "
+        raise ImportError("libppd.so or the call module for this Python is not built: run `python -m paper_2603_13358_amd.build` "
                           "(or __graft_entry__.build()); there is no CPU path")
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64

@@ -1,4 +1,4 @@
-"""Builds libppd.so (hand-written HIP for gfx950, with hipcc) and the call module ppd_call.so (host C) in-tree.  `python -m paper_2603_13358_amd.build`."""
+"""Builds libppd.so (hand-written HIP for gfx950, with hipcc) and the call module ppd_call (host C, one file per Python ABI) in-tree.  `python -m paper_2603_13358_amd.build`."""
 import os
 import subprocess
 import sys
@@ -7,7 +7,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libppd.so")
-CALL = os.path.join(HERE, "ppd_call.so")
+CALL = os.path.join(HERE, "ppd_call" + sysconfig.get_config_var("EXT_SUFFIX"))  # of this interpreter
 CALL_SOURCE = os.path.join(CSRC, "ppd_call.c")
 SOURCES = ["ppd_api.hip", "ppd_kernels.hip", "ppd_plan.cpp", "ppd_route.cpp"]
 HEADERS = ["ppd_internal.h", os.path.join("..", "..", "include", "ppd.h")]

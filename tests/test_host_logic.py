@@ -416,3 +416,27 @@ def test_handles_are_taken_in_every_form_that_ctypes_takes(monkeypatch):
                 with pytest.raises(ctypes.ArgumentError):
                     call(*args)
     assert not seen
+
+
+def test_call_module_belongs_to_one_python_abi(monkeypatch):
+    """The call module is built and loaded under this interpreter's ABI tag: for another interpreter the build is stale and
+    the load says so, instead of running a module that was compiled for this one."""
+    import importlib.util
+    import os
+    import sysconfig
+    from paper_2603_13358_amd import binding, build
+
+    def fresh(module):
+        spec = importlib.util.spec_from_file_location(module.__name__ + "_of_another_python", module.__file__)
+        copy = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(copy)
+        return copy
+
+    ppd.load_library()
+    assert build.CALL == binding._CALL_PATH and build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    real = sysconfig.get_config_var
+    monkeypatch.setattr(sysconfig, "get_config_var", lambda name: ".another-abi.so" if name == "EXT_SUFFIX" else real(name))
+    other_build, other_binding = fresh(build), fresh(binding)
+    assert os.path.basename(other_build.CALL) == "ppd_call.another-abi.so" and other_build.is_stale()
+    with pytest.raises(ImportError, match="for this Python"):
+        other_binding.load_library()
