@@ -428,7 +428,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         const int64_t rounds = n_wave == 0 ? slots / (ppd::kWgPerCu * ctx->num_cus) : 0;
         kp.four_waves = ppd::runs_on_four_waves(D, ctx->fp8_pages, kp.mean_tile_keys, rounds);
         if (n_wave == 0 && slots <= wgs && !kp.four_waves) kp.merge_groups = d_groups;
-        kp.by_index = slots <= 2 * wgs && kp.mean_tile_keys * (ctx->fp8_pages ? 1 : 2) < 3072;  // (1536 keys of bf16 pages)
+        kp.by_index = plan.by_index;
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {

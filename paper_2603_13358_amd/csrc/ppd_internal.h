@@ -105,6 +105,7 @@ struct MergeUnit {
 
 struct Plan {
     int32_t queue_begin[kQueues + 1];  // items [queue_begin[q], queue_begin[q+1]) belong to queue q
+    bool by_index = false;           // decode-only launches: the second round of slots is handed out by index
     int32_t narrow_cus = 16;         // of the 32 compute units of an XCD, how many take narrow tiles first
     std::vector<ppd_work_item> items;
     std::vector<MergeGroup> groups;

@@ -193,6 +193,46 @@ static int64_t choose_narrow_chunk(const std::vector<int64_t>& lengths, int Hkv,
     return best_chunk;
 }
 
+// Whether a decode-only launch of more slots than workgroups hands its second round out by index (ppd_narrow_kernel) instead of
+// by claims.  Workgroup b gets slot b and slot 2 * wgs - 1 - b.  By index where that costs no more than any order must:
+//  * at most two rounds, of tiles below 1536 keys of bf16 pages or 3072 of FP8 pages (figures at the kernel);
+//  * the heaviest workgroup's two slots are at most 96 KiB of K/V above what no order can undercut -- the longest slot, the mean
+//    of the workgroups, or the two shortest slots of which two must share a workgroup -- where a slot's fixed cost counts as
+//    128 KiB.  Equal and evenly spread lengths pair off to almost nothing above it; a long tile among short ones gets another
+//    behind it, where claims would leave it alone (us of 64 sequences of 800 keys, one of them 2.4 and 4 times as long, claimed
+//    43.8 and 49.0, by index 46.0 and 58.3; of log-normal lengths around 800 keys 40.6 and 42.5, at D = 64 25.6 and 28.6);
+//  * in a second round of less than a quarter, tiles below 256 KiB: a few workgroups decide such a step, and claims give its
+//    second tiles to those that are done first (264, 288, 304 and 320 tiles by 256 workgroups, by index against claimed: 1500
+//    keys of bf16 pages -4.1, -2.6, -1.0, +0.7 %, 1000 keys -3.1, -1.2, +0.4, +1.9, 600 keys -1.3, -0.4, +1.2, +2.5, 300 keys +6
+//    at 288; 3000 keys of FP8 pages -2.2, -1.3, -1.3, -0.4, 1200 keys -0.1, +1.2, +1.6, +2.3; D = 64, 1200 keys of bf16 pages
+//    -1.8, +1.2, +1.1, +1.4, 1000 keys +0.8, +1.3, +2.7, +3.3).
+// Over 558 launches of 33-64 sequences, equal, spread and log-normal around 250-3000 keys, on both formats and head sizes: 4.5 %
+// less time than claims on average and nowhere more by a measurable amount (-1.2 % at worst, runs differ by 1); every second
+// round by index 4.3 % on average and up to 14 % more time at worst.
+bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
+    const int n_wg = plan.queue_begin[kWaveQueue], n_items = plan.queue_begin[kQueues];
+    const int64_t slots = n_wg + ((int64_t)n_items - n_wg + kNarrowKernelWaves - 1) / kNarrowKernelWaves;
+    if (slots <= wgs || slots > 2 * wgs) return false;
+    constexpr int64_t kFixed = 128 * 1024, kAbove = 96 * 1024, kShort = 256 * 1024;
+    const int64_t key_bytes = 2LL * head_dim * elem_bytes;
+    std::vector<int64_t> cost((size_t)slots, kFixed);
+    int64_t keys = 0;
+    for (int i = 0; i < n_items; ++i) {
+        const int64_t k = plan.items[i].kv_end - plan.items[i].kv_begin;
+        cost[i < n_wg ? i : n_wg + (i - n_wg) / kNarrowKernelWaves] += k * key_bytes;
+        keys += k;
+    }
+    if (keys / n_items * elem_bytes >= 3072) return false;
+    if (4 * slots < 5 * wgs && keys / n_items * key_bytes >= kShort) return false;
+    int64_t sum = 0, longest = 0, heaviest = 0;
+    for (int64_t b = 0; b < slots; ++b) {
+        sum += cost[b];
+        longest = std::max(longest, cost[b]);
+        if (b < wgs) heaviest = std::max(heaviest, cost[b] + (2 * wgs - 1 - b < slots ? cost[2 * wgs - 1 - b] : 0));
+    }
+    return heaviest <= std::max({longest, sum / wgs, cost[wgs - 1] + cost[wgs]}) + kAbove;
+}
+
 ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, int32_t B, const PlanOptions& o,
                       Plan* plan, const char** err) {
     static const char* kNull = "L / n is NULL";
@@ -430,6 +470,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     // a workgroup's eight waves take eight wave tiles at a time
     const int64_t wave_groups = (plan->queue_begin[kQueues] - plan->queue_begin[kWaveQueue] + kWaves - 1) / kWaves;
     st.grid = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slots, plan->queue_begin[kWaveQueue] + wave_groups));
+    plan->by_index = n_mfma == 0 && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }
 

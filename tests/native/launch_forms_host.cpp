@@ -1,0 +1,145 @@
+// Host-only checks of how a decode-only step is launched (built and run by tests/test_launch_forms.py): ppd_api.hip as it
+// is, compiled against the stand-in runtime of host_runtime/, whose launches are recorded instead of run.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <random>
+#include <vector>
+
+#include "../../paper_2603_13358_amd/csrc/ppd_api.hip"
+
+static ppd::KParams g_params;
+static int g_grid = 0, g_merges = 0;
+
+std::function<void()> sim_bind(const void* f, void** args) {
+    if (f != reinterpret_cast<const void*>(&ppd_upload_kernel)) std::abort();
+    auto host = *static_cast<const uint4**>(args[0]);
+    auto dev = *static_cast<uint4**>(args[1]);
+    auto granules = *static_cast<int64_t*>(args[2]);
+    auto counters = *static_cast<uint32_t**>(args[3]);
+    auto read = *static_cast<uint32_t**>(args[4]);
+    auto serial = *static_cast<uint32_t*>(args[5]);
+    return [=] { ppd_upload_kernel(host, dev, granules, counters, read, serial); };
+}
+
+namespace ppd {
+int prepare_mixed_kernels() { return 0; }
+int launch_mixed(const KParams&, int, int, void*, bool) { std::abort(); }
+int launch_narrow(const KParams& p, int, int grid, void*, bool) {
+    g_params = p;
+    g_grid = grid;
+    return 0;
+}
+int launch_mfma_only(const KParams&, int, int, void*) { std::abort(); }
+int launch_stream_only(const KParams&, int, int, void*) { std::abort(); }
+int launch_merge(const MergeParams&, void*) {
+    ++g_merges;
+    return 0;
+}
+int launch_kv_append(const uint16_t*, const uint16_t*, void*, const int64_t*, int64_t, int, int, int64_t, int, int64_t, uint32_t*,
+                     void*, bool, float, float) { return 0; }
+}  // namespace ppd
+
+#define CHECK(x)                                                      \
+    do {                                                              \
+        if (!(x)) {                                                   \
+            std::printf("%s:%d: not so: %s\n", __FILE__, __LINE__, #x); \
+            std::fflush(stdout);                                      \
+            std::_Exit(1);                                            \
+        }                                                             \
+    } while (0)
+
+struct Step {
+    bool by_index, four_waves, merges_itself, merge_launched;
+    int64_t items, groups;
+};
+
+// One decode step of sequences that see `keys` keys each, by 8 KV heads.
+static Step step(std::vector<int32_t> keys, int head_dim, bool fp8, int64_t chunk, int64_t grid, bool use_static = false) {
+    alignas(16) static char device[16];
+    const ppd_shape s = {32, 8, head_dim, 16, 1 << 20};
+    ppd_ctx* ctx = nullptr;
+    CHECK(ppd_create(&s, 0, &ctx) == PPD_OK);
+    if (fp8) CHECK(ppd_set_kv_format(ctx, PPD_KV_FP8_E4M3, 1.f, 1.f) == PPD_OK);
+    CHECK(ppd_set_option(ctx, "narrow_chunk", chunk) == PPD_OK && ppd_set_option(ctx, "grid", grid) == PPD_OK);
+    for (auto& k : keys) k -= 1;
+    const std::vector<int32_t> n(keys.size(), 1);
+    g_merges = 0;
+    auto fn = use_static ? ppd_mixed_attention_static : ppd_mixed_attention;
+    CHECK(fn(ctx, device, device, reinterpret_cast<const int32_t*>(device), 1 << 16, keys.data(), n.data(), (int32_t)keys.size(), 1.f, device, nullptr) == PPD_OK);
+    sim.null_stream.run();
+    ppd_plan_stats st;
+    CHECK(ppd_get_plan_stats(ctx, &st) == PPD_OK && st.n_mfma == 0);
+    ppd_destroy(ctx);
+    return Step{g_params.by_index != 0, g_params.four_waves != 0, g_params.merge_groups != nullptr, g_merges == 1, st.n_items, st.n_groups};
+}
+
+static std::vector<int32_t> lengths(int count, int32_t keys, int n_long = 0, int32_t longer = 0) {
+    std::vector<int32_t> v((size_t)count, keys);
+    for (int i = 0; i < n_long; ++i) v[i] = longer;
+    return v;
+}
+
+// Whatever the lengths and the grid, split ranges are merged exactly once: by a form that can, or by the merge launch.  Which
+// form runs does not depend on the grid.
+static void merged_once() {
+    std::mt19937 rng(1);
+    int four = 0, itself = 0, launched = 0;
+    for (int trial = 0; trial < 150; ++trial) {
+        const int D = rng() % 4 ? 128 : 64;
+        const bool fp8 = rng() % 4 == 0, use_static = rng() % 4 == 0;
+        const int64_t chunks[] = {0, 64, 1024, 4096, 8192};
+        const int64_t chunk = chunks[rng() % 5];
+        const int32_t longest = 200 << (rng() % 8);
+        std::vector<int32_t> keys((size_t)(1 + rng() % 70));
+        const int32_t low = rng() % 2 ? longest / 2 : 0;
+        for (auto& k : keys) k = 1 + low + (int32_t)(rng() % (longest - low));
+        if (use_static && (chunk == 64 || chunk == 0)) continue;  // (plans that do not fit the static array)
+        const Step a = step(keys, D, fp8, chunk, 0, use_static);
+        for (int64_t grid : {256, 512, 600, 4096, 65536}) {
+            const Step b = step(keys, D, fp8, chunk, grid, use_static);
+            if (chunk > 0) CHECK(b.four_waves == a.four_waves);  // (an automatic split size goes by the grid)
+            CHECK(!(b.four_waves && b.merges_itself));
+            CHECK((b.groups > 0) == (b.merges_itself || b.merge_launched) && !(b.merges_itself && b.merge_launched));
+            if (b.items <= 256) CHECK(!b.four_waves);
+            four += b.four_waves;
+            itself += b.merges_itself;
+            launched += b.merge_launched;
+        }
+    }
+    CHECK(four > 20 && itself > 20 && launched > 20);
+}
+
+// The second round of a decode-only launch (256 workgroups) is handed out by index where its pairs are balanced.
+static void second_round() {
+    const int64_t whole = 16384;  // no range is split
+    auto by_index = [&](const std::vector<int32_t>& keys, int D = 128, bool fp8 = false) { return step(keys, D, fp8, whole, 0).by_index; };
+    CHECK(!by_index(lengths(32, 800)) && !by_index(lengths(65, 800)));                     // one round, more than two
+    CHECK(by_index(lengths(64, 800)) && by_index(lengths(64, 1535)) && !by_index(lengths(64, 1536)));
+    CHECK(by_index(lengths(64, 3071), 128, true) && !by_index(lengths(64, 3072), 128, true));
+    CHECK(by_index(lengths(64, 1535), 64) && !by_index(lengths(64, 1536), 64));
+    CHECK(by_index(lengths(40, 1500)) && !by_index(lengths(39, 1500)) && by_index(lengths(39, 511)) && !by_index(lengths(39, 512)));
+    CHECK(by_index(lengths(33, 511)) && by_index(lengths(33, 1023), 64) && !by_index(lengths(33, 1024), 64));
+    CHECK(by_index(lengths(33, 1023), 128, true) && !by_index(lengths(33, 1024), 128, true));
+    for (int32_t keys : {500, 800, 1300})                                                  // another tile behind a long one
+        for (int n_long : {1, 8})
+            for (bool fp8 : {false, true})
+                for (int D : {64, 128}) {
+                    CHECK(!by_index(lengths(64, keys, n_long, 4 * keys), D, fp8));
+                    CHECK(by_index(lengths(64, keys, n_long, keys + 32), D, fp8));
+                }
+    CHECK(!by_index(lengths(52, 800, 14, 1600)));                                          // 16 long tiles of 112 would get one
+    CHECK(by_index(lengths(52, 800, 12, 1600)));                                           // none of 96 would
+    std::vector<int32_t> even(64);
+    for (int i = 0; i < 64; ++i) even[i] = 64 + i * 24;                                     // evenly spread: the pairs balance
+    CHECK(by_index(even));
+}
+
+int main(int argc, char** argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "merged_once") merged_once();
+    else if (what == "second_round") second_round();
+    else return 2;
+    std::printf("ok\n");
+    return 0;
+}
