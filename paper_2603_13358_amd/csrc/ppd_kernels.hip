@@ -1458,16 +1458,16 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
             const int mine = idx + __builtin_amdgcn_readfirstlane(tid >> 6);
             if (mine < P.queue_begin[kQueues]) {
                 const ppd_work_item it = P.items[mine];
-                if constexpr (FP8) narrow_item_wide<HD, 1, kFp8StreamSets, true, true>(P, it, smem);
-                else narrow_item<HD, 1, kMixedSets, kMixedSets, true>(P, it, smem);
+                if constexpr (FP8) narrow_item_wide<HD, 1, fp8_sets(HD), true, true>(P, it, smem);
+                else narrow_item<HD, 1, mixed_sets(HD), mixed_sets(HD), true>(P, it, smem);
             }
             if (own >= 0) return;
             continue;
         }
         const ppd_work_item it = P.items[idx];
         if (it.kind == 0) {
-            if constexpr (FP8) narrow_item_wide<HD, kWaves, kFp8StreamSets, false, true>(P, it, smem);
-            else narrow_item<HD, kWaves, kMixedSets, kMixedSets, false>(P, it, smem);
+            if constexpr (FP8) narrow_item_wide<HD, kWaves, fp8_sets(HD), false, true>(P, it, smem);
+            else narrow_item<HD, kWaves, mixed_sets(HD), mixed_sets(HD), false>(P, it, smem);
         } else {
             mfma_item<HD, false, FP8>(P, it, smem);
         }
@@ -1562,8 +1562,8 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // The list and its bounds (n_wg whole-workgroup tiles, `end` tiles in all) are arguments of their own, which arrive in scalar registers:
 // a workgroup's first read is its work item, where it used to be the arguments, then the bounds, then the item (6 decodes of
 // 1K-3K keys 20.0 -> 19.7 us a layer, 11 of 300-6500 33.4 -> 33.1).
-// NSETS: rotating register sets (one page each) of a streaming wave on bf16 pages, kLongSets where the tiles are long and
-// kShortSets where they are short.  NW: eight waves, or four of twice the registers where the tiles are long and there are many
+// NSETS: rotating register sets of a streaming wave of a whole-workgroup tile, of one page each on bf16 pages (kLongSets where
+// the tiles are long and kShortSets where they are short) and of a page pair on FP8 pages (one, or fp8_sets).  NW: eight waves, or four of twice the registers where the tiles are long and there are many
 // (runs_on_four_waves); launch_narrow has the figures of the former.
 // ---------------------------------------------------------------------------------------------------
 template <int HD, bool FP8, int NW, int NSETS>
@@ -1578,7 +1578,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
     while (slot < slots) {
         if (slot < n_wg) {
             const ppd_work_item it = items[slot];
-            if constexpr (FP8) narrow_item_wide<HD, NW, kFp8StreamSets, false, true>(P, it, smem);
+            if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true>(P, it, smem);
             else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves>(P, it, smem);
             if constexpr (NW == kWaves)  // the host gives the four-wave form no merge_groups
                 if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, &s_arrived);
@@ -1586,7 +1586,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
             const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
             if (mine < end) {
                 const ppd_work_item it = items[mine];
-                if constexpr (FP8) narrow_item_wide<HD, 1, kFp8StreamSets, true, true>(P, it, smem);
+                if constexpr (FP8) narrow_item_wide<HD, 1, fp8_sets(HD), true, true>(P, it, smem);
                 else narrow_item<HD, 1, NSETS, NSETS, true>(P, it, smem);
             }
         }
@@ -1939,8 +1939,9 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kLongSets>), NarrowCombine<NW>::bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kShortSets>), NarrowCombine<NW>::bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, false, NW, kShortSets>), NarrowCombine<NW>::bytes(64));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, true, NW, kShortSets>), NarrowCombine<NW>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, NW, kShortSets>), NarrowCombine<NW>::bytes(64));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, true, NW, fp8_sets(128)>), NarrowCombine<NW>::bytes(128));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, NW, fp8_sets(64)>), NarrowCombine<NW>::bytes(64));
+    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, NW, 1>), NarrowCombine<NW>::bytes(64));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<128>), ring_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<64>), ring_lds_bytes(64));
     return (int)e;
@@ -1970,8 +1971,11 @@ int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool f
     // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
     // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
     const bool long_tiles = p.mean_tile_keys >= 1536;
+    // FP8 pages at D = 64: eight waves by two pairs are 512 keys.  One and two sets, us: 1144 tiles of 80 keys 22.8 and 24.5, 1160
+    // of 290 27.6 and 29.3, 624 of 420 18.3 and 19.2; 376 of 1475 21.8 and 21.4, 346 of 2140 25.0 and 23.5, 744 of 5050 89.0 and
+    // 85.0, 136 of 1900 21.4 and 19.5.
     if (head_dim == 128 && fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, fp8_sets(128)>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
     else if (head_dim == 128 && p.four_waves)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), dim3(grid), dim3(64 * kStreamingWaves),
                            NarrowCombine<kStreamingWaves>::bytes(128), st, p.items, p.n_wg, p.n_items, p);
@@ -1979,8 +1983,10 @@ int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool f
         hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kLongSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
     else if (head_dim == 128)
         hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
+    else if (fp8_pages && p.mean_tile_keys < 512)
+        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, 1>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
     else if (fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
+        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, fp8_sets(64)>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
     else
         hipLaunchKernelGGL((ppd_narrow_kernel<64, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
     return (int)hipGetLastError();
