@@ -39,7 +39,7 @@ constexpr int kStreamThreads = 64 * kStreamWaves;
 constexpr int kStreamKSets = PPD_STREAM_KSETS;
 constexpr int kStreamVSets = PPD_STREAM_VSETS;
 // Rotating register sets of a wave that streams bf16 pages, one page each: in the mixed kernel, and in the decode-only kernel
-// for long and for short tiles (launch_narrow has the figures).  In the mixed kernel at D = 128 four sets left its row-block loop
+// for long and for short tiles (narrow_form has the figures).  In the mixed kernel at D = 128 four sets left its row-block loop
 // no register to spare and streamed less: 128 long decodes beside 4 turns 2804 -> 2755 us with three.  At D = 64 they fit and
 // are ahead wherever the decodes take part in the time (49 decodes of 15000 keys beside 6 turns 143.9 us with three, 135.8 with
 // four, 88 of 3600 beside 2 64.3 and 58.3; 100 drawn steps 1.9 % less on average, +1.4 % at worst).
@@ -58,7 +58,7 @@ inline bool runs_on_four_waves(int head_dim, bool fp8_pages, int64_t mean_tile_k
 // The same on FP8 pages, one page pair each.  One at D = 128: a wave asks for a pair and works it, and the other seven keep the
 // unit's loads going.  A second set is slower at every length (160 drawn decode steps 7 % on average; one decode of 4000 keys
 // 20.5 -> 19.1 us a layer without it).  Two at D = 64, where a pair is half the bytes, but for whole-workgroup tiles that are
-// too short to fill them (launch_narrow).
+// too short to fill them (narrow_form).
 constexpr int fp8_sets(int head_dim) { return head_dim == 64 ? 2 : 1; }
 // Waves per workgroup of ppd_narrow_kernel, but for rounds of long tiles (kStreamingWaves).  Two workgroups of four waves per
 // unit (two tiles in flight there) measured the same on short tiles and 10 % slower on cfg2.

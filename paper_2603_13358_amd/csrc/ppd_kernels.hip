@@ -768,9 +768,13 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
 // K and NV <= NK for V rotate, so that K of NK - 1 and V of NV - 1 pages per wave are in flight while one page is
 // computed), then the waves' (o, m, l) are combined through LDS, CB columns per pass.
 // ---------------------------------------------------------------------------------------------------
-// A narrow tile's partial may be read by another workgroup of the same launch (merge_last): it goes past the caches of this
-// XCD, which the other XCDs do not see.
-__device__ __forceinline__ void store_partial(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Where a launch merges split ranges itself (MERGED), a narrow tile's partial is read by another workgroup of the launch
+// (merge_last): it goes past the caches of this XCD, which the other XCDs do not see.
+template <bool MERGED>
+__device__ __forceinline__ void store_partial(float* p, float v) {
+    if constexpr (MERGED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
 __device__ __forceinline__ f32x2 load_partial2(const float* p) {
     return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
@@ -792,7 +796,7 @@ struct NarrowCombine {
 // 1.65655e-3, of which the rounding of the result to bf16 alone is 1.65654e-3 (1.65654e-3 with the nearest number first).
 // Sums of their own for the second numbers keep infinities as well and are 0.5 % slower (decode steps of 64 sequences
 // of 1K-8K keys 810.7 -> 814.9 us over four calls with their appends, and 813.4 -> 813.6 this way).
-template <int HD, int NW, int NK, int NV, bool SOLO = false, bool SPLIT_P = false>
+template <int HD, int NW, int NK, int NV, bool SOLO = false, bool SPLIT_P = false, bool MERGED = false>
 __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
     constexpr int EB = 2;  // bytes per pool element
@@ -1042,10 +1046,10 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
                 if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
             } else {
                 float* pp = P.partials + it.part_off;
-                store_partial(pp + (int64_t)col * HD + d, o);
+                store_partial<MERGED>(pp + (int64_t)col * HD + d, o);
                 if (d == 0) {
-                    store_partial(pp + (int64_t)ncols * HD + col * 2, mm);
-                    store_partial(pp + (int64_t)ncols * HD + col * 2 + 1, l);
+                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2, mm);
+                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2 + 1, l);
                 }
             }
         }
@@ -1065,7 +1069,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
 //   the octet the lane's V granules hold.
 // NS register sets of one page pair each rotate: NS - 1 pairs are in flight per wave besides the one being computed.
 // ---------------------------------------------------------------------------------------------------
-template <int HD, int NW, int NS, bool SOLO, bool FP8>
+template <int HD, int NW, int NS, bool SOLO, bool FP8, bool MERGED = false>
 __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
     constexpr int EB = FP8 ? 1 : 2;                       // bytes per pool element
@@ -1312,10 +1316,10 @@ __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_wor
                 if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
             } else {
                 float* pp = P.partials + it.part_off;
-                store_partial(pp + (int64_t)col * HD + d, o);
+                store_partial<MERGED>(pp + (int64_t)col * HD + d, o);
                 if (d == 0) {
-                    store_partial(pp + (int64_t)ncols * HD + col * 2, mm);
-                    store_partial(pp + (int64_t)ncols * HD + col * 2 + 1, l);
+                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2, mm);
+                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2 + 1, l);
                 }
             }
         }
@@ -1564,13 +1568,25 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // 1K-3K keys 20.0 -> 19.7 us a layer, 11 of 300-6500 33.4 -> 33.1).
 // NSETS: rotating register sets of a streaming wave of a whole-workgroup tile, of one page each on bf16 pages (kLongSets where
 // the tiles are long and kShortSets where they are short) and of a page pair on FP8 pages (one, or fp8_sets).  NW: eight waves, or four of twice the registers where the tiles are long and there are many
-// (runs_on_four_waves); launch_narrow has the figures of the former.
+// (runs_on_four_waves); narrow_form has the figures of the former.  MERGES: a launch with a workgroup for every tile, none of
+// them on a single wave, that merges split ranges itself.  A form of its own: beside the loop over slots the merge costs every
+// tile of the other launches registers and spilled scalars, and the loop the merging ones (drawn decode steps, 150 on each format,
+// 5 % less time on FP8 pages and 1 % on bf16 pages; of up to 12 long sequences, 120 each, 6 % and 2 %).
 // ---------------------------------------------------------------------------------------------------
-template <int HD, bool FP8, int NW, int NSETS>
+template <int HD, bool FP8, int NW, int NSETS, bool MERGES = false>
 __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_work_item* items, int n_wg, int end, const KParams P) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // the combine buffer
-    __shared__ int s_next_slot, s_arrived;
-    volatile int* s_next = &s_next_slot;
+    __shared__ int s_shared;
+    volatile int* s_next = &s_shared;
+    if constexpr (MERGES) {
+        const int slot = blockIdx.x;
+        if (slot >= n_wg) return;
+        const ppd_work_item it = items[slot];
+        if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, true>(P, it, smem);
+        else narrow_item<HD, NW, NSETS, NSETS, false, false, true>(P, it, smem);
+        if (it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, s_next);
+        return;
+    }
     const int tid = threadIdx.x;
     const int slots = n_wg + (end - n_wg + NW - 1) / NW;
     const bool claims = slots > (int)gridDim.x && !P.by_index;  // the same for every workgroup of the launch
@@ -1580,10 +1596,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
             const ppd_work_item it = items[slot];
             if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true>(P, it, smem);
             else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves>(P, it, smem);
-            if constexpr (NW == kWaves)  // the host gives the four-wave form no merge_groups
-                if (P.merge_groups && it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, &s_arrived);
         } else if constexpr (NW == kWaves) {
-            const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
+            const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
             if (mine < end) {
                 const ppd_work_item it = items[mine];
                 if constexpr (FP8) narrow_item_wide<HD, 1, fp8_sets(HD), true, true>(P, it, smem);
@@ -1923,6 +1937,38 @@ static size_t mixed_lds_bytes(int head_dim) {
     return rings > combine ? rings : combine;
 }
 
+// The forms of the decode-only kernel.
+struct NarrowForm {
+    void (*kernel)(const ppd_work_item*, int, int, const KParams);
+    int waves;
+    size_t lds;
+};
+template <int HD, bool FP8, int NSETS>
+static NarrowForm narrow_form_of(bool merges) {
+    constexpr int NW = kNarrowKernelWaves;
+    return {merges ? &ppd_narrow_kernel<HD, FP8, NW, NSETS, true> : &ppd_narrow_kernel<HD, FP8, NW, NSETS, false>, NW, NarrowCombine<NW>::bytes(HD)};
+}
+static NarrowForm narrow_form(int head_dim, bool fp8_pages, bool four_waves, int64_t mean_tile_keys, bool merges) {
+    // Register sets on bf16 pages.  Two make a loop of half the instructions, which short tiles never get to stream from a warm
+    // instruction cache; long tiles want K and V of two pages in flight.  Two and three sets, us a layer with its append: 64
+    // decodes of 200-400 keys 22.8 and 24.0, of 400-800 33.2 and 34.1, of 800-1600 (8 KV heads, tiles of 1200 on average) 54.7
+    // and 55.2; 64 of 1600-3200 99.9 and 98.8, of 6400-9000 306 and 303; 8 of 6400-9000 (tiles of 2000) 59.3 and 58.3.  The four
+    // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
+    // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
+    const bool long_tiles = mean_tile_keys >= 1536;
+    // FP8 pages at D = 64: eight waves by two pairs are 512 keys.  One and two sets, us: 1144 tiles of 80 keys 22.8 and 24.5, 1160
+    // of 290 27.6 and 29.3, 624 of 420 18.3 and 19.2; 376 of 1475 21.8 and 21.4, 346 of 2140 25.0 and 23.5, 744 of 5050 89.0 and
+    // 85.0, 136 of 1900 21.4 and 19.5.
+    if (four_waves)
+        return {&ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>, kStreamingWaves, NarrowCombine<kStreamingWaves>::bytes(128)};
+    if (head_dim == 128 && fp8_pages) return narrow_form_of<128, true, fp8_sets(128)>(merges);
+    if (head_dim == 128 && long_tiles) return narrow_form_of<128, false, kLongSets>(merges);
+    if (head_dim == 128) return narrow_form_of<128, false, kShortSets>(merges);
+    if (fp8_pages && mean_tile_keys < 512) return narrow_form_of<64, true, 1>(merges);
+    if (fp8_pages) return narrow_form_of<64, true, fp8_sets(64)>(merges);
+    return narrow_form_of<64, false, kShortSets>(merges);
+}
+
 // More than 64 KiB of dynamic LDS has to be allowed per kernel, on the device that is current (ppd_create calls
 // this once per context, with the context's device current).
 int prepare_mixed_kernels() {
@@ -1934,14 +1980,10 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, false>), mixed_lds_bytes(64));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<128, true>), mixed_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, true>), mixed_lds_bytes(64));
-    constexpr int NW = kNarrowKernelWaves;
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), NarrowCombine<kStreamingWaves>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kLongSets>), NarrowCombine<NW>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, false, NW, kShortSets>), NarrowCombine<NW>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, false, NW, kShortSets>), NarrowCombine<NW>::bytes(64));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<128, true, NW, fp8_sets(128)>), NarrowCombine<NW>::bytes(128));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, NW, fp8_sets(64)>), NarrowCombine<NW>::bytes(64));
-    allow(reinterpret_cast<const void*>(&ppd_narrow_kernel<64, true, NW, 1>), NarrowCombine<NW>::bytes(64));
+    auto allow_narrow = [&](const NarrowForm& f) { allow(reinterpret_cast<const void*>(f.kernel), f.lds); };
+    allow_narrow(narrow_form(128, false, true, 0, false));
+    for (int form = 0; form < 16; ++form)  // head size, page format, short and long tiles, merged in the launch or not
+        allow_narrow(narrow_form(form & 1 ? 128 : 64, (form & 2) != 0, false, form & 4 ? 1 << 20 : 0, (form & 8) != 0));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<128>), ring_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<64>), ring_lds_bytes(64));
     return (int)e;
@@ -1961,34 +2003,8 @@ int launch_mixed(const KParams& p, int head_dim, int grid, void* stream, bool fp
 }
 
 int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool fp8_pages) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    constexpr int NW = kNarrowKernelWaves;
-    const size_t lds128 = NarrowCombine<NW>::bytes(128), lds64 = NarrowCombine<NW>::bytes(64);
-    // Register sets on bf16 pages.  Two make a loop of half the instructions, which short tiles never get to stream from a warm
-    // instruction cache; long tiles want K and V of two pages in flight.  Two and three sets, us a layer with its append: 64
-    // decodes of 200-400 keys 22.8 and 24.0, of 400-800 33.2 and 34.1, of 800-1600 (8 KV heads, tiles of 1200 on average) 54.7
-    // and 55.2; 64 of 1600-3200 99.9 and 98.8, of 6400-9000 306 and 303; 8 of 6400-9000 (tiles of 2000) 59.3 and 58.3.  The four
-    // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
-    // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
-    const bool long_tiles = p.mean_tile_keys >= 1536;
-    // FP8 pages at D = 64: eight waves by two pairs are 512 keys.  One and two sets, us: 1144 tiles of 80 keys 22.8 and 24.5, 1160
-    // of 290 27.6 and 29.3, 624 of 420 18.3 and 19.2; 376 of 1475 21.8 and 21.4, 346 of 2140 25.0 and 23.5, 744 of 5050 89.0 and
-    // 85.0, 136 of 1900 21.4 and 19.5.
-    if (head_dim == 128 && fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, true, NW, fp8_sets(128)>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
-    else if (head_dim == 128 && p.four_waves)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>), dim3(grid), dim3(64 * kStreamingWaves),
-                           NarrowCombine<kStreamingWaves>::bytes(128), st, p.items, p.n_wg, p.n_items, p);
-    else if (head_dim == 128 && long_tiles)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kLongSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
-    else if (head_dim == 128)
-        hipLaunchKernelGGL((ppd_narrow_kernel<128, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds128, st, p.items, p.n_wg, p.n_items, p);
-    else if (fp8_pages && p.mean_tile_keys < 512)
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, 1>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
-    else if (fp8_pages)
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, true, NW, fp8_sets(64)>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
-    else
-        hipLaunchKernelGGL((ppd_narrow_kernel<64, false, NW, kShortSets>), dim3(grid), dim3(64 * NW), lds64, st, p.items, p.n_wg, p.n_items, p);
+    const NarrowForm f = narrow_form(head_dim, fp8_pages, p.four_waves != 0, p.mean_tile_keys, p.merge_groups != nullptr);
+    hipLaunchKernelGGL(f.kernel, dim3(grid), dim3(64 * f.waves), f.lds, static_cast<hipStream_t>(stream), p.items, p.n_wg, p.n_items, p);
     return (int)hipGetLastError();
 }
 
