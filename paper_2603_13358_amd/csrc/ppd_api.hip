@@ -380,6 +380,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.mean_tile_keys = plan.stats.kv_bytes_tiles / (2LL * ctx->shape.head_dim * (ctx->fp8_pages ? 1 : 2)) / plan.stats.n_items;
     kp.queue_begin = reinterpret_cast<const int32_t*>(static_cast<const char*>(d_plan) + total - bounds_bytes);
     kp.n_wg = plan.queue_begin[ppd::kWaveQueue];
+    kp.pace_keys = kp.mean_tile_keys;
     kp.four_waves = 0;
     kp.by_index = 0;
     kp.pref_mode = ctx->opts.pref_mode;
@@ -429,6 +430,8 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         kp.four_waves = ppd::runs_on_four_waves(D, ctx->fp8_pages, kp.mean_tile_keys, rounds);
         if (n_wave == 0 && slots <= wgs && !kp.four_waves) kp.merge_groups = d_groups;
         kp.by_index = plan.by_index;
+        const ppd_work_item& longest = plan.items[plan.queue_begin[ppd::kNarrowQueue]];
+        kp.pace_keys = std::max<int64_t>(kp.mean_tile_keys, (longest.kv_end - longest.kv_begin) * wgs / std::max(wgs, slots));
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {

@@ -145,6 +145,7 @@ struct KParams {
     int64_t num_pages;
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average
+    int64_t pace_keys;       // ppd_narrow_kernel: the same, or the longest tile's keys over the launch's rounds where that is more
     int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (runs_on_four_waves), which leaves split ranges to ppd_merge_kernel
     int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed

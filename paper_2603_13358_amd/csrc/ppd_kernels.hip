@@ -1567,8 +1567,9 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // a workgroup's first read is its work item, where it used to be the arguments, then the bounds, then the item (6 decodes of
 // 1K-3K keys 20.0 -> 19.7 us a layer, 11 of 300-6500 33.4 -> 33.1).
 // NSETS: rotating register sets of a streaming wave of a whole-workgroup tile, of one page each on bf16 pages (kLongSets where
-// the tiles are long and kShortSets where they are short) and of a page pair on FP8 pages (one, or fp8_sets).  NW: eight waves, or four of twice the registers where the tiles are long and there are many
-// (runs_on_four_waves); narrow_form has the figures of the former.  MERGES: a launch with a workgroup for every tile, none of
+// the tiles are long and kShortSets where they are short) and of a page pair on FP8 pages (one, or fp8_sets).  NW: eight
+// waves, or four of twice the registers where the tiles are long and there are many (runs_on_four_waves); narrow_form has the
+// figures of the former.  MERGES: a launch with a workgroup for every tile, none of
 // them on a single wave, that merges split ranges itself.  A form of its own: beside the loop over slots the merge costs every
 // tile of the other launches registers and spilled scalars, and the loop the merging ones (drawn decode steps, 150 on each format,
 // 5 % less time on FP8 pages and 1 % on bf16 pages; of up to 12 long sequences, 120 each, 6 % and 2 %).
@@ -1948,7 +1949,7 @@ static NarrowForm narrow_form_of(bool merges) {
     constexpr int NW = kNarrowKernelWaves;
     return {merges ? &ppd_narrow_kernel<HD, FP8, NW, NSETS, true> : &ppd_narrow_kernel<HD, FP8, NW, NSETS, false>, NW, NarrowCombine<NW>::bytes(HD)};
 }
-static NarrowForm narrow_form(int head_dim, bool fp8_pages, bool four_waves, int64_t mean_tile_keys, bool merges) {
+static NarrowForm narrow_form(int head_dim, bool fp8_pages, bool four_waves, int64_t mean_tile_keys, int64_t pace_keys, bool merges) {
     // Register sets on bf16 pages.  Two make a loop of half the instructions, which short tiles never get to stream from a warm
     // instruction cache; long tiles want K and V of two pages in flight.  Two and three sets, us a layer with its append: 64
     // decodes of 200-400 keys 22.8 and 24.0, of 400-800 33.2 and 34.1, of 800-1600 (8 KV heads, tiles of 1200 on average) 54.7
@@ -1956,15 +1957,17 @@ static NarrowForm narrow_form(int head_dim, bool fp8_pages, bool four_waves, int
     // sets that all tiles had were behind both at every length but 200-400 (200-400 23.6, 400-800 34.0, 6400-9000 308).  At
     // D = 64 a page is half the bytes and two sets are ahead at every length (32 of 6400-9000 keys 37.1 and 42.2).
     const bool long_tiles = mean_tile_keys >= 1536;
-    // FP8 pages at D = 64: eight waves by two pairs are 512 keys.  One and two sets, us: 1144 tiles of 80 keys 22.8 and 24.5, 1160
-    // of 290 27.6 and 29.3, 624 of 420 18.3 and 19.2; 376 of 1475 21.8 and 21.4, 346 of 2140 25.0 and 23.5, 744 of 5050 89.0 and
-    // 85.0, 136 of 1900 21.4 and 19.5.
+    // FP8 pages at D = 64: eight waves by two pairs are 512 keys.  Shorter tiles do not fill two sets, and what counts is the tiles
+    // that make the time: all of them in many rounds, the longest in one.  Two sets against one, 300 drawn decode steps: one round
+    // with a longest tile below 200 keys -8 %, of 200-500 -3, 500-700 +1, 700-1500 +6, more +16; several rounds of tiles of
+    // up to 200 keys on average -9, 200-500 -2, 500-700 +3, 700-1500 +9, more +16; split and merged in the launch, at 512 and 768
+    // keys -3, 1024 +1, 1536 and more +3.
     if (four_waves)
         return {&ppd_narrow_kernel<128, false, kStreamingWaves, kStreamingSets>, kStreamingWaves, NarrowCombine<kStreamingWaves>::bytes(128)};
     if (head_dim == 128 && fp8_pages) return narrow_form_of<128, true, fp8_sets(128)>(merges);
     if (head_dim == 128 && long_tiles) return narrow_form_of<128, false, kLongSets>(merges);
     if (head_dim == 128) return narrow_form_of<128, false, kShortSets>(merges);
-    if (fp8_pages && mean_tile_keys < 512) return narrow_form_of<64, true, 1>(merges);
+    if (fp8_pages && pace_keys < (merges ? 1024 : 512)) return narrow_form_of<64, true, 1>(merges);
     if (fp8_pages) return narrow_form_of<64, true, fp8_sets(64)>(merges);
     return narrow_form_of<64, false, kShortSets>(merges);
 }
@@ -1981,9 +1984,9 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<128, true>), mixed_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, true>), mixed_lds_bytes(64));
     auto allow_narrow = [&](const NarrowForm& f) { allow(reinterpret_cast<const void*>(f.kernel), f.lds); };
-    allow_narrow(narrow_form(128, false, true, 0, false));
+    allow_narrow(narrow_form(128, false, true, 0, 0, false));
     for (int form = 0; form < 16; ++form)  // head size, page format, short and long tiles, merged in the launch or not
-        allow_narrow(narrow_form(form & 1 ? 128 : 64, (form & 2) != 0, false, form & 4 ? 1 << 20 : 0, (form & 8) != 0));
+        allow_narrow(narrow_form(form & 1 ? 128 : 64, (form & 2) != 0, false, form & 4 ? 1 << 20 : 0, form & 4 ? 1 << 20 : 0, (form & 8) != 0));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<128>), ring_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<64>), ring_lds_bytes(64));
     return (int)e;
@@ -2003,7 +2006,7 @@ int launch_mixed(const KParams& p, int head_dim, int grid, void* stream, bool fp
 }
 
 int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool fp8_pages) {
-    const NarrowForm f = narrow_form(head_dim, fp8_pages, p.four_waves != 0, p.mean_tile_keys, p.merge_groups != nullptr);
+    const NarrowForm f = narrow_form(head_dim, fp8_pages, p.four_waves != 0, p.mean_tile_keys, p.pace_keys, p.merge_groups != nullptr);
     hipLaunchKernelGGL(f.kernel, dim3(grid), dim3(64 * f.waves), f.lds, static_cast<hipStream_t>(stream), p.items, p.n_wg, p.n_items, p);
     return (int)hipGetLastError();
 }

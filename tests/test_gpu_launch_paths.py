@@ -462,11 +462,12 @@ def test_infinite_values_stay_infinite_on_four_waves(options):
             assert np.array_equal(got[:, :, rest], plain[:, :, rest])
 
 
-@pytest.mark.parametrize("L,options", [([510] * 5, {}), ([511] * 5, {}), ([5000, 3, 47, 801], {}), ([9000, 31, 2500], {"narrow_chunk": 1024}),
+@pytest.mark.parametrize("L,options", [([510] * 5, {}), ([511] * 5, {}), ([5000, 3, 47, 801], {}), ([200] * 40 + [3000], {}),
+                                       ([9000, 31, 2500], {"narrow_chunk": 960}), ([9000, 31, 2500], {"narrow_chunk": 1024}),
                                        ([300] * 17 + [12], {"wave_tiles": 1}), ([380] * 9 + [4000] * 3, {"wave_tiles": 1})])
 def test_decode_only_kernel_on_fp8_pages_of_head_size_64(L, options):
-    """Tiles of 511, of 512 and of mixed lengths on average (the decode-only kernel takes other register sets from 512 on), split
-    and on single waves: the oracle's result, and bit for bit the mixed kernel's."""
+    """Tiles of 511, of 512 and of mixed lengths (the decode-only kernel takes other register sets from 512 on, 1024 where it
+    merges), split and on single waves: the oracle's result, and bit for bit the mixed kernel's."""
     b = si.make_batch("sets8", L=L, n=np.ones(len(L), np.int64), Hq=32, Hkv=8, D=64, seed=len(L), slack_pages=2)
     options = dict({"narrow_chunk": 8192}, **options)
     pool, out, stats = gpu_step_fp8(b, 0.0173, 0.0421, options=options)
