@@ -424,10 +424,8 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         // pages 18.2 -> 16.6, 11 decodes of 300-6500 keys 34.4 -> 33.4).  With more rounds every tile but the last ones would
         // stop for its count while its unit could stream (66 decodes of 1K-32K, FP8 pages, 1576 tiles: +3 us of 440).  Tiles that
         // run on single waves leave their partials to the merge launch as well.
-        // Nor do the four-wave tiles merge; they are chosen by the device's workgroups and not by the launch's, because they round
-        // differently and the grid option stays scheduling only.
-        const int64_t rounds = n_wave == 0 ? slots / (ppd::kWgPerCu * ctx->num_cus) : 0;
-        kp.four_waves = ppd::runs_on_four_waves(D, ctx->fp8_pages, kp.mean_tile_keys, rounds);
+        // Nor do the four-wave tiles merge: their form has no merge.
+        kp.four_waves = plan.four_waves;
         if (n_wave == 0 && slots <= wgs && !kp.four_waves) kp.merge_groups = d_groups;
         kp.by_index = plan.by_index;
         const ppd_work_item& longest = plan.items[plan.queue_begin[ppd::kNarrowQueue]];

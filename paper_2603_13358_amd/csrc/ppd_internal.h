@@ -47,14 +47,6 @@ constexpr int mixed_sets(int head_dim) { return head_dim == 64 ? 4 : 3; }
 constexpr int kLongSets = 3, kShortSets = 2;
 // Waves and register sets of the decode-only kernel's tiles where they are long and many: one wave per SIMD.
 constexpr int kStreamingWaves = 4, kStreamingSets = 4;
-// Where every unit streams long tiles one after the other, HBM is the bound, and it delivers more to half the waves, each with
-// one more page in flight: us of 128 sequences of 7000-8000 keys by 8 heads 597 -> 574 (6.6 -> 6.9 TB/s), 64 of 3200-6400
-// 192.8 -> 187.0, 128 of 1000-8000 345 -> 339, 256 of them 697 -> 687.  A unit alone streams less that way (42 against 52
-// GB/s), so launches of less than two rounds stay on eight waves (16 sequences of 3200-6400 keys 70 -> 83), and so do tiles
-// below 3072 keys, where the gain ends: 256 of 1600-2000 297 -> 298, 32 of 3200-6400 (512 tiles of 2400) 103.9 -> 107.2.
-inline bool runs_on_four_waves(int head_dim, bool fp8_pages, int64_t mean_tile_keys, int64_t rounds) {
-    return head_dim == 128 && !fp8_pages && mean_tile_keys >= 3072 && rounds >= 2;
-}
 // The same on FP8 pages, one page pair each.  One at D = 128: a wave asks for a pair and works it, and the other seven keep the
 // unit's loads going.  A second set is slower at every length (160 drawn decode steps 7 % on average; one decode of 4000 keys
 // 20.5 -> 19.1 us a layer without it).  Two at D = 64, where a pair is half the bytes, but for whole-workgroup tiles that are
@@ -106,6 +98,7 @@ struct MergeUnit {
 
 struct Plan {
     int32_t queue_begin[kQueues + 1];  // items [queue_begin[q], queue_begin[q+1]) belong to queue q
+    bool four_waves = false;         // decode-only launches: the form of four waves per workgroup
     bool by_index = false;           // decode-only launches: the second round of slots is handed out by index
     int32_t narrow_cus = 16;         // of the 32 compute units of an XCD, how many take narrow tiles first
     std::vector<ppd_work_item> items;
@@ -146,7 +139,7 @@ struct KParams {
     int64_t page_stride;  // elements per page = 2 * Hkv * 16 * D
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average
     int64_t pace_keys;       // ppd_narrow_kernel: the same, or the longest tile's keys over the launch's rounds where that is more
-    int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (runs_on_four_waves), which leaves split ranges to ppd_merge_kernel
+    int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (long_tiles_on_four_waves), which leaves split ranges to ppd_merge_kernel
     int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed
     int32_t n_items;

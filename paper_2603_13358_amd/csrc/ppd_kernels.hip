@@ -1568,7 +1568,7 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // 1K-3K keys 20.0 -> 19.7 us a layer, 11 of 300-6500 33.4 -> 33.1).
 // NSETS: rotating register sets of a streaming wave of a whole-workgroup tile, of one page each on bf16 pages (kLongSets where
 // the tiles are long and kShortSets where they are short) and of a page pair on FP8 pages (one, or fp8_sets).  NW: eight
-// waves, or four of twice the registers where the tiles are long and there are many (runs_on_four_waves); narrow_form has the
+// waves, or four of twice the registers where the tiles are long and there are many (long_tiles_on_four_waves); narrow_form has the
 // figures of the former.  MERGES: a launch with a workgroup for every tile, none of
 // them on a single wave, that merges split ranges itself.  A form of its own: beside the loop over slots the merge costs every
 // tile of the other launches registers and spilled scalars, and the loop the merging ones (drawn decode steps, 150 on each format,

@@ -193,6 +193,28 @@ static int64_t choose_narrow_chunk(const std::vector<int64_t>& lengths, int Hkv,
     return best_chunk;
 }
 
+// Whether the tiles of a decode-only launch run on four waves (kStreamingWaves; D = 128, bf16 pages, a multiple of 8 KV heads)
+// instead of eight.  Where every unit streams long tiles one after the other, HBM is the bound, and it delivers more to half the waves, each with one more
+// page in flight: us of 128 sequences of 7000-8000 keys by 8 heads 597 -> 574 (6.6 -> 6.9 TB/s), 64 of 3200-6400 192.8 -> 187.0, 128
+// of 1000-8000 345 -> 339, 256 of them 697 -> 687.  A unit alone streams less that way (42 against 52 GB/s): launches of less than
+// two rounds stay on eight waves (16 sequences of 3200-6400 keys 70 -> 83), and so do tiles below 3072 keys, where the gain ends
+// (256 of 1600-2000 297 -> 298, 32 of 3200-6400, 512 tiles of 2400, 103.9 -> 107.2).  For the same reason the last round counts:
+// while fewer than 70 % of the units have a tile they lose what the full ones won, unless what is left by then is short.  Equal
+// tiles, four waves against eight: 2.2 rounds 225 against 206 us, 3.2 277 and 261, 5.1 439 and 423, 2.97 330 and 338.  And the KV
+// heads: where they are not a multiple of the 8 XCDs the full rounds win nothing (220 drawn launches under the rule: 8 heads 1.8 % on
+// average, -1.5 at worst, 16 heads 1.7 %, 12 heads 0.1, 4 heads -0.3, 1, 2 and 6 heads -0.1 to -0.5).
+// By the device's workgroups, not by a grid override: the two forms round differently, and that option stays scheduling only.
+static bool long_tiles_on_four_waves(const Plan& plan, int64_t wgs, int head_dim, int num_kv_heads, int elem_bytes) {
+    const int n = plan.queue_begin[kQueues];
+    if (head_dim != 128 || elem_bytes != 2 || num_kv_heads % kXcds != 0 || n < 2 * wgs || plan.queue_begin[kWaveQueue] != n) return false;
+    auto keys = [&](int64_t i) { return (int64_t)(plan.items[i].kv_end - plan.items[i].kv_begin); };
+    int64_t sum = 0;
+    for (int i = 0; i < n; ++i) sum += keys(i);
+    if (sum / n < 3072) return false;
+    const int64_t last = n % wgs;  // tiles of the last round, the shortest ones
+    return last == 0 || 10 * last >= 7 * wgs || 10 * keys(n - last) <= sum / wgs;
+}
+
 // Whether a decode-only launch of more slots than workgroups hands its second round out by index (ppd_narrow_kernel) instead of
 // by claims.  Workgroup b gets slot b and slot 2 * wgs - 1 - b.  By index where that costs no more than any order must:
 //  * at most two rounds, of tiles below 1536 keys of bf16 pages or 3072 of FP8 pages (figures at the kernel);
@@ -209,7 +231,7 @@ static int64_t choose_narrow_chunk(const std::vector<int64_t>& lengths, int Hkv,
 // Over 558 launches of 33-64 sequences, equal, spread and log-normal around 250-3000 keys, on both formats and head sizes: 4.5 %
 // less time than claims on average and nowhere more by a measurable amount (-1.2 % at worst, runs differ by 1); every second
 // round by index 4.3 % on average and up to 14 % more time at worst.
-bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
+static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int n_wg = plan.queue_begin[kWaveQueue], n_items = plan.queue_begin[kQueues];
     const int64_t slots = n_wg + ((int64_t)n_items - n_wg + kNarrowKernelWaves - 1) / kNarrowKernelWaves;
     if (slots <= wgs || slots > 2 * wgs) return false;
@@ -470,6 +492,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     // a workgroup's eight waves take eight wave tiles at a time
     const int64_t wave_groups = (plan->queue_begin[kQueues] - plan->queue_begin[kWaveQueue] + kWaves - 1) / kWaves;
     st.grid = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slots, plan->queue_begin[kWaveQueue] + wave_groups));
+    plan->four_waves = n_mfma == 0 && long_tiles_on_four_waves(*plan, kWgPerCu * o.num_cus, D, Hkv, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->by_index = n_mfma == 0 && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }

@@ -54,10 +54,10 @@ struct Step {
     int64_t items, groups;
 };
 
-// One decode step of sequences that see `keys` keys each, by 8 KV heads.
-static Step step(std::vector<int32_t> keys, int head_dim, bool fp8, int64_t chunk, int64_t grid, bool use_static = false) {
+// One decode step of sequences that see `keys` keys each.
+static Step step(std::vector<int32_t> keys, int head_dim, bool fp8, int64_t chunk, int64_t grid, bool use_static = false, int hkv = 8) {
     alignas(16) static char device[16];
-    const ppd_shape s = {32, 8, head_dim, 16, 1 << 20};
+    const ppd_shape s = {4 * hkv, hkv, head_dim, 16, 1 << 20};
     ppd_ctx* ctx = nullptr;
     CHECK(ppd_create(&s, 0, &ctx) == PPD_OK);
     if (fp8) CHECK(ppd_set_kv_format(ctx, PPD_KV_FP8_E4M3, 1.f, 1.f) == PPD_OK);
@@ -91,7 +91,7 @@ static void merged_once() {
         const int64_t chunks[] = {0, 64, 1024, 4096, 8192};
         const int64_t chunk = chunks[rng() % 5];
         const int32_t longest = 200 << (rng() % 8);
-        std::vector<int32_t> keys((size_t)(1 + rng() % 70));
+        std::vector<int32_t> keys((size_t)(1 + rng() % 120));
         const int32_t low = rng() % 2 ? longest / 2 : 0;
         for (auto& k : keys) k = 1 + low + (int32_t)(rng() % (longest - low));
         if (use_static && (chunk == 64 || chunk == 0)) continue;  // (plans that do not fit the static array)
@@ -107,7 +107,23 @@ static void merged_once() {
             launched += b.merge_launched;
         }
     }
+    std::printf("four waves %d, merged in the launch %d, by the merge launch %d\n", four, itself, launched);
     CHECK(four > 20 && itself > 20 && launched > 20);
+}
+
+// Long tiles run on four waves (256 workgroups) where their last round is nearly full or short.
+static void four_waves() {
+    auto four = [&](const std::vector<int32_t>& keys, int D = 128, bool fp8 = false) { return step(keys, D, fp8, 16384, 0).four_waves; };
+    CHECK(four(lengths(64, 3072)) && !four(lengths(64, 3071)) && !four(lengths(63, 5000)));  // two full rounds, less
+    for (int hkv : {4, 8, 12, 16}) CHECK(step(lengths(1536 / hkv, 5000), 128, false, 16384, 0, false, hkv).four_waves == (hkv % 8 == 0));
+    CHECK(!four(lengths(64, 5000), 64) && !four(lengths(64, 8000), 128, true));
+    CHECK(!four(lengths(65, 5000)) && !four(lengths(86, 5000)) && four(lengths(87, 5000)) && four(lengths(96, 5000)));
+    CHECK(!four(lengths(97, 5000)) && !four(lengths(200, 5000)) && four(lengths(330, 4000)));  // the tenth round: a tenth of it
+    std::vector<int32_t> keys = lengths(72, 5000);                                            // the last round is short
+    for (int i = 64; i < 72; ++i) keys[i] = 900;
+    CHECK(four(keys));
+    keys[70] = 1200;
+    CHECK(!four(keys));
 }
 
 // The second round of a decode-only launch (256 workgroups) is handed out by index where its pairs are balanced.
@@ -138,6 +154,7 @@ static void second_round() {
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "merged_once") merged_once();
+    else if (what == "four_waves") four_waves();
     else if (what == "second_round") second_round();
     else return 2;
     std::printf("ok\n");

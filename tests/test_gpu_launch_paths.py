@@ -370,7 +370,7 @@ def test_two_rounds_of_short_tiles_are_handed_out_by_index(B, fp8, wave):
 
 
 @pytest.mark.parametrize("static", [False, True])
-@pytest.mark.parametrize("G,grid", [(4, 0), (4, 1024), (1, 600), (8, 512)])
+@pytest.mark.parametrize("G,grid", [(4, 0), (4, 1024), (1, 720), (8, 512)])
 def test_long_split_tiles_are_merged_whatever_the_grid(G, grid, static):
     """Decode-only launches of at least two rounds of long tiles with split ranges, whole ones and ranges of one to three
     pages beside them, with fewer workgroups than tiles (grid 0) and with one for each (the sequences share two sequences'
@@ -378,7 +378,7 @@ def test_long_split_tiles_are_merged_whatever_the_grid(G, grid, static):
     import torch
     import paper_2603_13358_amd as ppd
 
-    B, longest = 40, 13000
+    B, longest = 48, 13000
     rng = np.random.default_rng(G)
     base = si.make_batch("grid", L=[longest - 1, longest - 9], n=[1, 1], Hq=8, Hkv=8, D=128, seed=G, slack_pages=2)
     pool, _, _ = gpu_step(base)
@@ -403,7 +403,7 @@ def test_long_split_tiles_are_merged_whatever_the_grid(G, grid, static):
             torch.cuda.synchronize()
             outs.append(from_dev_u16(out))
         stats = ctx.plan_stats()
-        assert stats.n_mfma == 0 and stats.n_groups > 0 and stats.n_items >= 512 and ctx.device_error_flags() == 0
+        assert stats.n_mfma == 0 and stats.n_groups > 0 and stats.n_items == 720 and ctx.device_error_flags() == 0  # 2.8 rounds
         assert stats.kv_bytes_tiles >= stats.n_items * 512 * 3072 and (g == 0 or stats.n_items <= stats.grid or g == 512)
         ctx.close()
     check_close(bits_to_f32(outs[0]).reshape(want.shape), want)
