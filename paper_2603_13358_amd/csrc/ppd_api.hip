@@ -383,6 +383,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.pace_keys = kp.mean_tile_keys;
     kp.four_waves = 0;
     kp.by_index = 0;
+    kp.partials_past_l2 = plan.stats.partial_floats * (int64_t)sizeof(float) >= 3 << 20;
     kp.pref_mode = ctx->opts.pref_mode;
     kp.narrow_cus = plan.narrow_cus;
     kp.max_pages = max_pages;

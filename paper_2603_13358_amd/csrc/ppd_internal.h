@@ -142,6 +142,7 @@ struct KParams {
     int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (long_tiles_on_four_waves), which leaves split ranges to ppd_merge_kernel
     int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed
+    int32_t partials_past_l2;  // ppd_narrow_kernel: see store_partial
     int32_t n_items;
     int32_t pref_mode;    // how a workgroup picks its preferred queue (see ppd_mixed_kernel)
     int32_t narrow_cus;   // pref_mode 2: compute units per XCD (of 32) that take narrow tiles first

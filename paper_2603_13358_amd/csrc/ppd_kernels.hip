@@ -768,11 +768,15 @@ __device__ __forceinline__ void mfma_item(const KParams& P, const ppd_work_item&
 // K and NV <= NK for V rotate, so that K of NK - 1 and V of NV - 1 pages per wave are in flight while one page is
 // computed), then the waves' (o, m, l) are combined through LDS, CB columns per pass.
 // ---------------------------------------------------------------------------------------------------
-// Where a launch merges split ranges itself (MERGED), a narrow tile's partial is read by another workgroup of the launch
-// (merge_last): it goes past the caches of this XCD, which the other XCDs do not see.
-template <bool MERGED>
-__device__ __forceinline__ void store_partial(float* p, float v) {
-    if constexpr (MERGED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// How a narrow tile's partial leaves.  Where the launch merges split ranges itself, another workgroup of the launch reads it
+// (merge_last): it goes past the caches of this XCD, which the other XCDs do not see.  Where a launch behind it merges, the L2
+// holds a few of them for it (64 sequences of 3500 keys log-normal, 0.6 MB of partials, past the L2 65.1 -> 68.4 us, 40 of 2900, 0.8
+// MB, 89.9 -> 92.6), but many cost the streams of a decode-only launch (181 of 8500 keys, 12 MB, 522 -> 513 us past the L2, 236 of
+// 15500, 20 MB, 1166 -> 1143; even at 2-3 MB): the launch says which.
+enum Partials { kToL2, kPastL2, kAsLaunched };
+template <Partials WAY>
+__device__ __forceinline__ void store_partial(const KParams& P, float* p, float v) {
+    if (WAY == kPastL2 || (WAY == kAsLaunched && P.partials_past_l2)) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else *p = v;
 }
 __device__ __forceinline__ f32x2 load_partial2(const float* p) {
@@ -796,7 +800,7 @@ struct NarrowCombine {
 // 1.65655e-3, of which the rounding of the result to bf16 alone is 1.65654e-3 (1.65654e-3 with the nearest number first).
 // Sums of their own for the second numbers keep infinities as well and are 0.5 % slower (decode steps of 64 sequences
 // of 1K-8K keys 810.7 -> 814.9 us over four calls with their appends, and 813.4 -> 813.6 this way).
-template <int HD, int NW, int NK, int NV, bool SOLO = false, bool SPLIT_P = false, bool MERGED = false>
+template <int HD, int NW, int NK, int NV, bool SOLO = false, bool SPLIT_P = false, Partials WAY = kToL2>
 __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
     constexpr int EB = 2;  // bytes per pool element
@@ -1046,10 +1050,10 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
                 if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
             } else {
                 float* pp = P.partials + it.part_off;
-                store_partial<MERGED>(pp + (int64_t)col * HD + d, o);
+                store_partial<WAY>(P, pp + (int64_t)col * HD + d, o);
                 if (d == 0) {
-                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2, mm);
-                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2 + 1, l);
+                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2, mm);
+                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2 + 1, l);
                 }
             }
         }
@@ -1069,7 +1073,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
 //   the octet the lane's V granules hold.
 // NS register sets of one page pair each rotate: NS - 1 pairs are in flight per wave besides the one being computed.
 // ---------------------------------------------------------------------------------------------------
-template <int HD, int NW, int NS, bool SOLO, bool FP8, bool MERGED = false>
+template <int HD, int NW, int NS, bool SOLO, bool FP8, Partials WAY = kToL2>
 __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
     constexpr int EB = FP8 ? 1 : 2;                       // bytes per pool element
@@ -1316,10 +1320,10 @@ __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_wor
                 if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
             } else {
                 float* pp = P.partials + it.part_off;
-                store_partial<MERGED>(pp + (int64_t)col * HD + d, o);
+                store_partial<WAY>(P, pp + (int64_t)col * HD + d, o);
                 if (d == 0) {
-                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2, mm);
-                    store_partial<MERGED>(pp + (int64_t)ncols * HD + col * 2 + 1, l);
+                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2, mm);
+                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2 + 1, l);
                 }
             }
         }
@@ -1583,8 +1587,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
         const int slot = blockIdx.x;
         if (slot >= n_wg) return;
         const ppd_work_item it = items[slot];
-        if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, true>(P, it, smem);
-        else narrow_item<HD, NW, NSETS, NSETS, false, false, true>(P, it, smem);
+        if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, kPastL2>(P, it, smem);
+        else narrow_item<HD, NW, NSETS, NSETS, false, false, kPastL2>(P, it, smem);
         if (it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, s_next);
         return;
     }
@@ -1595,8 +1599,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
     while (slot < slots) {
         if (slot < n_wg) {
             const ppd_work_item it = items[slot];
-            if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true>(P, it, smem);
-            else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves>(P, it, smem);
+            if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, kAsLaunched>(P, it, smem);
+            else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves, kAsLaunched>(P, it, smem);
         } else if constexpr (NW == kWaves) {
             const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
             if (mine < end) {

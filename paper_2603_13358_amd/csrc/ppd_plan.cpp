@@ -212,7 +212,7 @@ static bool long_tiles_on_four_waves(const Plan& plan, int64_t wgs, int head_dim
     for (int i = 0; i < n; ++i) sum += keys(i);
     if (sum / n < 3072) return false;
     const int64_t last = n % wgs;  // tiles of the last round, the shortest ones
-    return last == 0 || 10 * last >= 7 * wgs || 10 * keys(n - last) <= sum / wgs;
+    return last == 0 || 10 * last >= 7 * wgs || 7 * keys(n - last) <= sum / wgs;
 }
 
 // Whether a decode-only launch of more slots than workgroups hands its second round out by index (ppd_narrow_kernel) instead of

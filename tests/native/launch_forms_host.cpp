@@ -118,11 +118,11 @@ static void four_waves() {
     for (int hkv : {4, 8, 12, 16}) CHECK(step(lengths(1536 / hkv, 5000), 128, false, 16384, 0, false, hkv).four_waves == (hkv % 8 == 0));
     CHECK(!four(lengths(64, 5000), 64) && !four(lengths(64, 8000), 128, true));
     CHECK(!four(lengths(65, 5000)) && !four(lengths(86, 5000)) && four(lengths(87, 5000)) && four(lengths(96, 5000)));
-    CHECK(!four(lengths(97, 5000)) && !four(lengths(200, 5000)) && four(lengths(330, 4000)));  // the tenth round: a tenth of it
+    CHECK(!four(lengths(97, 5000)) && !four(lengths(200, 5000)) && four(lengths(230, 4000)));  // the eighth round: a seventh of the mean load
     std::vector<int32_t> keys = lengths(72, 5000);                                            // the last round is short
-    for (int i = 64; i < 72; ++i) keys[i] = 900;
+    for (int i = 64; i < 72; ++i) keys[i] = 1400;
     CHECK(four(keys));
-    keys[70] = 1200;
+    keys[70] = 1500;
     CHECK(!four(keys));
 }
 
