@@ -18,7 +18,10 @@
  *  - q, out, k, v and every page pool must start on a 16-byte boundary (the kernels move 16 bytes per lane);
  *    slot_mapping on an 8-byte, page_tables on a 4-byte boundary.  Anything else is PPD_ERR_RANGE.
  *  - bf16 = the upper 16 bits of an IEEE binary32.  Arithmetic: bf16 inputs, fp32 accumulation and
- *    softmax, probabilities rounded to bf16 before the PV product, bf16 output (round to nearest even).
+ *    softmax, probabilities rounded to bf16 before the PV product (one form of the decode-only kernel enters each
+ *    as two bf16 numbers, with less error: option "narrow_kernel" below), bf16 output (round to nearest even).
+ *  - A visible V element that is infinite makes its output column infinite, and NaN where infinities of both signs
+ *    meet or the element's probability is zero; NaN stays NaN.
  *  - Both calls are asynchronous on `stream` (a hipStream_t passed as void*; NULL = the default stream);
  *    the caller synchronises.  Host-side argument checks are complete before anything is enqueued: a
  *    negative return value means no device side effect.
@@ -132,8 +135,15 @@ const char *ppd_last_error(const ppd_ctx *ctx);
  * tiles on the caller's stream, narrow tiles on a stream of the context's own, joined before the call's work ends
  * -- 2 = the two specialised kernels also for steps of one kind), "narrow_kernel" (1, the default = with launch_mode 0 a step
  * without row-block tiles, i.e. a decode-only step, runs a kernel of its own that hands the first tiles out by
- * workgroup index instead of by atomic claims; same tiles, bit-identical results; 0 = always the one kernel), "timing" (1 = record HIP
- * events on the call's stream right before and after the attention kernel(s), see ppd_last_kernel_ms). */
+ * workgroup index instead of by atomic claims; same tiles; 0 = always the one kernel), "timing" (1 = record HIP
+ * events on the call's stream right before and after the attention kernel(s), see ppd_last_kernel_ms).
+ * The results with "narrow_kernel" 0 and 1 are bit-identical, except where the decode-only kernel runs its tiles on four
+ * waves: head_dim 128, bf16 pages, a multiple of 8 KV heads, no one-wave tiles, at least two tiles per compute unit, 3072 keys
+ * or more per tile on average, and the last round of tiles nearly full (70 % of the units) or short (its longest tile at
+ * most a seventh of a unit's mean load).  There the results have less error (probabilities as two bf16 numbers, four partial
+ * softmaxes per tile instead of eight), and so a row's rounding depends on the rest of its batch, as it does with the
+ * automatic split sizes.  "grid" changes which workgroup runs what, not the results, as long as "narrow_chunk" and
+ * "mfma_chunk" are set. */
 ppd_status ppd_set_option(ppd_ctx *ctx, const char *key, int64_t value);
 
 /* Element format of the page pools a context works on.  PPD_KV_BF16 (the default) is the paper's setting: KV in
@@ -191,7 +201,7 @@ double ppd_transfer_delay_s(int64_t n_tokens, int64_t kv_bytes_per_token, double
  *   L, n          HOST int32 [B]
  *   scale         softmax scale (>= 0, finite), applied to q.k before the softmax
  * Result per row is the softmax-weighted average of the visible V rows; run-to-run bitwise deterministic
- * for fixed arguments and options.  B = 0 is a no-op.  A batch whose work list would exceed 2^22 tiles (far beyond
+ * for fixed arguments and options (of the whole batch: split sizes and the kernel's form follow from it).  B = 0 is a no-op.  A batch whose work list would exceed 2^22 tiles (far beyond
  * any step that fits the chip: a 128K-token full prefill needs ~10^5) is refused with PPD_ERR_RANGE. */
 ppd_status ppd_mixed_attention(ppd_ctx *ctx, const void *q, const void *kv_pages, const int32_t *page_tables,
                                int32_t max_pages, const int32_t *L, const int32_t *n, int32_t B, float scale,
