@@ -1987,10 +1987,12 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, false>), mixed_lds_bytes(64));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<128, true>), mixed_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, true>), mixed_lds_bytes(64));
-    auto allow_narrow = [&](const NarrowForm& f) { allow(reinterpret_cast<const void*>(f.kernel), f.lds); };
-    allow_narrow(narrow_form(128, false, true, 0, 0, false));
-    for (int form = 0; form < 16; ++form)  // head size, page format, short and long tiles, merged in the launch or not
-        allow_narrow(narrow_form(form & 1 ? 128 : 64, (form & 2) != 0, false, form & 4 ? 1 << 20 : 0, form & 4 ? 1 << 20 : 0, (form & 8) != 0));
+    for (int form = 0; form < 8; ++form) {  // of the decode-only kernel eight waves at D = 128: page format, short and long tiles, merged in the launch or not
+        const int64_t keys = form & 2 ? 1 << 20 : 0;
+        const NarrowForm f = narrow_form(128, (form & 1) != 0, false, keys, keys, (form & 4) != 0);
+        allow(reinterpret_cast<const void*>(f.kernel), f.lds);
+    }
+    static_assert(NarrowCombine<kNarrowKernelWaves>::bytes(64) < 64 * 1024 - 16 && NarrowCombine<kStreamingWaves>::bytes(128) < 64 * 1024 - 16, "the other forms fit");
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<128>), ring_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<64>), ring_lds_bytes(64));
     return (int)e;

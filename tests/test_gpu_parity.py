@@ -475,16 +475,19 @@ def test_step_replays_from_a_hip_graph():
     ctx.close()
 
 
-def test_decode_only_step_replays_from_a_hip_graph():
-    """The same for a step without row-block tiles (the decode-only kernel), with more slots than workgroups so that
-    every replay claims from the cursor the replay before it has re-armed."""
+@pytest.mark.parametrize("options", [{"grid": 16}, {"grid": 1 << 12, "narrow_chunk": 128, "wave_tiles": 0}])
+def test_decode_only_step_replays_from_a_hip_graph(options):
+    """The same for a step without row-block tiles (the decode-only kernel): with more slots than workgroups, so that
+    every replay claims from the cursor the replay before it has re-armed, and with a workgroup for every tile, where
+    the last tile of a split range merges it and sets the count of its tiles back."""
     import torch
     from gpu_helpers import from_dev_u16, to_dev_u16
     rng = np.random.default_rng(63)
     b = si.make_batch("graph_dec", L=rng.integers(1, 900, size=60), n=np.ones(60, np.int64), Hq=32, Hkv=8, D=128, seed=63,
                       slack_pages=3)
-    pool_ref, out_ref, stats, ctx = _step(b, return_ctx=True, options={"grid": 16})
+    pool_ref, out_ref, stats, ctx = _step(b, return_ctx=True, options=options)
     assert stats["n_mfma"] == 0 and stats["n_narrow"] > 16
+    assert options["grid"] == 16 or (stats["n_groups"] > 0 and stats["n_items"] <= stats["grid"])
     dev = torch.device("cuda:0")
     pool = to_dev_u16(pool_ref, torch, dev)
     q = to_dev_u16(b.q, torch, dev)
