@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <unordered_map>
 
 #include "ppd_internal.h"
@@ -222,22 +223,24 @@ static bool long_tiles_on_four_waves(const Plan& plan, int64_t wgs, int head_dim
 //    of the workgroups, or the two shortest slots of which two must share a workgroup -- where a slot's fixed cost counts as
 //    128 KiB.  Equal and evenly spread lengths pair off to almost nothing above it; a long tile among short ones gets another
 //    behind it, where claims would leave it alone (us of 64 sequences of 800 keys, one of them 2.4 and 4 times as long, claimed
-//    43.8 and 49.0, by index 46.0 and 58.3; of log-normal lengths around 800 keys 40.6 and 42.5, at D = 64 25.6 and 28.6);
-//  * in a second round of less than a quarter, tiles below 256 KiB: a few workgroups decide such a step, and claims give its
-//    second tiles to those that are done first (264, 288, 304 and 320 tiles by 256 workgroups, by index against claimed: 1500
+//    43.8 and 49.0, by index 46.0 and 58.3; of log-normal lengths around 800 keys 40.6 and 42.5, at D = 64 25.6 and 28.6; 202 of
+//    205 keys on single waves and 10 of 530 39.1 and 46.1);
+//  * in a second round of less than a quarter, slots there below 256 KiB: a few workgroups decide such a step, and claims give
+//    them to those that are done first (264, 288, 304 and 320 tiles by 256 workgroups, by index against claimed: 1500
 //    keys of bf16 pages -4.1, -2.6, -1.0, +0.7 %, 1000 keys -3.1, -1.2, +0.4, +1.9, 600 keys -1.3, -0.4, +1.2, +2.5, 300 keys +6
 //    at 288; 3000 keys of FP8 pages -2.2, -1.3, -1.3, -0.4, 1200 keys -0.1, +1.2, +1.6, +2.3; D = 64, 1200 keys of bf16 pages
-//    -1.8, +1.2, +1.1, +1.4, 1000 keys +0.8, +1.3, +2.7, +3.3).
-// Over 558 launches of 33-64 sequences, equal, spread and log-normal around 250-3000 keys, on both formats and head sizes: 4.5 %
-// less time than claims on average and nowhere more by a measurable amount (-1.2 % at worst, runs differ by 1); every second
-// round by index 4.3 % on average and up to 14 % more time at worst.
+//    -1.8, +1.2, +1.1, +1.4, 1000 keys +0.8, +1.3, +2.7, +3.3); of three eighths where they are of one-wave tiles (264, 320 and
+//    400 slots of 300 keys, bf16 pages -3.9, -0.8 and +1.1 %, D = 64 -4.1, -2.8 and -0.5).
+// Over 558 launches of 33-64 sequences (equal, spread and log-normal around 250-3000 keys, both formats and head sizes) 5.4 % less
+// time than claims on average, over 800 of 264-500 sequences on single waves 2.4 %, -3.1 % at worst; every second round by index 5.1
+// and 1.9 % on average and up to 17 % more time at worst.
 static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int n_wg = plan.queue_begin[kWaveQueue], n_items = plan.queue_begin[kQueues];
     const int64_t slots = n_wg + ((int64_t)n_items - n_wg + kNarrowKernelWaves - 1) / kNarrowKernelWaves;
     if (slots <= wgs || slots > 2 * wgs) return false;
     constexpr int64_t kFixed = 128 * 1024, kAbove = 96 * 1024, kShort = 256 * 1024;
     const int64_t key_bytes = 2LL * head_dim * elem_bytes;
-    std::vector<int64_t> cost((size_t)slots, kFixed);
+    std::vector<int64_t> cost((size_t)slots, 0);
     int64_t keys = 0;
     for (int i = 0; i < n_items; ++i) {
         const int64_t k = plan.items[i].kv_end - plan.items[i].kv_begin;
@@ -245,13 +248,19 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
         keys += k;
     }
     if (keys / n_items * elem_bytes >= 3072) return false;
-    if (4 * slots < 5 * wgs && keys / n_items * key_bytes >= kShort) return false;
+    if (8 * slots < (wgs < n_wg ? 10 : 11) * wgs && cost[wgs] >= kShort) return false;
     int64_t sum = 0, longest = 0, heaviest = 0;
     for (int64_t b = 0; b < slots; ++b) {
+        if (b >= n_wg) cost[b] = cost[b] * 3 / 2 + kFixed;  // single waves start and stream slower: 370 keys of FP8 pages, D = 64, 16 us
+        cost[b] += kFixed;
         sum += cost[b];
+    }
+    for (int64_t b = 0; b < slots; ++b) {
         longest = std::max(longest, cost[b]);
         if (b < wgs) heaviest = std::max(heaviest, cost[b] + (2 * wgs - 1 - b < slots ? cost[2 * wgs - 1 - b] : 0));
     }
+    // (tiles are in order of their length, but a slot of eight one-wave tiles may take longer than the whole-workgroup tiles before it)
+    if (!std::is_sorted(cost.begin(), cost.end(), std::greater<int64_t>())) std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
     return heaviest <= std::max({longest, sum / wgs, cost[wgs - 1] + cost[wgs]}) + kAbove;
 }
 

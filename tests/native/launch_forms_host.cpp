@@ -146,6 +146,8 @@ static void second_round() {
                 }
     CHECK(!by_index(lengths(52, 800, 14, 1600)));                                          // 16 long tiles of 112 would get one
     CHECK(by_index(lengths(52, 800, 12, 1600)));                                           // none of 96 would
+    CHECK(by_index(lengths(300, 60)) && !by_index(lengths(351, 205)) && by_index(lengths(352, 205)));  // slots of eight one-wave tiles
+    CHECK(!by_index(lengths(212, 205, 10, 530)));
     std::vector<int32_t> even(64);
     for (int i = 0; i < 64; ++i) even[i] = 64 + i * 24;                                     // evenly spread: the pairs balance
     CHECK(by_index(even));
