@@ -383,6 +383,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.pace_keys = kp.mean_tile_keys;
     kp.four_waves = 0;
     kp.by_index = 0;
+    kp.wave_unit = 0;
     kp.partials_past_l2 = plan.stats.partial_floats * (int64_t)sizeof(float) >= 3 << 20;
     kp.pref_mode = ctx->opts.pref_mode;
     kp.narrow_cus = plan.narrow_cus;
@@ -425,13 +426,15 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         // pages 18.2 -> 16.6, 11 decodes of 300-6500 keys 34.4 -> 33.4).  With more rounds every tile but the last ones would
         // stop for its count while its unit could stream (66 decodes of 1K-32K, FP8 pages, 1576 tiles: +3 us of 440).  Tiles that
         // run on single waves leave their partials to the merge launch as well.
-        // Nor do the four-wave tiles merge: their form has no merge.
+        // Nor do the four-wave tiles merge: their form has no merge.  (Launches on single waves have no split range.)
         kp.four_waves = plan.four_waves;
+        kp.wave_unit = plan.wave_unit;
         if (n_wave == 0 && slots <= wgs && !kp.four_waves) kp.merge_groups = d_groups;
         kp.by_index = plan.by_index;
         const ppd_work_item& longest = plan.items[plan.queue_begin[ppd::kNarrowQueue]];
         kp.pace_keys = std::max<int64_t>(kp.mean_tile_keys, (longest.kv_end - longest.kv_begin) * wgs / std::max(wgs, slots));
-        rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, slots)), stream, ctx->fp8_pages);
+        const int64_t places = kp.wave_unit > 0 ? (kp.n_items + kp.wave_unit - 1) / kp.wave_unit : slots;  // of what a workgroup takes at a time
+        rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, places)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {
         rc = ppd::launch_mixed(kp, D, plan.stats.grid, stream, ctx->fp8_pages);

@@ -789,6 +789,13 @@ struct NarrowCombine {
     static constexpr size_t bytes(int head_dim) { return (size_t)NW * CB * (head_dim + 2) * sizeof(float); }
 };
 
+// Two probabilities as two bf16 numbers each (see SPLIT_P): the largest one below it, and the rounding of what that left out.
+__device__ __forceinline__ u32x2 split_bf16(float p0, float p1) {
+    const uint32_t b0 = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, p0), 1u) & 0xFFFF0000u;
+    const uint32_t b1 = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, p1), 1u) & 0xFFFF0000u;
+    return u32x2{b0 >> 16 | b1, pack_bf16(p0 - __builtin_bit_cast(float, b0), p1 - __builtin_bit_cast(float, b1))};
+}
+
 // SOLO: the calling wave runs the whole tile on its own (NW = 1): no LDS, no barrier, the result is written from the
 // accumulator registers; the other waves of the workgroup run other tiles at the same time.
 // (bf16 pages; FP8 pages are read by narrow_item_wide.)
@@ -927,16 +934,11 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = fast_exp2(__builtin_fmaf(sa[i], c, -mc));
         l_run += (p[0] + p[1]) + (p[2] + p[3]);
-        u32x2 pw;
-        float rest[4];
+        u32x2 pw, rp;
         if constexpr (SPLIT_P) {
-            uint32_t below[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                below[i] = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, p[i]), 1u) & 0xFFFF0000u;
-                rest[i] = p[i] - __builtin_bit_cast(float, below[i]);
-            }
-            pw = u32x2{below[0] >> 16 | below[1], below[2] >> 16 | below[3]};
+            const u32x2 a = split_bf16(p[0], p[1]), b = split_bf16(p[2], p[3]);
+            pw = u32x2{a[0], b[0]};
+            rp = u32x2{a[1], b[1]};
         } else {
             pw = u32x2{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
         }
@@ -945,7 +947,6 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
         for (int db = 0; db < DBN; ++db)
             oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), pb4, oacc[db], 0, 0, 0);
         if constexpr (SPLIT_P) {
-            const u32x2 rp = {pack_bf16(rest[0], rest[1]), pack_bf16(rest[2], rest[3])};
             const s16x4 rb4 = __builtin_bit_cast(s16x4, rp);
 #pragma unroll
             for (int db = 0; db < DBN; ++db)
@@ -1073,7 +1074,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
 //   the octet the lane's V granules hold.
 // NS register sets of one page pair each rotate: NS - 1 pairs are in flight per wave besides the one being computed.
 // ---------------------------------------------------------------------------------------------------
-template <int HD, int NW, int NS, bool SOLO, bool FP8, Partials WAY = kToL2>
+template <int HD, int NW, int NS, bool SOLO, bool FP8, bool SPLIT_P = false, Partials WAY = kToL2>
 __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
     constexpr int EB = FP8 ? 1 : 2;                       // bytes per pool element
@@ -1206,7 +1207,7 @@ __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_wor
             m_run = m_new;
         }
         const float mc = m_run == NEG_INF ? 0.f : m_run * c;
-        u32x4 pw[2];
+        u32x4 pw[2], rest[2];
         float psum = 0.f;
 #pragma unroll
         for (int pg = 0; pg < 2; ++pg)
@@ -1215,14 +1216,23 @@ __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_wor
                 const float p0 = fast_exp2(__builtin_fmaf(sa[pg * 8 + 2 * e], c, -mc));
                 const float p1 = fast_exp2(__builtin_fmaf(sa[pg * 8 + 2 * e + 1], c, -mc));
                 psum += p0 + p1;
-                pw[pg][e] = pack_bf16(p0, p1);
+                if constexpr (SPLIT_P) {
+                    const u32x2 two = split_bf16(p0, p1);
+                    pw[pg][e] = two[0];
+                    rest[pg][e] = two[1];
+                } else {
+                    pw[pg][e] = pack_bf16(p0, p1);
+                }
             }
         l_run += psum;
 #pragma unroll
         for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(s.v[pg][db]), as_bf16x8(pw[pg]), oacc[db], 0, 0, 0);
+            for (int db = 0; db < DB; ++db) {
+                const bf16x8 v = operand(s.v[pg][db]);
+                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, as_bf16x8(pw[pg]), oacc[db], 0, 0, 0);
+                if constexpr (SPLIT_P) oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, as_bf16x8(rest[pg]), oacc[db], 0, 0, 0);
+            }
     };
 
     if (my_steps > 0) {
@@ -1587,7 +1597,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
         const int slot = blockIdx.x;
         if (slot >= n_wg) return;
         const ppd_work_item it = items[slot];
-        if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, kPastL2>(P, it, smem);
+        if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, false, kPastL2>(P, it, smem);
         else narrow_item<HD, NW, NSETS, NSETS, false, false, kPastL2>(P, it, smem);
         if (it.part_off >= 0) merge_last<HD, NW>(P, items + slot, smem, s_next);
         return;
@@ -1599,7 +1609,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
     while (slot < slots) {
         if (slot < n_wg) {
             const ppd_work_item it = items[slot];
-            if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, kAsLaunched>(P, it, smem);
+            if constexpr (FP8) narrow_item_wide<HD, NW, NSETS, false, true, false, kAsLaunched>(P, it, smem);
             else narrow_item<HD, NW, NSETS, NSETS, false, NW != kWaves, kAsLaunched>(P, it, smem);
         } else if constexpr (NW == kWaves) {
             const int mine = n_wg + (slot - n_wg) * NW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1621,6 +1631,30 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
         __syncthreads();  // everyone has read s_next, and the previous tile's combine is over
     }
     if (claims && tid == 0) rearm_cursors(P, kNarrowQueue, kNarrowQueue + 1, 10);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Decode-only launches of many tiles, each on one wave (tiles_on_waves decides, and says what it measured).  A wave goes from
+// tile to tile on its own -- no LDS, no barrier, no claim -- so that what a tile costs before and after its stream of loads passes
+// under the streams of the unit's other waves.  Tiles come longest first and are taken in units of neighbours, which read the heads'
+// pieces of the same pages: units go to the workgroups up, down, up the list (unit 0 and the 512th last meet on the first
+// workgroup), so that every compute unit has as many bytes to read, and to the 8 / unit groups of a workgroup's waves in turn.
+// A wave has one running reference for a whole tile where eight have eight, hence SPLIT_P.  Bound by HBM: 256 sequences of
+// 64-700 keys by 8 heads, 405 MB, 81 us on whole workgroups (5.0 TB/s), 75 with a tile to a wave in the list's order (the first units
+// have the longest tiles only and cannot stream faster than 55 GB/s), 67.5 this way (6.0 TB/s).  Two register sets, on FP8 pages two page
+// pairs: three and four of bf16 pages are 7 and 5 % slower on average over 260 drawn launches and one FP8 pair 8 %, single wave or full chip.
+// ---------------------------------------------------------------------------------------------------
+template <int HD, bool FP8>
+__global__ __launch_bounds__(kThreads, 2) void ppd_wave_kernel(const ppd_work_item* items, int n_items, int unit, const KParams P) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grid = (int)gridDim.x, block = (int)blockIdx.x, groups = kWaves / unit;
+    for (int round = wave / unit;; round += groups) {
+        const int64_t mine = (int64_t)(round & 1 ? (round + 1) * grid - 1 - block : round * grid + block) * unit + wave % unit;
+        if (mine >= n_items) break;  // later rounds are further down the list
+        const ppd_work_item it = items[mine];
+        if constexpr (FP8) narrow_item_wide<HD, 1, kSoloSets, true, true, true>(P, it, nullptr);
+        else narrow_item<HD, 1, kSoloSets, kSoloSets, true, true>(P, it, nullptr);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -2012,6 +2046,12 @@ int launch_mixed(const KParams& p, int head_dim, int grid, void* stream, bool fp
 }
 
 int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool fp8_pages) {
+    if (p.wave_unit > 0) {
+        auto* const kernel = head_dim == 128 ? (fp8_pages ? &ppd_wave_kernel<128, true> : &ppd_wave_kernel<128, false>)
+                                             : (fp8_pages ? &ppd_wave_kernel<64, true> : &ppd_wave_kernel<64, false>);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), p.items, p.n_items, p.wave_unit, p);
+        return (int)hipGetLastError();
+    }
     const NarrowForm f = narrow_form(head_dim, fp8_pages, p.four_waves != 0, p.mean_tile_keys, p.pace_keys, p.merge_groups != nullptr);
     hipLaunchKernelGGL(f.kernel, dim3(grid), dim3(64 * f.waves), f.lds, static_cast<hipStream_t>(stream), p.items, p.n_wg, p.n_items, p);
     return (int)hipGetLastError();

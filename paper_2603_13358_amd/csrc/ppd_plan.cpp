@@ -264,6 +264,53 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
     return heaviest <= std::max({longest, sum / wgs, cost[wgs - 1] + cost[wgs]}) + kAbove;
 }
 
+// Whether every tile of a decode-only launch runs on one wave (ppd_wave_kernel), and in units of how many neighbours (0: no).  By
+// estimate, against the tiles on whole workgroups:
+//  * on whole workgroups a launch takes 6 us, 2.15 per round of tiles (3.3 on FP8 pages; tiles that the list already has on single waves
+//    count an eighth), and its bytes at 7.2 TB/s: within 4 % of 208 measured launches on average;
+//  * on waves it takes the longer of two flows of the bytes out of HBM at 6.7 TB/s: to the compute units, of which none takes more
+//    than 40 GB/s, and to the waves' chains of tiles, of which none takes more than 12 GB/s (6 at D = 64; FP8 pages 8 and 5).
+//    All take the same until the one with the least to read is done, and the others share what it took; then 4 us (6): within 4.5 %.
+// 4 % less has to come out.  Of 208 drawn launches of 520 tiles and more, bf16 and FP8 pages, both head sizes, equal, spread and log-normal
+// lengths around 60-4000 keys, it takes 83, for 22 % less time on average (200 sequences of 75 keys by 8 heads 0.41 of the time, 256 of
+// 64-700 keys 0.83, FP8 pages 0.63) and 2 % more at worst; taking the faster one each time would gain 0.1 % more over all of them.
+// Split ranges stay on whole workgroups, which merge them.  Below two and a half tiles for each compute unit (520 launches of 257-640 tiles) it is slower on average and not taken, and where
+// the list has every tile on single waves as it is (at most 384 keys each, and 1536 of them) the two differ by -18 to +27 %: that form stays.
+// Units of two where there are fewer than six tiles for each compute unit: more units have work then (640-1100 tiles 1.3 % less time).
+// By the device's workgroups, not by a grid override: the forms round differently, and that option stays scheduling only.
+static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
+    const int64_t n = plan.queue_begin[kQueues], n_wg = plan.queue_begin[kWaveQueue];
+    if (2 * n < 5 * wgs || n_wg == 0 || !plan.groups.empty()) return 0;
+    const bool fp8 = elem_bytes == 1;
+    const double key_bytes = 2.0 * head_dim * elem_bytes;
+    constexpr double kHbm = 6.7e6, kUnit = 40e3;  // bytes per us
+    const double wave_rate = fp8 ? (head_dim == 64 ? 5e3 : 8e3) : (head_dim == 64 ? 6e3 : 12e3);
+    const int64_t unit = n >= 6 * wgs ? 4 : 2, groups = kWaves / unit;
+    std::vector<double> units((size_t)wgs, 0.0), chains((size_t)(wgs * groups), 0.0);
+    double bytes = 0;
+    for (int64_t u = 0; u * unit < n; ++u) {  // as ppd_wave_kernel deals them
+        const int64_t round = u / wgs, at = u % wgs, wg = round & 1 ? wgs - 1 - at : at;
+        double sum = 0;
+        for (int64_t i = u * unit; i < std::min(n, (u + 1) * unit); ++i) sum += (plan.items[i].kv_end - plan.items[i].kv_begin) * key_bytes;
+        units[wg] += sum;
+        chains[wg * groups + round % groups] += (plan.items[u * unit].kv_end - plan.items[u * unit].kv_begin) * key_bytes;
+        bytes += sum;
+    }
+    auto flow = [&](std::vector<double>& loads, double each, int64_t readers) {  // us; a load is that of `readers` waves
+        std::sort(loads.begin(), loads.end());
+        double t = 0, level = 0;
+        for (size_t i = 0; i < loads.size(); ++i) {
+            t += (loads[i] - level) / std::min(each, kHbm / (double)((loads.size() - i) * readers));
+            level = loads[i];
+        }
+        return t;
+    };
+    const double on_waves = std::max(flow(units, kUnit, 1), flow(chains, wave_rate, unit)) + (fp8 ? 6.0 : 4.0);
+    const double rounds = ((double)n_wg + (double)(n - n_wg) / kWaves) / (double)wgs;
+    const double on_workgroups = 6.0 + (fp8 ? 3.3 : 2.15) * rounds + bytes / 7.2e6;
+    return on_waves < 0.96 * on_workgroups ? (int32_t)unit : 0;
+}
+
 ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, int32_t B, const PlanOptions& o,
                       Plan* plan, const char** err) {
     static const char* kNull = "L / n is NULL";
@@ -502,6 +549,8 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     const int64_t wave_groups = (plan->queue_begin[kQueues] - plan->queue_begin[kWaveQueue] + kWaves - 1) / kWaves;
     st.grid = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slots, plan->queue_begin[kWaveQueue] + wave_groups));
     plan->four_waves = n_mfma == 0 && long_tiles_on_four_waves(*plan, kWgPerCu * o.num_cus, D, Hkv, o.kv_elem_bytes == 1 ? 1 : 2);
+    plan->wave_unit = n_mfma == 0 && !plan->four_waves && o.wave_tiles < 0 && o.force_kind != 1
+                          ? tiles_on_waves(*plan, kWgPerCu * o.num_cus, D, o.kv_elem_bytes == 1 ? 1 : 2) : 0;
     plan->by_index = n_mfma == 0 && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }

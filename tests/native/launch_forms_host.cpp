@@ -153,11 +153,37 @@ static void second_round() {
     CHECK(by_index(even));
 }
 
+// Tiles run on single waves (256 compute units) where that is estimated to be faster: not below 640 tiles, not where a wave's chain
+// or a unit's bytes would outlast the rest, not where the list has all of them on single waves.
+static void on_waves() {
+    auto unit = [&](const std::vector<int32_t>& keys, int D = 128, bool fp8 = false, int64_t chunk = 0, int64_t grid = 0) {
+        const Step s = step(keys, D, fp8, chunk, grid);
+        CHECK((s.groups > 0) == (s.merges_itself || s.merge_launched) && !(s.merges_itself && s.merge_launched));
+        CHECK(!g_params.wave_unit || (g_grid <= 256 || grid > 256) && !s.merges_itself);
+        return g_params.wave_unit;
+    };
+    for (bool fp8 : {false, true}) {
+        for (int D : {64, 128}) {
+            CHECK(unit(lengths(79, 100), D, fp8) == 0 && unit(lengths(80, 100), D, fp8) == 2);
+            CHECK(unit(lengths(191, 100), D, fp8) == 2 && unit(lengths(192, 100), D, fp8) == 0);         // all in the list of one-wave tiles
+            CHECK(unit(lengths(192, 100, 16, 400), D, fp8) == 4);                                          // not all
+            CHECK(unit(lengths(192, 100, 16, 400), D, fp8, 0, 7) == 4 && unit(lengths(192, 100, 16, 400), D, fp8, 0, 4096) == 4);
+            CHECK(unit(lengths(100, 100, 1, 4000), D, fp8) == 0 && unit(lengths(192, 300, 64, 8000), D, fp8) == 0);
+        }
+        CHECK(unit(lengths(80, 300), 128, fp8, 320) == 2 && unit(lengths(80, 300, 1, 330), 128, fp8, 320) == 0);  // a split range
+    }
+    std::vector<int32_t> even(256);
+    for (int i = 0; i < 256; ++i) even[i] = 64 + i * 636 / 255;
+    CHECK(unit(even) == 4 && unit(even, 128, true) == 4 && unit(even, 64) == 4);
+    CHECK(unit(lengths(256, 3500)) == 0 && unit(lengths(64, 2000)) == 0);
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "merged_once") merged_once();
     else if (what == "four_waves") four_waves();
     else if (what == "second_round") second_round();
+    else if (what == "on_waves") on_waves();
     else return 2;
     std::printf("ok\n");
     return 0;
