@@ -274,13 +274,14 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
 // 4 % less has to come out.  Of 208 drawn launches of 520 tiles and more, bf16 and FP8 pages, both head sizes, equal, spread and log-normal
 // lengths around 60-4000 keys, it takes 83, for 22 % less time on average (200 sequences of 75 keys by 8 heads 0.41 of the time, 256 of
 // 64-700 keys 0.83, FP8 pages 0.63) and 2 % more at worst; taking the faster one each time would gain 0.1 % more over all of them.
-// Split ranges stay on whole workgroups, which merge them.  Below two and a half tiles for each compute unit (520 launches of 257-640 tiles) it is slower on average and not taken, and where
+// Split ranges stay on whole workgroups, which merge them, and so do more tiles than one round of the chip's waves and fewer than two:
+// the units of the second round come on top of evenly loaded compute units there (300 sequences of 64-700 keys 92 us where 467 MB need 70).  Below two and a half tiles for each compute unit (520 launches of 257-640 tiles) it is slower on average and not taken, and where
 // the list has every tile on single waves as it is (at most 384 keys each, and 1536 of them) the two differ by -18 to +27 %: that form stays.
 // Units of two where there are fewer than six tiles for each compute unit: more units have work then (640-1100 tiles 1.3 % less time).
 // By the device's workgroups, not by a grid override: the forms round differently, and that option stays scheduling only.
 static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int64_t n = plan.queue_begin[kQueues], n_wg = plan.queue_begin[kWaveQueue];
-    if (2 * n < 5 * wgs || n_wg == 0 || !plan.groups.empty()) return 0;
+    if (2 * n < 5 * wgs || (n > kWaves * wgs && n < 2 * kWaves * wgs) || n_wg == 0 || !plan.groups.empty()) return 0;
     const bool fp8 = elem_bytes == 1;
     const double key_bytes = 2.0 * head_dim * elem_bytes;
     constexpr double kHbm = 6.7e6, kUnit = 40e3;  // bytes per us

@@ -174,6 +174,7 @@ static void on_waves() {
     }
     std::vector<int32_t> even(256);
     for (int i = 0; i < 256; ++i) even[i] = 64 + i * 636 / 255;
+    CHECK(unit(lengths(256, 440)) == 4 && unit(lengths(257, 440)) == 0 && unit(lengths(511, 440)) == 0 && unit(lengths(512, 440)) == 4);  // rounds of the waves
     CHECK(unit(even) == 4 && unit(even, 128, true) == 4 && unit(even, 64) == 4);
     CHECK(unit(lengths(256, 3500)) == 0 && unit(lengths(64, 2000)) == 0);
 }

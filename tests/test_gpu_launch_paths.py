@@ -478,7 +478,8 @@ def test_decode_only_kernel_on_fp8_pages_of_head_size_64(L, options):
 
 
 @pytest.mark.parametrize("B,Hkv,D,n_long,options", [(80, 8, 128, 0, {}), (83, 8, 64, 0, {"grid": 7}), (161, 4, 128, 0, {}),
-                                                    (200, 8, 128, 25, {"grid": 4096}), (230, 7, 64, 30, {}), (260, 8, 128, 255, {})])
+                                                    (200, 8, 128, 25, {"grid": 4096}), (230, 7, 64, 30, {}), (256, 8, 128, 251, {}),
+                                                    (520, 8, 64, 500, {})])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_decode_tiles_on_single_waves(B, Hkv, D, n_long, options, fp8):
     """Launches of 640 short tiles and more, a wave to a tile: pages, and units of tiles, that are not full, one to three rounds of
