@@ -52,6 +52,7 @@ constexpr int kStreamingWaves = 4, kStreamingSets = 4;
 // 20.5 -> 19.1 us a layer without it).  Two at D = 64, where a pair is half the bytes, but for whole-workgroup tiles that are
 // too short to fill them (narrow_form).
 constexpr int fp8_sets(int head_dim) { return head_dim == 64 ? 2 : 1; }
+constexpr int kMaxPipelinedKeys = 64 * kPage * kWaves;  // of a tile of ppd_pipelined_kernel: a wave holds 64 page ids
 // Register sets of a wave of ppd_wave_kernel (one page of bf16 pages, one pair of FP8 pages each).
 constexpr int kSoloSets = 2;
 // Waves per workgroup of ppd_narrow_kernel, but for rounds of long tiles (kStreamingWaves).  Two workgroups of four waves per
@@ -102,6 +103,7 @@ struct Plan {
     int32_t queue_begin[kQueues + 1];  // items [queue_begin[q], queue_begin[q+1]) belong to queue q
     bool four_waves = false;         // decode-only launches: the form of four waves per workgroup
     int32_t wave_unit = 0;           // decode-only launches: not 0 where every tile runs on one wave (ppd_wave_kernel), in units of this many neighbours
+    bool pipelined = false;          // decode-only launches: more tiles than workgroups run one after the other in ppd_pipelined_kernel
     bool by_index = false;           // decode-only launches: the second round of slots is handed out by index
     int32_t narrow_cus = 16;         // of the 32 compute units of an XCD, how many take narrow tiles first
     std::vector<ppd_work_item> items;
@@ -143,6 +145,7 @@ struct KParams {
     int64_t mean_tile_keys;  // keys of the work list's tiles, on average
     int64_t pace_keys;       // ppd_narrow_kernel: the same, or the longest tile's keys over the launch's rounds where that is more
     int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (long_tiles_on_four_waves), which leaves split ranges to ppd_merge_kernel
+    int32_t pipelined;       // ppd_pipelined_kernel, which has at least as many slots as workgroups and no one-wave tiles
     int32_t wave_unit;       // not 0: ppd_wave_kernel, which takes the tiles in units of this many (1, 2, 4 or 8)
     int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed

@@ -796,9 +796,51 @@ __device__ __forceinline__ u32x2 split_bf16(float p0, float p1) {
     return u32x2{b0 >> 16 | b1, pack_bf16(p0 - __builtin_bit_cast(float, b0), p1 - __builtin_bit_cast(float, b1))};
 }
 
-// SOLO: the calling wave runs the whole tile on its own (NW = 1): no LDS, no barrier, the result is written from the
-// accumulator registers; the other waves of the workgroup run other tiles at the same time.
-// (bf16 pages; FP8 pages are read by narrow_item_wide.)
+// The waves' (o, m, l) of up to CB columns from c0 on, which each wave has left in `all`, become results or a partial.
+template <int HD, int NW, Partials WAY>
+__device__ __forceinline__ void narrow_combine(const KParams& P, const ppd_work_item& it, const float* all, int c0) {
+    constexpr int CB = NarrowCombine<NW>::CB, WSTRIDE = CB * (HD + 2), NT = NW * 64;
+    const int tid = threadIdx.x, G = P.G, ncols = it.nrows * G;
+    const float c = P.scale_log2e;
+    const int nc = ncols - c0 < CB ? ncols - c0 : CB;
+    for (int idx = tid; idx < nc * HD; idx += NT) {
+        const int cl = idx / HD, d = idx % HD;
+        const int col = c0 + cl;
+        float mw[NW], mm = NEG_INF;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            mw[w] = all[w * WSTRIDE + CB * HD + cl * 2];
+            mm = fmaxf(mm, mw[w]);
+        }
+        float o = 0.f, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float f = mw[w] == NEG_INF ? 0.f : fast_exp2((mw[w] - mm) * c);
+            o += f * all[w * WSTRIDE + cl * HD + d];
+            l += f * all[w * WSTRIDE + CB * HD + cl * 2 + 1];
+        }
+        if (it.part_off < 0) {
+            const int crow = col_row(col, P.invG);
+            const int64_t orow = (int64_t)(it.grow0 + crow) * P.Hq + it.kvh * G + (col - crow * G);
+            const float val = (o / l) * P.v_scale;
+            const float other = __shfl_xor(val, 1, 64);  // d and d^1 sit in neighbouring lanes
+            if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
+        } else {
+            float* pp = P.partials + it.part_off;
+            store_partial<WAY>(P, pp + (int64_t)col * HD + d, o);
+            if (d == 0) {
+                store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2, mm);
+                store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2 + 1, l);
+            }
+        }
+    }
+}
+
+// One page of a narrow tile: tokens t0 .. t0 + 15 of the sequence, whose K and V operands are in rs and rw.
+template <int HD>
+struct NarrowK { u32x4 k[HD / 32]; };  // K operand of the page: 16 tokens x 32 d per k-step
+template <int HD>
+struct NarrowV { u32x2 v[HD / 16]; };  // V^T operand: 4 tokens of one d, one per 16-row d block
 // SPLIT_P: a probability enters the second product as two bf16 numbers, the largest one below it and the rounding of what that
 // left out.  The probabilities of a wave are rounded relative to the wave's own running reference, and fewer waves have fewer
 // of them: four waves without it would have more rounding error than eight.  Below it, not nearest to it: both numbers of a
@@ -807,6 +849,75 @@ __device__ __forceinline__ u32x2 split_bf16(float p0, float p1) {
 // 1.65655e-3, of which the rounding of the result to bf16 alone is 1.65654e-3 (1.65654e-3 with the nearest number first).
 // Sums of their own for the second numbers keep infinities as well and are 0.5 % slower (decode steps of 64 sequences
 // of 1K-8K keys 810.7 -> 814.9 us over four calls with their appends, and 813.4 -> 813.6 this way).
+template <int HD, bool SPLIT_P>
+__device__ __forceinline__ void narrow_step(const ppd_work_item& it, int t0, int limit, float c, const bf16x8 (&qreg)[HD / 32], const NarrowK<HD>& rs,
+                                            NarrowV<HD>& rw, f32x4 (&oacc)[HD / 16], float& m_run, float& l_run) {
+    constexpr int KS = HD / 32, DBN = HD / 16;
+    const int g4 = (threadIdx.x & 63) >> 4;
+    const int min_limit = it.L + it.row0;
+    f32x4 sa = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(rs.k[ks]), qreg[ks], sa, 0, 0, 0);
+    // sa[i]: token 4*g4 + i of the page
+    const bool masked = t0 + kPage - 1 > min_limit || t0 + kPage > it.kv_end;
+    if (masked) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pa = t0 + 4 * g4 + i;
+            if (pa > limit || pa >= it.kv_end) sa[i] = NEG_INF;
+        }
+        if (t0 + kPage > it.kv_total) {  // rows of the last page that were never written
+#pragma unroll
+            for (int db = 0; db < DBN; ++db) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int pos = t0 + 4 * g4 + e;
+                    if (pos >= it.kv_total) rw.v[db][e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+                }
+            }
+        }
+    }
+    float mx = fmaxf(fmaxf(sa[0], sa[1]), fmaxf(sa[2], sa[3]));
+    mx = fmaxf(mx, xor_shuffle(mx, 16));
+    mx = max_halves(mx);
+    const float m_new = fmaxf(m_run, mx);
+    if (__any((m_new - m_run) * c > kLazyRescale)) {
+        const float m_use = m_new == NEG_INF ? 0.f : m_new;
+        const float alpha = fast_exp2(m_run * c - m_use * c);
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < DBN; ++db) oacc[db] *= alpha;
+        m_run = m_new;
+    }
+    const float mc = m_run == NEG_INF ? 0.f : m_run * c;
+    float p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = fast_exp2(__builtin_fmaf(sa[i], c, -mc));
+    l_run += (p[0] + p[1]) + (p[2] + p[3]);
+    u32x2 pw, rp;
+    if constexpr (SPLIT_P) {
+        const u32x2 a = split_bf16(p[0], p[1]), b = split_bf16(p[2], p[3]);
+        pw = u32x2{a[0], b[0]};
+        rp = u32x2{a[1], b[1]};
+    } else {
+        pw = u32x2{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
+    }
+    const s16x4 pb4 = __builtin_bit_cast(s16x4, pw);
+#pragma unroll
+    for (int db = 0; db < DBN; ++db)
+        oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), pb4, oacc[db], 0, 0, 0);
+    if constexpr (SPLIT_P) {
+        const s16x4 rb4 = __builtin_bit_cast(s16x4, rp);
+#pragma unroll
+        for (int db = 0; db < DBN; ++db)
+            oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), rb4, oacc[db], 0, 0, 0);
+    }
+}
+
+// SOLO: the calling wave runs the whole tile on its own (NW = 1): no LDS, no barrier, the result is written from the
+// accumulator registers; the other waves of the workgroup run other tiles at the same time.
+// (bf16 pages; FP8 pages are read by narrow_item_wide.)
 template <int HD, int NW, int NK, int NV, bool SOLO = false, bool SPLIT_P = false, Partials WAY = kToL2>
 __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_item& it, char* smem) {
     static_assert(!SOLO || NW == 1, "a solo tile is one wave");
@@ -862,8 +973,8 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
     // and may still be in the batch before (ids_old).
     int ids_old = 0, ids_cur = 0, ids_nxt = 0, k_batch = 0;
     auto load_ids = [&](int batch) { return load_page_id(pt_row, wave_first_page + batch * 64 + lane, last_page); };
-    struct KRegs { KVec k[KS]; };   // K operand of the page: 16 tokens x 32 d per k-step
-    struct VRegs { VVec v[DBN]; };  // V^T operand: 4 tokens of one d, one per 16-row d block
+    using KRegs = NarrowK<HD>;
+    using VRegs = NarrowV<HD>;
     KRegs rk[NK];
     VRegs rv[NV];
     const int my_steps = s_hi - s_lo;
@@ -892,67 +1003,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
         for (int db = 0; db < DBN; ++db)
             r.v[db] = __builtin_nontemporal_load(reinterpret_cast<const VVec*>(vb + v_lane_bytes + db * (128 * EB)));
     };
-    auto compute_step = [&](int k, KRegs& rs, VRegs& rw) {
-        f32x4 sa = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(rs.k[ks]), qreg[ks], sa, 0, 0, 0);
-        // sa[i]: token 4*g4 + i of the page
-        const int t0 = it.kv_begin + (s_lo + k) * kPage;
-        const bool masked = t0 + kPage - 1 > min_limit || t0 + kPage > it.kv_end;
-        if (masked) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int pa = t0 + 4 * g4 + i;
-                if (pa > limit || pa >= it.kv_end) sa[i] = NEG_INF;
-            }
-            if (t0 + kPage > it.kv_total) {  // rows of the last page that were never written
-#pragma unroll
-                for (int db = 0; db < DBN; ++db) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int pos = t0 + 4 * g4 + e;
-                        if (pos >= it.kv_total) rw.v[db][e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
-                    }
-                }
-            }
-        }
-        float mx = fmaxf(fmaxf(sa[0], sa[1]), fmaxf(sa[2], sa[3]));
-        mx = fmaxf(mx, xor_shuffle(mx, 16));
-        mx = max_halves(mx);
-        const float m_new = fmaxf(m_run, mx);
-        if (__any((m_new - m_run) * c > kLazyRescale)) {
-            const float m_use = m_new == NEG_INF ? 0.f : m_new;
-            const float alpha = fast_exp2(m_run * c - m_use * c);
-            l_run *= alpha;
-#pragma unroll
-            for (int db = 0; db < DBN; ++db) oacc[db] *= alpha;
-            m_run = m_new;
-        }
-        const float mc = m_run == NEG_INF ? 0.f : m_run * c;
-        float p[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) p[i] = fast_exp2(__builtin_fmaf(sa[i], c, -mc));
-        l_run += (p[0] + p[1]) + (p[2] + p[3]);
-        u32x2 pw, rp;
-        if constexpr (SPLIT_P) {
-            const u32x2 a = split_bf16(p[0], p[1]), b = split_bf16(p[2], p[3]);
-            pw = u32x2{a[0], b[0]};
-            rp = u32x2{a[1], b[1]};
-        } else {
-            pw = u32x2{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
-        }
-        const s16x4 pb4 = __builtin_bit_cast(s16x4, pw);
-#pragma unroll
-        for (int db = 0; db < DBN; ++db)
-            oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), pb4, oacc[db], 0, 0, 0);
-        if constexpr (SPLIT_P) {
-            const s16x4 rb4 = __builtin_bit_cast(s16x4, rp);
-#pragma unroll
-            for (int db = 0; db < DBN; ++db)
-                oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, rw.v[db]), rb4, oacc[db], 0, 0, 0);
-        }
-    };
+    auto compute_step = [&](int k, KRegs& rs, VRegs& rw) { narrow_step<HD, SPLIT_P>(it, it.kv_begin + (s_lo + k) * kPage, limit, c, qreg, rs, rw, oacc, m_run, l_run); };
 
     // K of NK - 1 pages and V of NV - 1 pages (4 KiB each at D = 128) are in flight per wave while one page is being
     // computed; the register sets rotate (period = NK steps if NK = NV, else NK * NV, unrolled).  The loads sit under conditions, so at
@@ -1026,38 +1077,7 @@ __device__ __forceinline__ void narrow_item(const KParams& P, const ppd_work_ite
             }
         }
         __syncthreads();
-        const int nc = ncols - c0 < CB ? ncols - c0 : CB;
-        for (int idx = tid; idx < nc * HD; idx += NT) {
-            const int cl = idx / HD, d = idx % HD;
-            const int col = c0 + cl;
-            float mw[NW], mm = NEG_INF;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                mw[w] = all[w * WSTRIDE + CB * HD + cl * 2];
-                mm = fmaxf(mm, mw[w]);
-            }
-            float o = 0.f, l = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float f = mw[w] == NEG_INF ? 0.f : fast_exp2((mw[w] - mm) * c);
-                o += f * all[w * WSTRIDE + cl * HD + d];
-                l += f * all[w * WSTRIDE + CB * HD + cl * 2 + 1];
-            }
-            if (it.part_off < 0) {
-                const int crow = col_row(col, P.invG);
-                const int64_t orow = (int64_t)(it.grow0 + crow) * P.Hq + it.kvh * G + (col - crow * G);
-                const float val = (o / l) * P.v_scale;
-                const float other = __shfl_xor(val, 1, 64);  // d and d^1 sit in neighbouring lanes
-                if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
-            } else {
-                float* pp = P.partials + it.part_off;
-                store_partial<WAY>(P, pp + (int64_t)col * HD + d, o);
-                if (d == 0) {
-                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2, mm);
-                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2 + 1, l);
-                }
-            }
-        }
+        narrow_combine<HD, NW, WAY>(P, it, all, c0);
     }
 }
 
@@ -1305,38 +1325,7 @@ __device__ __forceinline__ void narrow_item_wide(const KParams& P, const ppd_wor
             }
         }
         __syncthreads();
-        const int nc = ncols - c0 < CB ? ncols - c0 : CB;
-        for (int idx = tid; idx < nc * HD; idx += NT) {
-            const int cl = idx / HD, d = idx % HD;
-            const int col = c0 + cl;
-            float mw[NW], mm = NEG_INF;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                mw[w] = all[w * WSTRIDE + CB * HD + cl * 2];
-                mm = fmaxf(mm, mw[w]);
-            }
-            float o = 0.f, l = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float f = mw[w] == NEG_INF ? 0.f : fast_exp2((mw[w] - mm) * c);
-                o += f * all[w * WSTRIDE + cl * HD + d];
-                l += f * all[w * WSTRIDE + CB * HD + cl * 2 + 1];
-            }
-            if (it.part_off < 0) {
-                const int crow = col_row(col, P.invG);
-                const int64_t orow = (int64_t)(it.grow0 + crow) * P.Hq + it.kvh * G + (col - crow * G);
-                const float val = (o / l) * P.v_scale;
-                const float other = __shfl_xor(val, 1, 64);  // d and d^1 sit in neighbouring lanes
-                if ((d & 1) == 0) *reinterpret_cast<uint32_t*>(P.out + orow * HD + d) = pack_bf16(val, other);
-            } else {
-                float* pp = P.partials + it.part_off;
-                store_partial<WAY>(P, pp + (int64_t)col * HD + d, o);
-                if (d == 0) {
-                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2, mm);
-                    store_partial<WAY>(P, pp + (int64_t)ncols * HD + col * 2 + 1, l);
-                }
-            }
-        }
+        narrow_combine<HD, NW, WAY>(P, it, all, c0);
     }
 }
 
@@ -1630,6 +1619,154 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
         slot = __builtin_amdgcn_readfirstlane(*s_next);
         __syncthreads();  // everyone has read s_next, and the previous tile's combine is over
     }
+    if (claims && tid == 0) rearm_cursors(P, kNarrowQueue, kNarrowQueue + 1, 10);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Decode-only launches of several rounds of short tiles (bf16 pages; whole-workgroup tiles).  A short tile streams for a few
+// microseconds, and the same again went by between its last load and the first one of the next tile: the combine, the claim, and
+// three reads that wait for one another (work item, page ids, K and V).  Here all of that happens ahead.  While a tile runs, the
+// workgroup holds the work item of the next two, page ids and queries of the next one, and a claim under way; the first kSets
+// pages of the next tile are asked for as soon as a wave is through with its share of this one, before the waves' results meet in
+// LDS (two buffers, so that a tile needs one barrier, which leaves the loads in flight).
+// The first three slots of a workgroup go by index, up, down and up the list, longest tiles first; the others are claimed.  Bit for bit
+// the results of ppd_narrow_kernel.  A launch of 8 tiles of 100 keys to a workgroup 47.0 -> 37.5 us, of 8 of 382 79.3 -> 74.3, of 3 of 800-1600
+// 79.1 -> 75.5 (6.2 TB/s); two, three and four register sets, and the heads of a page on one XCD or on eight, are within 1 %.  What is left of a
+// tile of 100 keys is 4 us: one trip of its loads, and its pages worked.
+// ---------------------------------------------------------------------------------------------------
+constexpr int kPipelinedSets = 3, kByIndexSlots = 3;
+template <int HD>
+constexpr size_t pipelined_lds_bytes() { return 2 * NarrowCombine<kWaves>::bytes(HD); }
+
+template <int HD>
+__global__ __launch_bounds__(kThreads, 2) void ppd_pipelined_kernel(const ppd_work_item* items, int slots, const KParams P) {
+    constexpr int NW = kWaves, NS = kPipelinedSets, KS = HD / 32, DBN = HD / 16, CB = NarrowCombine<NW>::CB, WSTRIDE = CB * (HD + 2);
+    static_assert(CB == kNarrowCols, "one pass of the combine takes all columns");
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // two combine buffers
+    __shared__ int s_claimed[2];
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grid = (int)gridDim.x, block = (int)blockIdx.x, G = P.G;
+    if (block >= slots) return;
+    const float c = P.scale_log2e;
+    const bool claims = slots > kByIndexSlots * grid;
+    typedef const __attribute__((address_space(4))) ppd_work_item* ItemPtr;  // read through the scalar cache: no kernel writes work items
+    // a tile as the workgroup holds it; one of no steps where the slot does not exist
+    struct Tile {
+        ppd_work_item it;
+        int slot, first_page, steps;  // of this wave: its share of the pages
+    };
+    auto tile_of = [&](int slot) {
+        Tile t;
+        t.slot = slot;
+        const ItemPtr p = (ItemPtr)(uintptr_t)(items + (slot < slots ? slot : slots - 1));
+        t.it.seq = p->seq; t.it.kvh = p->kvh; t.it.row0 = p->row0; t.it.nrows = p->nrows; t.it.grow0 = p->grow0; t.it.L = p->L;
+        t.it.kv_total = p->kv_total; t.it.kv_begin = p->kv_begin; t.it.kv_end = p->kv_end; t.it.part_off = p->part_off;
+        const int npages = (t.it.kv_end - t.it.kv_begin + kPage - 1) >> 4;
+        t.first_page = wave * npages / NW;
+        t.steps = slot < slots ? (wave + 1) * npages / NW - t.first_page : 0;
+        t.first_page += t.it.kv_begin >> 4;
+        return t;
+    };
+    // lane i: the page of the share's logical page i (a share is at most 64 pages)
+    auto ids_of = [&](const Tile& t) {
+        return load_page_id(P.page_tables + (int64_t)t.it.seq * P.max_pages, t.first_page + lane, (t.it.kv_total - 1) >> 4);
+    };
+    struct Column { int jrow, head; };
+    auto column = [&](const Tile& t) {
+        const int ncols = t.it.nrows * G, colc = c16 < ncols ? c16 : ncols - 1, jrow = col_row(colc, P.invG);
+        return Column{jrow, t.it.kvh * G + (colc - jrow * G)};
+    };
+    struct Queries { u32x4 w[KS]; };
+    auto queries_of = [&](const Tile& t) {
+        const Column col = column(t);
+        const uint16_t* qp = P.q + ((int64_t)(t.it.grow0 + col.jrow) * P.Hq + col.head) * HD + g4 * 8;
+        Queries q;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) q.w[ks] = *reinterpret_cast<const u32x4*>(qp + ks * 32);
+        return q;
+    };
+    NarrowK<HD> rk[NS];
+    NarrowV<HD> rv[NS];
+    const uint32_t k_lane_bytes = (uint32_t)(g4 * 128 + c16 * 8) * 2;                          // + ks * 512 elements
+    const uint32_t v_lane_bytes = (uint32_t)(((g4 >> 1) * HD + c16) * 8 + (g4 & 1) * 4) * 2;  // + db * 128 elements
+    const int64_t v_off = (int64_t)P.Hkv * (kPage * HD);
+    auto issue = [&](const Tile& t, int ids, int k, NarrowK<HD>& r, NarrowV<HD>& w) {
+        const int64_t pa = checked_page(P, __builtin_amdgcn_readlane(ids, k));
+        const char* kb = reinterpret_cast<const char*>(P.pool) + (pa * P.page_stride + (int64_t)t.it.kvh * (kPage * HD)) * 2;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) r.k[ks] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kb + k_lane_bytes + ks * 1024));
+        const char* vb = kb + v_off * 2;
+#pragma unroll
+        for (int db = 0; db < DBN; ++db) w.v[db] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(vb + v_lane_bytes + db * 256));
+    };
+    auto begin = [&](const Tile& t, int ids) {
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+            if (j < t.steps) issue(t, ids, j, rk[j], rv[j]);
+    };
+    unsigned claim = 0;
+    auto draw = [&]() {  // only thread 0's is used
+        if (claims && tid == 0) claim = atomicAdd(&P.counters[kCursorBase + kNarrowQueue * kCursorStride], 1u);
+    };
+
+    Tile cur = tile_of(block), nxt = tile_of(2 * grid - 1 - block), far = tile_of(2 * grid + block);
+    int ids_cur = ids_of(cur);
+    Queries q_cur = queries_of(cur);
+    int ids_nxt = ids_of(nxt);
+    Queries q_nxt = queries_of(nxt);
+    draw();
+    begin(cur, ids_cur);
+    for (int parity = 0;; parity ^= 1) {
+        const int ncols = cur.it.nrows * G, limit = cur.it.L + cur.it.row0 + column(cur).jrow;
+        bf16x8 qreg[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qreg[ks] = as_bf16x8(c16 < ncols ? q_cur.w[ks] : u32x4{0, 0, 0, 0});
+        f32x4 oacc[DBN];
+#pragma unroll
+        for (int db = 0; db < DBN; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float m_run = NEG_INF, l_run = 0.f;
+        for (int k = 0; k < cur.steps; k += NS) {
+#pragma unroll
+            for (int j = 0; j < NS; ++j) {
+                if (k + j < cur.steps) {
+                    narrow_step<HD, false>(cur.it, (cur.first_page + k + j) * kPage, limit, c, qreg, rk[j], rv[j], oacc, m_run, l_run);
+                    if (k + j + NS < cur.steps) issue(cur, ids_cur, k + j + NS, rk[j], rv[j]);
+                }
+            }
+        }
+        // the next tile's pages, and what the one behind it needs
+        begin(nxt, ids_nxt);
+        ids_cur = ids_nxt;
+        q_cur = q_nxt;
+        ids_nxt = ids_of(far);
+        q_nxt = queries_of(far);
+        const int drawn = (int)claim;
+        if (grid * kByIndexSlots + drawn < slots) draw();
+        l_run += xor_shuffle(l_run, 16);
+        l_run = sum_halves(l_run);
+        float* const all = reinterpret_cast<float*>(smem) + parity * (NW * WSTRIDE);
+        float* const wbuf = all + wave * WSTRIDE;
+        if (c16 < ncols) {
+#pragma unroll
+            for (int db = 0; db < DBN; ++db) *reinterpret_cast<f32x4*>(wbuf + c16 * HD + db * 16 + 4 * g4) = oacc[db];
+            if (g4 == 0) {
+                wbuf[CB * HD + c16 * 2] = m_run;
+                wbuf[CB * HD + c16 * 2 + 1] = l_run;
+            }
+        }
+        if (tid == 0) s_claimed[parity] = drawn;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // for LDS only: the loads stay in flight
+        const int slot = claims ? kByIndexSlots * grid + __builtin_amdgcn_readfirstlane(*(volatile int*)&s_claimed[parity]) : slots;
+        const Tile got = tile_of(slot);
+        narrow_combine<HD, NW, kAsLaunched>(P, cur.it, all, 0);
+        cur = nxt;
+        nxt = far;
+        far = got;
+        if (cur.slot >= slots) break;
+    }
+    // this workgroup's last claim has to have reached its cursor before the cursor is re-armed
+    asm volatile("" : : "v"(claim));
     if (claims && tid == 0) rearm_cursors(P, kNarrowQueue, kNarrowQueue + 1, 10);
 }
 
@@ -2027,6 +2164,8 @@ int prepare_mixed_kernels() {
         allow(reinterpret_cast<const void*>(f.kernel), f.lds);
     }
     static_assert(NarrowCombine<kNarrowKernelWaves>::bytes(64) < 64 * 1024 - 16 && NarrowCombine<kStreamingWaves>::bytes(128) < 64 * 1024 - 16, "the other forms fit");
+    allow(reinterpret_cast<const void*>(&ppd_pipelined_kernel<128>), pipelined_lds_bytes<128>());
+    allow(reinterpret_cast<const void*>(&ppd_pipelined_kernel<64>), pipelined_lds_bytes<64>());
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<128>), ring_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mfma_kernel<64>), ring_lds_bytes(64));
     return (int)e;
@@ -2046,6 +2185,13 @@ int launch_mixed(const KParams& p, int head_dim, int grid, void* stream, bool fp
 }
 
 int launch_narrow(const KParams& p, int head_dim, int grid, void* stream, bool fp8_pages) {
+    if (p.pipelined) {
+        if (head_dim == 128)
+            hipLaunchKernelGGL(ppd_pipelined_kernel<128>, dim3(grid), dim3(kThreads), pipelined_lds_bytes<128>(), static_cast<hipStream_t>(stream), p.items, p.n_wg, p);
+        else
+            hipLaunchKernelGGL(ppd_pipelined_kernel<64>, dim3(grid), dim3(kThreads), pipelined_lds_bytes<64>(), static_cast<hipStream_t>(stream), p.items, p.n_wg, p);
+        return (int)hipGetLastError();
+    }
     if (p.wave_unit > 0) {
         auto* const kernel = head_dim == 128 ? (fp8_pages ? &ppd_wave_kernel<128, true> : &ppd_wave_kernel<128, false>)
                                              : (fp8_pages ? &ppd_wave_kernel<64, true> : &ppd_wave_kernel<64, false>);

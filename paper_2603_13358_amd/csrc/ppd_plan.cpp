@@ -264,6 +264,22 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
     return heaviest <= std::max({longest, sum / wgs, cost[wgs - 1] + cost[wgs]}) + kAbove;
 }
 
+// Whether the whole-workgroup tiles of a decode-only launch on bf16 pages run in ppd_pipelined_kernel where a workgroup gets more than one.
+// What it saves is the gap between two tiles, which counts while tiles are short; and it holds three tiles ahead, so that a workgroup
+// with one far longer than the others keeps what an idle one could have run.  Of 181 drawn launches of 257-2500 tiles, against tiles
+// one after the other (mean keys at D = 128, longest by mean): up to 300, up to 1.7 -13 %; up to 300, 1.7-3 -8; 300-600, up to 1.7 -3; 600-900 -2;
+// 900-2500 +1; 300-900, 1.7-2.2 +0.5; above 3 +11.  At D = 64 up to 300, 3.0 -8 %; 300-900, 1.7 -9; 900-1300 -7; above 3 +8.
+// 320 KiB are 625 keys at D = 128 and 1250 at D = 64.
+static bool tiles_pipelined(const Plan& plan, int head_dim, int elem_bytes) {
+    const int64_t n = plan.queue_begin[kQueues];
+    if (elem_bytes != 2 || n == 0 || plan.queue_begin[kWaveQueue] != n) return false;
+    int64_t sum = 0;
+    for (int64_t i = 0; i < n; ++i) sum += plan.items[i].kv_end - plan.items[i].kv_begin;
+    const int64_t longest = plan.items[0].kv_end - plan.items[0].kv_begin, mean_bytes = sum / n * 2 * head_dim * elem_bytes;
+    static_assert(kMaxPipelinedKeys >= 3 * (320 << 10) / (2 * 64 * 2), "a wave's share of the longest tile fits its page ids");
+    return mean_bytes <= 320 << 10 && longest * n * 10 <= sum * (mean_bytes <= 150 << 10 ? 30 : 17);
+}
+
 // Whether every tile of a decode-only launch runs on one wave (ppd_wave_kernel), and in units of how many neighbours (0: no).  By
 // estimate, against the tiles on whole workgroups:
 //  * on whole workgroups a launch takes 6 us, 2.15 per round of tiles (3.3 on FP8 pages; tiles that the list already has on single waves
@@ -275,7 +291,8 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
 // lengths around 60-4000 keys, it takes 83, for 22 % less time on average (200 sequences of 75 keys by 8 heads 0.41 of the time, 256 of
 // 64-700 keys 0.83, FP8 pages 0.63) and 2 % more at worst; taking the faster one each time would gain 0.1 % more over all of them.
 // Split ranges stay on whole workgroups, which merge them, and so do more tiles than one round of the chip's waves and fewer than two:
-// the units of the second round come on top of evenly loaded compute units there (300 sequences of 64-700 keys 92 us where 467 MB need 70).  Below two and a half tiles for each compute unit (520 launches of 257-640 tiles) it is slower on average and not taken, and where
+// the units of the second round come on top of evenly loaded compute units there (300 sequences of 64-700 keys 83 us
+// where 467 MB need 70), and whole workgroups give the mixed kernel's results bit for bit.  Below two and a half tiles for each compute unit (520 launches of 257-640 tiles) it is slower on average and not taken, and where
 // the list has every tile on single waves as it is (at most 384 keys each, and 1536 of them) the two differ by -18 to +27 %: that form stays.
 // Units of two where there are fewer than six tiles for each compute unit: more units have work then (640-1100 tiles 1.3 % less time).
 // By the device's workgroups, not by a grid override: the forms round differently, and that option stays scheduling only.
@@ -552,6 +569,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     plan->four_waves = n_mfma == 0 && long_tiles_on_four_waves(*plan, kWgPerCu * o.num_cus, D, Hkv, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->wave_unit = n_mfma == 0 && !plan->four_waves && o.wave_tiles < 0 && o.force_kind != 1
                           ? tiles_on_waves(*plan, kWgPerCu * o.num_cus, D, o.kv_elem_bytes == 1 ? 1 : 2) : 0;
+    plan->pipelined = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && tiles_pipelined(*plan, D, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->by_index = n_mfma == 0 && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }

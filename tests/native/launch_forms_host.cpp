@@ -179,12 +179,26 @@ static void on_waves() {
     CHECK(unit(lengths(256, 3500)) == 0 && unit(lengths(64, 2000)) == 0);
 }
 
+// More tiles than workgroups run pipelined where they are short and of a length, on bf16 pages and whole workgroups.
+static void pipelined() {
+    auto runs = [&](const std::vector<int32_t>& keys, int D = 128, bool fp8 = false, int64_t grid = 0, int hkv = 8) {
+        step(keys, D, fp8, 8192, grid, false, hkv);
+        CHECK(!g_params.pipelined || (!g_params.wave_unit && !g_params.four_waves && !g_params.merge_groups && g_params.n_wg == g_params.n_items && g_grid < g_params.n_items));
+        return g_params.pipelined != 0;
+    };
+    CHECK(!runs(lengths(32, 200)) && runs(lengths(33, 200)) && runs(lengths(79, 200)) && runs(lengths(20, 200), 128, false, 100));
+    CHECK(!runs(lengths(33, 200), 128, true) && runs(lengths(33, 640)) && !runs(lengths(33, 641)) && runs(lengths(33, 1280), 64) && !runs(lengths(33, 1281), 64));
+    CHECK(runs(lengths(40, 400, 4, 700)) && !runs(lengths(40, 400, 4, 800)) && runs(lengths(40, 200, 4, 600)) && !runs(lengths(40, 200, 4, 800)));
+    CHECK(!runs(lengths(64, 5000)) && !runs(lengths(256, 100)) && !runs(lengths(256, 440)));
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "merged_once") merged_once();
     else if (what == "four_waves") four_waves();
     else if (what == "second_round") second_round();
     else if (what == "on_waves") on_waves();
+    else if (what == "pipelined") pipelined();
     else return 2;
     std::printf("ok\n");
     return 0;

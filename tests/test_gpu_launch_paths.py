@@ -508,3 +508,35 @@ def test_decode_tiles_on_single_waves(B, Hkv, D, n_long, options, fp8):
         outs.append(out)
     assert np.array_equal(outs[0], outs[1])
     assert errors[0] <= 0.875 * errors[2], errors
+
+
+@pytest.mark.parametrize("B,Hkv,D,grid", [(33, 8, 128, 0), (70, 8, 128, 0), (37, 2, 128, 8), (49, 1, 128, 16), (48, 1, 64, 16), (23, 3, 64, 5), (130, 1, 128, 3)])
+def test_rounds_of_short_tiles_run_pipelined(B, Hkv, D, grid):
+    """Decode-only launches of 1.03 to 43 rounds of short whole-workgroup tiles on bf16 pages: three rounds go by index and the rest is
+    claimed; shares of no page and of several, last pages partly filled, multi-row tiles.  The oracle's result, bit for bit the
+    mixed kernel's, and again on one context (the cursor is left re-armed)."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    rng = np.random.default_rng(B)
+    L = rng.integers(60, 420, B)
+    L[:5] = [0, 15, 16, 17, 419]
+    n = np.where(np.arange(B) % 7 == 6, 3, 1)
+    b = si.make_batch("pipe", L=L, n=n, Hq=4 * Hkv, Hkv=Hkv, D=D, seed=B, slack_pages=3)
+    options = {"grid": grid, "wave_tiles": 0}
+    pool, out, stats = gpu_step(b, options=options)
+    assert stats["n_mfma"] == 0 and stats["n_narrow"] == B * Hkv > stats["grid"] and stats["n_groups"] == 0
+    check_close(bits_to_f32(out), oracle_out(b))
+    _, mixed, _ = gpu_step(b, options=dict(options, narrow_kernel=0))
+    assert np.array_equal(out, mixed)
+    dev = torch.device("cuda:0")
+    ctx = ppd.Context(4 * Hkv, Hkv, D, b.num_pages)
+    for key, value in options.items():
+        ctx.set_option(key, value)
+    dpool, q, pt = to_dev_u16(pool, torch, dev), to_dev_u16(b.q, torch, dev), torch.from_numpy(b.page_tables).to(dev)
+    for call in (ctx.mixed_attention, ctx.mixed_attention, ctx.mixed_attention_static, ctx.mixed_attention):
+        got = torch.zeros((b.T, b.Hq, b.D), dtype=torch.int16, device=dev)
+        call(q, dpool, pt, b.L, b.n, b.scale, got)
+        torch.cuda.synchronize()
+        assert np.array_equal(from_dev_u16(got).reshape(out.shape), out)
+    ctx.close()
