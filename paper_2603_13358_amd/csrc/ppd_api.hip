@@ -57,7 +57,11 @@ struct ppd_ctx {
     // engine step call with the same lengths): such calls skip planning and upload
     std::vector<int32_t> plan_L, plan_n;
     ppd::PlanOptions plan_opts;
+    int plan_launch_mode = 0;
     bool plan_on_device = false;
+    // the mixed kernel's list is in the order of its workgroups, one for each entry
+    bool plan_by_block = false;
+    std::vector<int32_t> block_order;
     // where that plan lives: 1 = the context's own workspace, 2 = the library's static scratch array
     int plan_where = 0;
     hipStream_t plan_stream = nullptr;  // the stream the plan was uploaded on and the last call ran on
@@ -253,7 +257,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     if (ctx->launch_mode != 0) opts.wave_tiles = 0;  // the specialised kernels run every narrow tile on four waves
     opts.kv_elem_bytes = ctx->fp8_pages ? 1 : 2;
     const bool same_opts = std::memcmp(&ctx->plan_opts, &opts, sizeof(ppd::PlanOptions)) == 0;
-    const bool reuse = ctx->plan_on_device && ctx->plan_where == where && same_opts &&
+    const bool reuse = ctx->plan_on_device && ctx->plan_where == where && same_opts && ctx->plan_launch_mode == ctx->launch_mode &&
                        (!use_static || g_scratch_owner[ctx->device] == ctx) && (int32_t)ctx->plan_L.size() == B &&
                        std::memcmp(ctx->plan_L.data(), L, sizeof(int32_t) * B) == 0 &&
                        std::memcmp(ctx->plan_n.data(), n, sizeof(int32_t) * B) == 0;
@@ -325,6 +329,11 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         }
         void* host = sg.host;
         std::memcpy(host, plan.items.data(), items_bytes);
+        ctx->plan_by_block = ctx->launch_mode == 0 && plan.stats.n_mfma > 0 && ppd::has_workgroup_per_entry(plan);
+        if (ctx->plan_by_block) {
+            ppd::order_by_block(plan, &ctx->block_order);
+            for (size_t b = 0; b < ctx->block_order.size(); ++b) static_cast<ppd_work_item*>(host)[b] = plan.items[ctx->block_order[b]];
+        }
         if (groups_bytes) {
             std::memcpy(static_cast<char*>(host) + items_bytes, plan.groups.data(), groups_bytes);
             std::memcpy(static_cast<char*>(host) + items_bytes + groups_bytes, plan.units.data(), units_bytes);
@@ -349,6 +358,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         ctx->plan_L.assign(L, L + B);
         ctx->plan_n.assign(n, n + B);
         ctx->plan_opts = opts;
+        ctx->plan_launch_mode = ctx->launch_mode;
         ctx->plan_on_device = true;
         ctx->plan_where = where;
         ctx->plan.stats.plan_host_us = (int32_t)std::chrono::duration_cast<std::chrono::microseconds>(
@@ -383,6 +393,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.pace_keys = kp.mean_tile_keys;
     kp.four_waves = 0;
     kp.by_index = 0;
+    kp.by_block = ctx->plan_by_block;
     kp.wave_unit = 0;
     kp.pipelined = 0;
     kp.partials_past_l2 = plan.stats.partial_floats * (int64_t)sizeof(float) >= 3 << 20;

@@ -124,6 +124,11 @@ struct PlanOptions {
     int32_t kv_elem_bytes = 2;  // bytes per K/V element in the pool: 2 (bf16 pages) or 1 (FP8 E4M3 pages)
 };
 
+// Whether a launch of the mixed kernel has a workgroup for every entry of its list; and the whole-workgroup tiles in the order of the
+// workgroups that take them: tile order[b] is workgroup b's.
+bool has_workgroup_per_entry(const Plan& plan);
+void order_by_block(const Plan& plan, std::vector<int32_t>* order);
+
 // Returns PPD_OK or an error code with a message in `err` (may be null).
 ppd_status validate_shape(const ppd_shape* s, const char** err);
 ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, int32_t B, const PlanOptions& o,
@@ -147,7 +152,8 @@ struct KParams {
     int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (long_tiles_on_four_waves), which leaves split ranges to ppd_merge_kernel
     int32_t pipelined;       // ppd_pipelined_kernel, which has at least as many slots as workgroups and no one-wave tiles
     int32_t wave_unit;       // not 0: ppd_wave_kernel, which takes the tiles in units of this many (1, 2, 4 or 8)
-    int32_t n_wg;         // ppd_narrow_kernel: whole-workgroup tiles, at the front of the work list
+    int32_t n_wg;         // whole-workgroup tiles, at the front of the work list
+    int32_t by_block;     // ppd_mixed_kernel: a workgroup for every entry, the work list in their order (order_by_block)
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed
     int32_t partials_past_l2;  // ppd_narrow_kernel: see store_partial
     int32_t n_items;

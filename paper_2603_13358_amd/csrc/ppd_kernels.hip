@@ -1347,31 +1347,6 @@ __device__ __forceinline__ void rearm_cursors(const KParams& P, int q0, int q1, 
     }
 }
 
-// The entry of a launch whose workgroups are as many as its entries (tiles, wave tiles kWaves to an entry): the index of
-// this workgroup's tile in the work list, or -1 when there are more entries than workgroups.  A claim costs such a launch
-// ~4 us of ~13: the first one, the one that finds the queues empty, and the re-arming of the cursors.  Workgroups go
-// round the XCDs in turn, so workgroup b takes from the queue of XCD b % 8 first (row blocks that read the same K/V then
-// share an L2 as they do when they are claimed); workgroups whose queue is too short take, in order, what the
-// longer queues and the narrow tiles have left.  Small steps of 4 layers: 233 -> 218, 59.3 -> 55.3 us.
-__device__ __forceinline__ int own_entry(const KParams& P) {
-    const int n_wave = P.queue_begin[kQueues] - P.queue_begin[kWaveQueue];
-    const int entries = P.queue_begin[kWaveQueue] + (n_wave + kWaves - 1) / kWaves;
-    const int grid = (int)gridDim.x, q = (int)blockIdx.x % kXcds, pos = (int)blockIdx.x / kXcds;
-    if (grid < entries) return -1;
-    auto length = [&](int x) { return P.queue_begin[x + 1] - P.queue_begin[x]; };
-    auto takers = [&](int x) { return (grid - x + kXcds - 1) / kXcds; };  // workgroups of XCD x
-    if (pos < length(q)) return P.queue_begin[q] + pos;
-    int rank = pos - length(q);  // among the workgroups whose queue is too short
-    for (int x = 0; x < q; ++x) rank += takers(x) > length(x) ? takers(x) - length(x) : 0;
-    for (int x = 0; x < kXcds; ++x) {
-        const int left = length(x) > takers(x) ? length(x) - takers(x) : 0;
-        if (rank < left) return P.queue_begin[x] + takers(x) + rank;
-        rank -= left;
-    }
-    const int n_narrow = length(kNarrowQueue);
-    return rank < n_narrow ? P.queue_begin[kNarrowQueue] + rank : P.queue_begin[kWaveQueue] + (rank - n_narrow) * kWaves;
-}
-
 template <int HD, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P) {
     // Dynamic LDS: rings of kStages + 1 stages of 4 pages of K and as many of V, then the page ids of a tile's key
@@ -1409,9 +1384,11 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
     // others are, instead of one failing atomic (a round trip to the L2 each, one after the other) per queue --
     // that chain used to be the last ~10 us of every workgroup, and so of every launch.
     unsigned dry = 0;
+    if (!P.by_block) {
 #pragma unroll
-    for (int q = 0; q < kQueues; ++q)
-        if (P.queue_begin[q + 1] == P.queue_begin[q]) dry |= 1u << q;
+        for (int q = 0; q < kQueues; ++q)
+            if (P.queue_begin[q + 1] == P.queue_begin[q]) dry |= 1u << q;
+    }
     constexpr unsigned kAllDry = (1u << kQueues) - 1;
     auto look_at_cursors = [&]() {
         unsigned cur[kQueues];
@@ -1422,7 +1399,12 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
         for (int q = 0; q < kQueues; ++q)
             if ((int)(cur[q] * (q == kWaveQueue ? kWaves : 1)) >= P.queue_begin[q + 1] - P.queue_begin[q]) dry |= 1u << q;
     };
-    const int own = own_entry(P);  // a launch with a workgroup for every tile claims nothing
+    // A launch with a workgroup for every entry (a tile, or kWaves one-wave tiles) claims nothing: its list is in the order of the
+    // workgroups, the one-wave tiles behind the others.  A claim costs such a launch ~4 us of ~13: the first one, the one that finds the
+    // queues empty, and the re-arming of the cursors (small steps of 4 layers 233 -> 218, 59.3 -> 55.3 us); and with the order in the list
+    // the first read from memory is the work item, where the queues' bounds and a search in them came before it (steps of 8, 80 and 48 tiles 9.14 -> 8.57, 25.2 -> 23.4 and 12.1 -> 11.5 us).
+    const int block = (int)blockIdx.x;
+    const int own = !P.by_block ? -1 : block < P.n_wg ? block : P.n_wg + (block - P.n_wg) * kWaves;
     for (;;) {
         if (own < 0 && tid == 0) {
             int idx = -1;
@@ -1460,10 +1442,10 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
             __syncthreads();  // everyone has read s_next, and the previous tile's LDS use is over
         }
         if (idx < 0) break;
-        if (idx >= P.queue_begin[kWaveQueue]) {
+        if (idx >= P.n_wg) {
             // a claim on the wave-tile queue: wave w runs tile idx + w on its own
             const int mine = idx + __builtin_amdgcn_readfirstlane(tid >> 6);
-            if (mine < P.queue_begin[kQueues]) {
+            if (mine < P.n_items) {
                 const ppd_work_item it = P.items[mine];
                 if constexpr (FP8) narrow_item_wide<HD, 1, fp8_sets(HD), true, true>(P, it, smem);
                 else narrow_item<HD, 1, mixed_sets(HD), mixed_sets(HD), true>(P, it, smem);

@@ -574,6 +574,29 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     return PPD_OK;
 }
 
+bool has_workgroup_per_entry(const Plan& plan) {
+    const int64_t n_wg = plan.queue_begin[kWaveQueue], n_wave = plan.queue_begin[kQueues] - n_wg;
+    return n_wg + (n_wave + kWaves - 1) / kWaves <= plan.stats.grid;
+}
+
+// Workgroups go round the XCDs in turn, so workgroup b takes from the queue of XCD b % 8 first (row blocks that read the same K/V then
+// share an L2 as they do when they are claimed); workgroups whose queue is too short take, in order, what the longer queues have
+// left, and then the narrow tiles.
+void order_by_block(const Plan& plan, std::vector<int32_t>* order) {
+    const int n_wg = plan.queue_begin[kWaveQueue];
+    order->assign((size_t)n_wg, -1);
+    std::vector<int32_t> left;
+    for (int q = 0; q < kXcds; ++q)
+        for (int i = plan.queue_begin[q], b = q; i < plan.queue_begin[q + 1]; ++i, b += kXcds) {
+            if (b < n_wg) (*order)[b] = i;
+            else left.push_back(i);
+        }
+    for (int i = plan.queue_begin[kNarrowQueue]; i < n_wg; ++i) left.push_back(i);
+    size_t next = 0;
+    for (auto& o : *order)
+        if (o < 0) o = left[next++];
+}
+
 }  // namespace ppd
 
 extern "C" ppd_status ppd_plan_build(const ppd_shape* shape, const int32_t* L, const int32_t* n, int32_t B,
