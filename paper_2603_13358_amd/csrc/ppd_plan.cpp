@@ -292,18 +292,21 @@ static bool tiles_pipelined(const Plan& plan, int head_dim, int elem_bytes) {
 // 64-700 keys 0.83, FP8 pages 0.63) and 2 % more at worst; taking the faster one each time would gain 0.1 % more over all of them.
 // Split ranges stay on whole workgroups, which merge them, and so do more tiles than one round of the chip's waves and fewer than two:
 // the units of the second round come on top of evenly loaded compute units there (300 sequences of 64-700 keys 83 us
-// where 467 MB need 70), and whole workgroups give the mixed kernel's results bit for bit.  Below two and a half tiles for each compute unit (520 launches of 257-640 tiles) it is slower on average and not taken, and where
+// where 467 MB need 70), and whole workgroups give the mixed kernel's results bit for bit.  Below two and a half tiles for each compute unit it is slower on average on bf16 pages and not taken, and where
 // the list has every tile on single waves as it is (at most 384 keys each, and 1536 of them) the two differ by -18 to +27 %: that form stays.
 // Units of two where there are fewer than six tiles for each compute unit: more units have work then (640-1100 tiles 1.3 % less time).
+// On FP8 pages, where a whole workgroup loses more between its tiles, from the second round on, in units of one and where
+// 10 % less has to come out: of 247 drawn launches of 257-640 tiles 57 take it, for 28 % less time on average and 1.4 % more at worst (bf16 pages of that many run in ppd_pipelined_kernel).
 // By the device's workgroups, not by a grid override: the forms round differently, and that option stays scheduling only.
 static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int64_t n = plan.queue_begin[kQueues], n_wg = plan.queue_begin[kWaveQueue];
-    if (2 * n < 5 * wgs || (n > kWaves * wgs && n < 2 * kWaves * wgs) || n_wg == 0 || !plan.groups.empty()) return 0;
     const bool fp8 = elem_bytes == 1;
+    if (fp8 ? n <= wgs : 2 * n < 5 * wgs) return 0;
+    if ((n > kWaves * wgs && n < 2 * kWaves * wgs) || n_wg == 0 || !plan.groups.empty()) return 0;
     const double key_bytes = 2.0 * head_dim * elem_bytes;
     constexpr double kHbm = 6.7e6, kUnit = 40e3;  // bytes per us
     const double wave_rate = fp8 ? (head_dim == 64 ? 5e3 : 8e3) : (head_dim == 64 ? 6e3 : 12e3);
-    const int64_t unit = n >= 6 * wgs ? 4 : 2, groups = kWaves / unit;
+    const int64_t unit = n >= 6 * wgs ? 4 : 2 * n >= 5 * wgs ? 2 : 1, groups = kWaves / unit;
     std::vector<double> units((size_t)wgs, 0.0), chains((size_t)(wgs * groups), 0.0);
     double bytes = 0;
     for (int64_t u = 0; u * unit < n; ++u) {  // as ppd_wave_kernel deals them
@@ -326,7 +329,7 @@ static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int e
     const double on_waves = std::max(flow(units, kUnit, 1), flow(chains, wave_rate, unit)) + (fp8 ? 6.0 : 4.0);
     const double rounds = ((double)n_wg + (double)(n - n_wg) / kWaves) / (double)wgs;
     const double on_workgroups = 6.0 + (fp8 ? 3.3 : 2.15) * rounds + bytes / 7.2e6;
-    return on_waves < 0.96 * on_workgroups ? (int32_t)unit : 0;
+    return on_waves < (unit == 1 ? 0.90 : 0.96) * on_workgroups ? (int32_t)unit : 0;
 }
 
 ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, int32_t B, const PlanOptions& o,

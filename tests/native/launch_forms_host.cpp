@@ -164,7 +164,8 @@ static void on_waves() {
     };
     for (bool fp8 : {false, true}) {
         for (int D : {64, 128}) {
-            CHECK(unit(lengths(79, 100), D, fp8) == 0 && unit(lengths(80, 100), D, fp8) == 2);
+            CHECK(unit(lengths(79, 100), D, fp8) == (fp8 ? 1 : 0) && unit(lengths(80, 100), D, fp8) == 2);
+            CHECK(unit(lengths(32, 100), D, fp8) == 0 && unit(lengths(33, 70), D, fp8) == (fp8 ? 1 : 0) && unit(lengths(33, 700), D, fp8) == 0);
             CHECK(unit(lengths(191, 100), D, fp8) == 2 && unit(lengths(192, 100), D, fp8) == 0);         // all in the list of one-wave tiles
             CHECK(unit(lengths(192, 100, 16, 400), D, fp8) == 4);                                          // not all
             CHECK(unit(lengths(192, 100, 16, 400), D, fp8, 0, 7) == 4 && unit(lengths(192, 100, 16, 400), D, fp8, 0, 4096) == 4);

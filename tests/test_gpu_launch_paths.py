@@ -479,14 +479,14 @@ def test_decode_only_kernel_on_fp8_pages_of_head_size_64(L, options):
 
 @pytest.mark.parametrize("B,Hkv,D,n_long,options", [(80, 8, 128, 0, {}), (83, 8, 64, 0, {"grid": 7}), (161, 4, 128, 0, {}),
                                                     (200, 8, 128, 25, {"grid": 4096}), (230, 7, 64, 30, {}), (256, 8, 128, 251, {}),
-                                                    (520, 8, 64, 500, {})])
+                                                    (520, 8, 64, 500, {}), (40, 8, 128, 0, {}), (67, 8, 64, 0, {"grid": 300})])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_decode_tiles_on_single_waves(B, Hkv, D, n_long, options, fp8):
-    """Launches of 640 short tiles and more, a wave to a tile: pages, and units of tiles, that are not full, one to three rounds of
+    """Launches of 640 short tiles and more (FP8 pages: of more than 256), a wave to a tile: pages, and units of tiles, that are not full, one to three rounds of
     the waves, multi-row tiles, infinite V.  The oracle's result, the same whatever the grid, and with less error than on whole
     workgroups (one bf16 rounding less: 0.71 of it where the results are averages over many keys)."""
     rng = np.random.default_rng(B + D)
-    L = rng.integers(70, 140, B)
+    L = rng.integers(70, 140, B) if B * Hkv >= 640 else rng.integers(60, 90, B)
     L[B - n_long:] = rng.integers(384, 420, n_long)
     L[1:5] = [0, 15, 16, 17]
     n = np.where(np.arange(B) % 9 == 8, 2, 1)
@@ -500,14 +500,14 @@ def test_decode_tiles_on_single_waves(B, Hkv, D, n_long, options, fp8):
         else:
             _, out, stats = gpu_step(b, options=dict(options, **extra))
             want = oracle_out(b)
-        assert stats["n_narrow"] >= 640 and stats["n_mfma"] == 0
+        assert stats["n_narrow"] > 256 and stats["n_mfma"] == 0
         got, finite = bits_to_f32(out), np.isfinite(want)
         assert np.array_equal(got[~finite], want[~finite]) and finite[1:].all() and finite[0].any() == fp8
         check_close(got[1:], want[1:])
         errors.append(np.linalg.norm(got[5:].astype(np.float64) - want[5:]))
         outs.append(out)
     assert np.array_equal(outs[0], outs[1])
-    assert errors[0] <= 0.875 * errors[2], errors
+    assert errors[0] <= (0.875 if fp8 or B * Hkv >= 640 else 1) * errors[2], errors
 
 
 @pytest.mark.parametrize("B,Hkv,D,grid", [(33, 8, 128, 0), (70, 8, 128, 0), (37, 2, 128, 8), (49, 1, 128, 16), (48, 1, 64, 16), (23, 3, 64, 5), (130, 1, 128, 3)])
