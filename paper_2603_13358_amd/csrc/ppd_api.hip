@@ -329,8 +329,9 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         }
         void* host = sg.host;
         std::memcpy(host, plan.items.data(), items_bytes);
-        ctx->plan_by_block = ctx->launch_mode == 0 && plan.stats.n_mfma > 0 && ppd::has_workgroup_per_entry(plan);
-        if (ctx->plan_by_block) {
+        const bool one_kernel = ctx->launch_mode == 0 || (ctx->launch_mode == 1 && (plan.stats.n_narrow == 0 || plan.stats.n_mfma == 0));
+        ctx->plan_by_block = one_kernel && ppd::has_workgroup_per_entry(plan);
+        if (ctx->plan_by_block && plan.stats.n_mfma > 0) {  // (narrow tiles alone are in that order)
             ppd::order_by_block(plan, &ctx->block_order);
             for (size_t b = 0; b < ctx->block_order.size(); ++b) static_cast<ppd_work_item*>(host)[b] = plan.items[ctx->block_order[b]];
         }

@@ -1,4 +1,4 @@
-// Host-only checks of how a decode-only step is launched (built and run by tests/test_launch_forms.py): ppd_api.hip as it
+// Host-only checks of how a step is launched (built and run by tests/test_launch_forms.py): ppd_api.hip as it
 // is, compiled against the stand-in runtime of host_runtime/, whose launches are recorded instead of run.
 #include <hip/hip_runtime.h>
 
@@ -24,7 +24,11 @@ std::function<void()> sim_bind(const void* f, void** args) {
 
 namespace ppd {
 int prepare_mixed_kernels() { return 0; }
-int launch_mixed(const KParams&, int, int, void*, bool) { std::abort(); }
+int launch_mixed(const KParams& p, int, int grid, void*, bool) {
+    g_params = p;
+    g_grid = grid;
+    return 0;
+}
 int launch_narrow(const KParams& p, int, int grid, void*, bool) {
     g_params = p;
     g_grid = grid;
@@ -193,6 +197,50 @@ static void pipelined() {
     CHECK(!runs(lengths(64, 5000)) && !runs(lengths(256, 100)) && !runs(lengths(256, 440)));
 }
 
+// The list of a launch of the mixed kernel with a workgroup for every entry is in the order of its workgroups: every tile once, workgroup b
+// with tile b / 8 of the queue of XCD b % 8 while that has one, the one-wave tiles behind the others.
+static void by_block() {
+    alignas(16) static char device[16];
+    std::mt19937 rng(2);
+    int in_order = 0, claimed = 0;
+    for (int trial = 0; trial < 300; ++trial) {
+        const int hkv = 1 << (rng() % 4), mode = rng() % 3 ? 0 : 1;
+        const ppd_shape s = {4 * hkv, hkv, 128, 16, 1 << 20};
+        ppd_ctx* ctx = nullptr;
+        CHECK(ppd_create(&s, 0, &ctx) == PPD_OK);
+        CHECK(ppd_set_option(ctx, "launch_mode", mode) == PPD_OK && ppd_set_option(ctx, "narrow_kernel", 0) == PPD_OK);
+        const int kinds = mode == 0 ? rng() % 3 : rng() % 2;  // decodes, turns, both (which launch_mode 1 runs as two kernels)
+        std::vector<int32_t> L, n;
+        for (int i = 1 + rng() % (1 << (rng() % 7)); i > 0; --i) {
+            const bool turn = kinds == 1 || (kinds == 2 && rng() % 2);
+            L.push_back((int32_t)(rng() % 3000));
+            n.push_back(turn ? 64 + (int32_t)(rng() % 300) : 1);
+        }
+        CHECK(ppd_mixed_attention(ctx, device, device, reinterpret_cast<const int32_t*>(device), 1 << 16, L.data(), n.data(), (int32_t)L.size(), 1.f, device, nullptr) == PPD_OK);
+        sim.null_stream.run();
+        const ppd::Plan& plan = ctx->plan;
+        const ppd_work_item* const list = g_params.items;
+        const int n_wg = plan.queue_begin[ppd::kWaveQueue], n_items = plan.queue_begin[ppd::kQueues];
+        const bool enough = n_wg + (n_items - n_wg + ppd::kWaves - 1) / ppd::kWaves <= g_grid;
+        CHECK((g_params.by_block != 0) == enough && g_params.n_wg == n_wg && g_params.n_items == n_items);
+        std::vector<int> times((size_t)n_items, 0);
+        for (int b = 0; b < n_items; ++b) {
+            int i = 0;
+            while (i < n_items && (times[i] || std::memcmp(&plan.items[i], &list[b], sizeof(ppd_work_item)) != 0)) ++i;
+            CHECK(i < n_items);
+            times[i] = 1;
+            const int q = b % ppd::kXcds, at = plan.queue_begin[q] + b / ppd::kXcds;
+            if (!enough || b >= n_wg) CHECK(i == b);
+            else if (at < plan.queue_begin[q + 1]) CHECK(i == at);
+        }
+        in_order += enough && plan.stats.n_mfma > 0;
+        claimed += !enough;
+        ppd_destroy(ctx);
+    }
+    std::printf("in the workgroups' order %d, claimed %d\n", in_order, claimed);
+    CHECK(in_order > 30 && claimed > 30);
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "merged_once") merged_once();
@@ -200,6 +248,7 @@ int main(int argc, char** argv) {
     else if (what == "second_round") second_round();
     else if (what == "on_waves") on_waves();
     else if (what == "pipelined") pipelined();
+    else if (what == "by_block") by_block();
     else return 2;
     std::printf("ok\n");
     return 0;
