@@ -18,7 +18,7 @@
  *  - q, out, k, v and every page pool must start on a 16-byte boundary (the kernels move 16 bytes per lane);
  *    slot_mapping on an 8-byte, page_tables on a 4-byte boundary.  Anything else is PPD_ERR_RANGE.
  *  - bf16 = the upper 16 bits of an IEEE binary32.  Arithmetic: bf16 inputs, fp32 accumulation and
- *    softmax, probabilities rounded to bf16 before the PV product (one form of the decode-only kernel enters each
+ *    softmax, probabilities rounded to bf16 before the PV product (two forms of decode-only launches enter each
  *    as two bf16 numbers, with less error: option "narrow_kernel" below), bf16 output (round to nearest even).
  *  - A visible V element that is infinite makes its output column infinite, and NaN where infinities of both signs
  *    meet or the element's probability is zero; NaN stays NaN.
@@ -140,8 +140,10 @@ const char *ppd_last_error(const ppd_ctx *ctx);
  * The results with "narrow_kernel" 0 and 1 are bit-identical, except where the decode-only kernel runs its tiles on four
  * waves: head_dim 128, bf16 pages, a multiple of 8 KV heads, no one-wave tiles, at least two tiles per compute unit, 3072 keys
  * or more per tile on average, and the last round of tiles nearly full (70 % of the units) or short (its longest tile at
- * most a seventh of a unit's mean load).  There the results have less error (probabilities as two bf16 numbers, four partial
- * softmaxes per tile instead of eight), and so a row's rounding depends on the rest of its batch, as it does with the
+ * most a seventh of a unit's mean load) -- and where it runs every tile on one wave: "wave_tiles" -1, no split ranges, at least
+ * 2.5 tiles per compute unit (FP8 pages: more than one), not between one and two tiles per wave of the chip, and estimated to be
+ * faster by the tiles' lengths.  In both the results have less error (probabilities as two bf16 numbers; four partial
+ * softmaxes per tile, or one, instead of eight), and so a row's rounding depends on the rest of its batch, as it does with the
  * automatic split sizes.  "grid" changes which workgroup runs what, not the results, as long as "narrow_chunk" and
  * "mfma_chunk" are set. */
 ppd_status ppd_set_option(ppd_ctx *ctx, const char *key, int64_t value);
