@@ -3,10 +3,25 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
+#include <cstdlib>
+#include <new>
 #include <random>
 #include <vector>
 
 #include "../../paper_2603_13358_amd/csrc/ppd_api.hip"
+
+static size_t g_allocations = 0;
+void* operator new(size_t bytes) {
+    ++g_allocations;
+    if (void* p = std::malloc(bytes ? bytes : 1)) return p;
+    throw std::bad_alloc();
+}
+void* operator new(size_t bytes, const std::nothrow_t&) noexcept {
+    ++g_allocations;
+    return std::malloc(bytes ? bytes : 1);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 static ppd::KParams g_params;
 static int g_grid = 0, g_merges = 0;
@@ -184,6 +199,37 @@ static void on_waves() {
     CHECK(unit(lengths(256, 3500)) == 0 && unit(lengths(64, 2000)) == 0);
 }
 
+// Where no order could make single waves win, the planner finds that out without laying the tiles out on the waves: the plan takes the memory
+// of one that must not ask ("wave_tiles" 0; no tile here is in the list of one-wave tiles).
+static void estimate() {
+    auto allocations = [&](const std::vector<int32_t>& L, int D, int elem_bytes, int32_t wave_tiles, int32_t* unit) {
+        const ppd_shape s = {64, 8, D, 16, 1 << 20};
+        const std::vector<int32_t> n(L.size(), 1);
+        ppd::PlanOptions o;
+        o.kv_elem_bytes = elem_bytes;
+        o.wave_tiles = wave_tiles;
+        ppd::Plan plan;
+        for (int call = 0; call < 2; ++call) {  // the second one finds the plan's own tables allocated
+            g_allocations = 0;
+            CHECK(ppd::build_plan(s, L.data(), n.data(), (int32_t)L.size(), o, &plan, nullptr) == PPD_OK);
+        }
+        *unit = plan.wave_unit;
+        return g_allocations;
+    };
+    auto asks = [&](const std::vector<int32_t>& L, int D, int elem_bytes) {
+        int32_t unit, never;
+        const size_t with = allocations(L, D, elem_bytes, -1, &unit), without = allocations(L, D, elem_bytes, 0, &never);
+        CHECK(never == 0 && with >= without && (unit == 0 || with > without));
+        return with > without;
+    };
+    std::mt19937 rng(3);
+    std::vector<int32_t> spread(64);
+    for (auto& l : spread) l = 64 + (int32_t)(rng() % 637);
+    for (int D : {64, 128}) CHECK(!asks(spread, D, 1) && !asks(lengths(64, 5000), D, 1) && !asks(lengths(79, 3000, 1, 20000), D, 1));
+    CHECK(!asks(lengths(36, 300), 128, 1) && !asks(lengths(100, 400, 1, 6000), 128, 2) && !asks(lengths(200, 4000), 128, 2));
+    CHECK(asks(lengths(33, 70), 128, 1) && asks(lengths(80, 100), 128, 2));
+}
+
 // More tiles than workgroups run pipelined where they are short and of a length, on bf16 pages and whole workgroups.
 static void pipelined() {
     auto runs = [&](const std::vector<int32_t>& keys, int D = 128, bool fp8 = false, int64_t grid = 0, int hkv = 8) {
@@ -247,6 +293,7 @@ int main(int argc, char** argv) {
     else if (what == "four_waves") four_waves();
     else if (what == "second_round") second_round();
     else if (what == "on_waves") on_waves();
+    else if (what == "estimate") estimate();
     else if (what == "pipelined") pipelined();
     else if (what == "by_block") by_block();
     else return 2;
