@@ -1692,13 +1692,16 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_pipelined_kernel(const ppd_wo
         if (claims && tid == 0) claim = atomicAdd(&P.counters[kCursorBase + kNarrowQueue * kCursorStride], 1u);
     };
 
-    Tile cur = tile_of(block), nxt = tile_of(2 * grid - 1 - block), far = tile_of(2 * grid + block);
+    // The first tile's pages before anything of the tiles behind it.  With the reads of those in front, a launch whose longest tiles have a
+    // workgroup to themselves took longer than one tile after the other does: 280 tiles of 37-485 keys 10.6 us against 10.2, 10.05 this way.
+    Tile cur = tile_of(block);
     int ids_cur = ids_of(cur);
     Queries q_cur = queries_of(cur);
+    begin(cur, ids_cur);
+    Tile nxt = tile_of(2 * grid - 1 - block), far = tile_of(2 * grid + block);
     int ids_nxt = ids_of(nxt);
     Queries q_nxt = queries_of(nxt);
     draw();
-    begin(cur, ids_cur);
     for (int parity = 0;; parity ^= 1) {
         const int ncols = cur.it.nrows * G, limit = cur.it.L + cur.it.row0 + column(cur).jrow;
         bf16x8 qreg[KS];
