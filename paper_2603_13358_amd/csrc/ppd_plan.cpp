@@ -270,13 +270,17 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
 // one after the other (mean keys at D = 128, longest by mean): up to 300, up to 1.7 -13 %; up to 300, 1.7-3 -8; 300-600, up to 1.7 -3; 600-900 -2;
 // 900-2500 +1; 300-900, 1.7-2.2 +0.5; above 3 +11.  At D = 64 up to 300, 3.0 -8 %; 300-900, 1.7 -9; 900-1300 -7; above 3 +8.
 // 320 KiB are 625 keys at D = 128 and 1250 at D = 64.
-static bool tiles_pipelined(const Plan& plan, int head_dim, int elem_bytes) {
+// In more than two rounds a workgroup's first three tiles go by index, the longest ones with two more behind them: not where the longest
+// is 1.2 times what a workgroup reads on average.  Of 283 drawn launches of more than two rounds, 6 beyond it 0.98 of the time on
+// average and 1.06 at worst (560 tiles around 298 keys, one sequence of 845, 21.1 -> 22.4 us), the others 0.85 and 1.005.
+static bool tiles_pipelined(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int64_t n = plan.queue_begin[kQueues];
     if (elem_bytes != 2 || n == 0 || plan.queue_begin[kWaveQueue] != n) return false;
     int64_t sum = 0;
     for (int64_t i = 0; i < n; ++i) sum += plan.items[i].kv_end - plan.items[i].kv_begin;
     const int64_t longest = plan.items[0].kv_end - plan.items[0].kv_begin, mean_bytes = sum / n * 2 * head_dim * elem_bytes;
     static_assert(kMaxPipelinedKeys >= 3 * (320 << 10) / (2 * 64 * 2), "a wave's share of the longest tile fits its page ids");
+    if (n > 2 * wgs && 5 * longest * wgs > 6 * sum) return false;
     return mean_bytes <= 320 << 10 && longest * n * 10 <= sum * (mean_bytes <= 150 << 10 ? 30 : 17);
 }
 
@@ -575,7 +579,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     plan->four_waves = n_mfma == 0 && long_tiles_on_four_waves(*plan, kWgPerCu * o.num_cus, D, Hkv, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->wave_unit = n_mfma == 0 && !plan->four_waves && o.wave_tiles < 0 && o.force_kind != 1
                           ? tiles_on_waves(*plan, kWgPerCu * o.num_cus, D, o.kv_elem_bytes == 1 ? 1 : 2) : 0;
-    plan->pipelined = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && tiles_pipelined(*plan, D, o.kv_elem_bytes == 1 ? 1 : 2);
+    plan->pipelined = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && tiles_pipelined(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->by_index = n_mfma == 0 && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }

@@ -240,6 +240,7 @@ static void pipelined() {
     CHECK(!runs(lengths(32, 200)) && runs(lengths(33, 200)) && runs(lengths(79, 200)) && runs(lengths(20, 200), 128, false, 100));
     CHECK(!runs(lengths(33, 200), 128, true) && runs(lengths(33, 640)) && !runs(lengths(33, 641)) && runs(lengths(33, 1280), 64) && !runs(lengths(33, 1281), 64));
     CHECK(runs(lengths(40, 400, 4, 700)) && !runs(lengths(40, 400, 4, 800)) && runs(lengths(40, 200, 4, 600)) && !runs(lengths(40, 200, 4, 800)));
+    CHECK(runs(lengths(64, 200, 1, 590)) && runs(lengths(65, 200, 1, 490)) && !runs(lengths(65, 200, 1, 500)));  // a long tile and two more behind it
     CHECK(!runs(lengths(64, 5000)) && !runs(lengths(256, 100)) && !runs(lengths(256, 440)));
 }
 
