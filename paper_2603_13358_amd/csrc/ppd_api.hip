@@ -57,10 +57,7 @@ struct ppd_ctx {
     // engine step call with the same lengths): such calls skip planning and upload
     std::vector<int32_t> plan_L, plan_n;
     ppd::PlanOptions plan_opts;
-    int plan_launch_mode = 0;
     bool plan_on_device = false;
-    // the mixed kernel's list is in the order of its workgroups, one for each entry
-    bool plan_by_block = false;
     std::vector<int32_t> block_order;
     // where that plan lives: 1 = the context's own workspace, 2 = the library's static scratch array
     int plan_where = 0;
@@ -257,7 +254,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     if (ctx->launch_mode != 0) opts.wave_tiles = 0;  // the specialised kernels run every narrow tile on four waves
     opts.kv_elem_bytes = ctx->fp8_pages ? 1 : 2;
     const bool same_opts = std::memcmp(&ctx->plan_opts, &opts, sizeof(ppd::PlanOptions)) == 0;
-    const bool reuse = ctx->plan_on_device && ctx->plan_where == where && same_opts && ctx->plan_launch_mode == ctx->launch_mode &&
+    const bool reuse = ctx->plan_on_device && ctx->plan_where == where && same_opts &&
                        (!use_static || g_scratch_owner[ctx->device] == ctx) && (int32_t)ctx->plan_L.size() == B &&
                        std::memcmp(ctx->plan_L.data(), L, sizeof(int32_t) * B) == 0 &&
                        std::memcmp(ctx->plan_n.data(), n, sizeof(int32_t) * B) == 0;
@@ -279,7 +276,18 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     }
 
     const ppd::Plan& plan = ctx->plan;
-    const size_t items_bytes = plan.items.size() * sizeof(ppd_work_item);
+    const size_t n_wg = (size_t)plan.queue_begin[ppd::kWaveQueue];
+    const size_t tables_bytes = plan.groups.size() * sizeof(ppd::MergeGroup) + plan.units.size() * sizeof(ppd::MergeUnit) + sizeof plan.queue_begin;
+    // The mixed kernel with a workgroup for every entry reads the whole-workgroup tiles in the order of the workgroups.  Where that is not
+    // the queues' order (narrow tiles alone are in it) they are uploaded in both, the one-wave tiles behind the second: the two kernels of
+    // the other launch modes claim from the queues, and a plan serves every mode.  A list that has no room for both is claimed.
+    bool by_block = ppd::has_workgroup_per_entry(plan);
+    size_t second_order = by_block && plan.stats.n_mfma > 0 ? n_wg : 0;
+    if (use_static && ((plan.items.size() + second_order) * sizeof(ppd_work_item) + tables_bytes + 15) / 16 * 16 > kStaticPlanBytes) {
+        by_block = false;
+        second_order = 0;
+    }
+    const size_t items_bytes = (plan.items.size() + second_order) * sizeof(ppd_work_item);
     const size_t groups_bytes = plan.groups.size() * sizeof(ppd::MergeGroup);
     const size_t units_bytes = plan.units.size() * sizeof(ppd::MergeUnit);
     const size_t bounds_bytes = sizeof plan.queue_begin;  // the queues' bounds travel behind the tables
@@ -328,13 +336,13 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
             }
         }
         void* host = sg.host;
-        std::memcpy(host, plan.items.data(), items_bytes);
-        const bool one_kernel = ctx->launch_mode == 0 || (ctx->launch_mode == 1 && (plan.stats.n_narrow == 0 || plan.stats.n_mfma == 0));
-        ctx->plan_by_block = one_kernel && ppd::has_workgroup_per_entry(plan);
-        if (ctx->plan_by_block && plan.stats.n_mfma > 0) {  // (narrow tiles alone are in that order)
+        ppd_work_item* const list = static_cast<ppd_work_item*>(host);
+        std::copy(plan.items.begin(), plan.items.begin() + n_wg, list);
+        if (second_order > 0) {
             ppd::order_by_block(plan, &ctx->block_order);
-            for (size_t b = 0; b < ctx->block_order.size(); ++b) static_cast<ppd_work_item*>(host)[b] = plan.items[ctx->block_order[b]];
+            for (size_t b = 0; b < n_wg; ++b) list[n_wg + b] = plan.items[ctx->block_order[b]];
         }
+        std::copy(plan.items.begin() + n_wg, plan.items.end(), list + n_wg + second_order);
         if (groups_bytes) {
             std::memcpy(static_cast<char*>(host) + items_bytes, plan.groups.data(), groups_bytes);
             std::memcpy(static_cast<char*>(host) + items_bytes + groups_bytes, plan.units.data(), units_bytes);
@@ -359,7 +367,6 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         ctx->plan_L.assign(L, L + B);
         ctx->plan_n.assign(n, n + B);
         ctx->plan_opts = opts;
-        ctx->plan_launch_mode = ctx->launch_mode;
         ctx->plan_on_device = true;
         ctx->plan_where = where;
         ctx->plan.stats.plan_host_us = (int32_t)std::chrono::duration_cast<std::chrono::microseconds>(
@@ -390,11 +397,11 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
     kp.n_items = (int32_t)plan.items.size();
     kp.mean_tile_keys = plan.stats.kv_bytes_tiles / (2LL * ctx->shape.head_dim * (ctx->fp8_pages ? 1 : 2)) / plan.stats.n_items;
     kp.queue_begin = reinterpret_cast<const int32_t*>(static_cast<const char*>(d_plan) + total - bounds_bytes);
-    kp.n_wg = plan.queue_begin[ppd::kWaveQueue];
+    kp.n_wg = (int32_t)n_wg;
     kp.pace_keys = kp.mean_tile_keys;
     kp.four_waves = 0;
     kp.by_index = 0;
-    kp.by_block = ctx->plan_by_block;
+    kp.by_block = 0;
     kp.wave_unit = 0;
     kp.pipelined = 0;
     kp.partials_past_l2 = plan.stats.partial_floats * (int64_t)sizeof(float) >= 3 << 20;
@@ -451,6 +458,8 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         rc = ppd::launch_narrow(kp, D, (int)std::max<int64_t>(1, std::min<int64_t>(wgs, places)), stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch narrow-tile kernel");
     } else if (mode == 0 || (mode == 1 && !(has_narrow && has_mfma))) {
+        kp.by_block = by_block;
+        if (by_block) kp.items += second_order;
         rc = ppd::launch_mixed(kp, D, plan.stats.grid, stream, ctx->fp8_pages);
         if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "launch mixed attention");
     } else {

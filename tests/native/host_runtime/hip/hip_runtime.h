@@ -72,6 +72,7 @@ struct Sim {
     hipError_t pending = hipSuccess;      // what hipGetLastError reports next
     hipError_t launch_status = hipSuccess;  // status of the next launches; a launch that fails enqueues nothing
     int device_syncs = 0, num_cus = 256;
+    bool capturing = false;               // what every stream says of itself
     SimStream* of(hipStream_t s) { return s ? s : &null_stream; }
 };
 inline Sim sim;
@@ -125,7 +126,10 @@ inline hipError_t hipGetSymbolAddress(void** p, T* symbol) { *p = symbol; return
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = new SimStream; return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t s) { delete s; return hipSuccess; }
 inline hipError_t hipStreamSynchronize(hipStream_t s) { sim.of(s)->run(); return hipSuccess; }
-inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) { *c = hipStreamCaptureStatusNone; return hipSuccess; }
+inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
+    *c = sim.capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 inline hipError_t hipDeviceSynchronize() { ++sim.device_syncs; sim.null_stream.run(); return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t* e) { *e = new SimEvent; return hipSuccess; }

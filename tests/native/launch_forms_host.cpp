@@ -49,8 +49,14 @@ int launch_narrow(const KParams& p, int, int grid, void*, bool) {
     g_grid = grid;
     return 0;
 }
-int launch_mfma_only(const KParams&, int, int, void*) { std::abort(); }
-int launch_stream_only(const KParams&, int, int, void*) { std::abort(); }
+int launch_mfma_only(const KParams& p, int, int, void*) {
+    g_params = p;
+    return 0;
+}
+int launch_stream_only(const KParams& p, int, int, void*) {
+    g_params = p;
+    return 0;
+}
 int launch_merge(const MergeParams&, void*) {
     ++g_merges;
     return 0;
@@ -288,6 +294,49 @@ static void by_block() {
     CHECK(in_order > 30 && claimed > 30);
 }
 
+// A plan serves every launch mode that plans alike (here "wave_tiles" 0, which the modes of two kernels imply): a step run eagerly in one
+// mode can be captured in another, and what is launched then finds the list in its own order, the queues' or the workgroups'.
+static void modes_share_a_plan() {
+    alignas(16) static char device[16];
+    std::mt19937 rng(4);
+    int in_order = 0;
+    for (int trial = 0; trial < 200; ++trial) {
+        const ppd_shape s = {32, 8, 128, 16, 1 << 20};
+        ppd_ctx* ctx = nullptr;
+        CHECK(ppd_create(&s, 0, &ctx) == PPD_OK && ppd_set_option(ctx, "wave_tiles", 0) == PPD_OK && ppd_set_option(ctx, "grid", rng() % 4 ? 0 : 65536) == PPD_OK);
+        const int kinds = rng() % 3;  // decodes, turns, both
+        std::vector<int32_t> L, n;
+        for (int i = 1 + rng() % (1 << (rng() % 7)); i > 0; --i) {
+            const bool turn = kinds == 1 || (kinds == 2 && rng() % 2);
+            L.push_back((int32_t)(rng() % 3000));
+            n.push_back(turn ? 64 + (int32_t)(rng() % 300) : 1);
+        }
+        for (int call = 0; call < 6; ++call) {
+            const bool use_static = trial % 2 != 0;
+            const int mode = (int)(rng() % 3);
+            sim.capturing = call > 0;
+            CHECK(ppd_set_option(ctx, "launch_mode", mode) == PPD_OK);
+            auto fn = use_static ? ppd_mixed_attention_static : ppd_mixed_attention;
+            const ppd_status st = fn(ctx, device, device, reinterpret_cast<const int32_t*>(device), 1 << 16, L.data(), n.data(), (int32_t)L.size(), 1.f, device, nullptr);
+            if (call == 0 && use_static && st == PPD_ERR_WORKSPACE) break;  // (the split partials of a large grid)
+            CHECK(st == PPD_OK);
+            sim.null_stream.run();
+            const ppd::Plan& plan = ctx->plan;
+            const bool mixed = mode == 0 ? plan.stats.n_mfma > 0 : mode == 1 && (plan.stats.n_narrow == 0 || plan.stats.n_mfma == 0);
+            CHECK((g_params.by_block != 0) == (mixed && plan.stats.n_items <= plan.stats.grid));
+            std::vector<int32_t> order;
+            if (g_params.by_block) ppd::order_by_block(plan, &order);
+            for (int b = 0; b < plan.stats.n_items; ++b)
+                CHECK(std::memcmp(&g_params.items[b], &plan.items[g_params.by_block ? order[b] : b], sizeof(ppd_work_item)) == 0);
+            CHECK(std::memcmp(g_params.queue_begin, plan.queue_begin, sizeof plan.queue_begin) == 0);
+            in_order += g_params.by_block && kinds > 0;
+        }
+        sim.capturing = false;
+        ppd_destroy(ctx);
+    }
+    CHECK(in_order > 100);
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "merged_once") merged_once();
@@ -297,6 +346,7 @@ int main(int argc, char** argv) {
     else if (what == "estimate") estimate();
     else if (what == "pipelined") pipelined();
     else if (what == "by_block") by_block();
+    else if (what == "modes_share_a_plan") modes_share_a_plan();
     else return 2;
     std::printf("ok\n");
     return 0;

@@ -18,7 +18,7 @@ def exe(tmp_path_factory):
     return path
 
 
-@pytest.mark.parametrize("what", ["merged_once", "four_waves", "second_round", "on_waves", "estimate", "pipelined", "by_block"])
+@pytest.mark.parametrize("what", ["merged_once", "four_waves", "second_round", "on_waves", "estimate", "pipelined", "by_block", "modes_share_a_plan"])
 def test_decode_only_launch_forms(exe, what):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0")
     env.pop("LD_PRELOAD", None)
