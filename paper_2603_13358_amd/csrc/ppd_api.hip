@@ -449,7 +449,7 @@ ppd_status mixed_attention_impl(ppd_ctx* ctx, const void* q, const void* kv_page
         // Nor do the four-wave tiles merge: their form has no merge.  (Launches on single waves have no split range.)
         kp.four_waves = plan.four_waves;
         kp.wave_unit = plan.wave_unit;
-        kp.pipelined = plan.pipelined && slots > wgs;
+        kp.pipelined = plan.pipelined;
         if (n_wave == 0 && slots <= wgs && !kp.four_waves) kp.merge_groups = d_groups;
         kp.by_index = plan.by_index;
         const ppd_work_item& longest = plan.items[plan.queue_begin[ppd::kNarrowQueue]];

@@ -1544,7 +1544,8 @@ __device__ __forceinline__ void merge_last(const KParams& P, const ppd_work_item
 // left) take as long as a fifth of such a launch.  us of 64 sequences with the append, claimed and by index: D = 128, 64-380 keys
 // 19.9 and 18.6, 400-800 33.0 and 31.9, FP8 pages 25.3 and 23.8; D = 64, 64-380 16.0 and 13.1, 400-800 21.6 and 18.9.  The launch
 // alone, 64 of equal length: 800 keys 38.6 and 37.1, 1500 64.5 and 63.1, FP8 pages 1600 42.4 and 40.6, 3000 67.5 and 65.9, D = 64
-// 1500 36.3 and 34.5 (second_round_by_index has the exact rule and its figures).  Longer tiles
+// 1500 36.3 and 34.5 (second_round_by_index has the exact rule and its figures; those of bf16 pages below 640 keys, 1280 at D = 64, are
+// from before such tiles ran in ppd_pipelined_kernel).  Longer tiles
 // and more rounds are claimed, because they do not take the time that their length says (48 of 2000-6000 keys 129.8 and 133.7, 100
 // of 800-1600 88.0 and 90.8, 400 of 800-1600 314 and 327).  Measured and not kept: claiming the next slot before running the
 // current one (hides the round trip but holds a slot that an idle workgroup could have run: cfg2 186 -> 206 us).

@@ -217,7 +217,8 @@ static bool long_tiles_on_four_waves(const Plan& plan, int64_t wgs, int head_dim
 }
 
 // Whether a decode-only launch of more slots than workgroups hands its second round out by index (ppd_narrow_kernel) instead of
-// by claims.  Workgroup b gets slot b and slot 2 * wgs - 1 - b.  By index where that costs no more than any order must:
+// by claims.  Asked where no other form takes the launch: on bf16 pages the shortest tiles of about one length run pipelined, so the figures
+// below 640 keys (1280 at D = 64) there are what led to the rule and now apply to one-wave slots and lengths further apart.  Workgroup b gets slot b and slot 2 * wgs - 1 - b.  By index where that costs no more than any order must:
 //  * at most two rounds, of tiles below 1536 keys of bf16 pages or 3072 of FP8 pages (figures at the kernel);
 //  * the heaviest workgroup's two slots are at most 96 KiB of K/V above what no order can undercut -- the longest slot, the mean
 //    of the workgroups, or the two shortest slots of which two must share a workgroup -- where a slot's fixed cost counts as
@@ -275,7 +276,7 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
 // average and 1.06 at worst (560 tiles around 298 keys, one sequence of 845, 21.1 -> 22.4 us), the others 0.85 and 1.005.
 static bool tiles_pipelined(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int64_t n = plan.queue_begin[kQueues];
-    if (elem_bytes != 2 || n == 0 || plan.queue_begin[kWaveQueue] != n) return false;
+    if (elem_bytes != 2 || n <= wgs || plan.queue_begin[kWaveQueue] != n) return false;
     int64_t sum = 0;
     for (int64_t i = 0; i < n; ++i) sum += plan.items[i].kv_end - plan.items[i].kv_begin;
     const int64_t longest = plan.items[0].kv_end - plan.items[0].kv_begin, mean_bytes = sum / n * 2 * head_dim * elem_bytes;
@@ -580,7 +581,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     plan->wave_unit = n_mfma == 0 && !plan->four_waves && o.wave_tiles < 0 && o.force_kind != 1
                           ? tiles_on_waves(*plan, kWgPerCu * o.num_cus, D, o.kv_elem_bytes == 1 ? 1 : 2) : 0;
     plan->pipelined = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && tiles_pipelined(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
-    plan->by_index = n_mfma == 0 && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
+    plan->by_index = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && !plan->pipelined && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }
 

@@ -96,6 +96,10 @@ static Step step(std::vector<int32_t> keys, int head_dim, bool fp8, int64_t chun
     ppd_plan_stats st;
     CHECK(ppd_get_plan_stats(ctx, &st) == PPD_OK && st.n_mfma == 0);
     ppd_destroy(ctx);
+    // one form at most, and only where it has what it hands out
+    CHECK((g_params.by_index != 0) + (g_params.four_waves != 0) + (g_params.wave_unit != 0) + (g_params.pipelined != 0) <= 1);
+    CHECK(!g_params.merge_groups || (g_params.by_index | g_params.four_waves | g_params.wave_unit | g_params.pipelined) == 0);
+    CHECK(!(g_params.by_index || g_params.pipelined) || st.n_items > g_grid);
     return Step{g_params.by_index != 0, g_params.four_waves != 0, g_params.merge_groups != nullptr, g_merges == 1, st.n_items, st.n_groups};
 }
 
@@ -151,7 +155,8 @@ static void four_waves() {
     CHECK(!four(keys));
 }
 
-// The second round of a decode-only launch (256 workgroups) is handed out by index where its pairs are balanced.
+// The second round of a decode-only launch (256 workgroups) is handed out by index where its pairs are balanced, and the tiles do not run
+// pipelined (bf16 pages, up to 640 keys of about one length here, 1280 at D = 64).
 static void second_round() {
     const int64_t whole = 16384;  // no range is split
     auto by_index = [&](const std::vector<int32_t>& keys, int D = 128, bool fp8 = false) { return step(keys, D, fp8, whole, 0).by_index; };
@@ -159,15 +164,16 @@ static void second_round() {
     CHECK(by_index(lengths(64, 800)) && by_index(lengths(64, 1535)) && !by_index(lengths(64, 1536)));
     CHECK(by_index(lengths(64, 3071), 128, true) && !by_index(lengths(64, 3072), 128, true));
     CHECK(by_index(lengths(64, 1535), 64) && !by_index(lengths(64, 1536), 64));
-    CHECK(by_index(lengths(40, 1500)) && !by_index(lengths(39, 1500)) && by_index(lengths(39, 511)) && !by_index(lengths(39, 512)));
-    CHECK(by_index(lengths(33, 511)) && by_index(lengths(33, 1023), 64) && !by_index(lengths(33, 1024), 64));
+    CHECK(by_index(lengths(40, 1500)) && !by_index(lengths(39, 1500)));
+    CHECK(by_index(lengths(39, 1023), 128, true) && !by_index(lengths(39, 1024), 128, true));
+    CHECK(by_index(lengths(33, 2047), 64, true) && !by_index(lengths(33, 2048), 64, true));
     CHECK(by_index(lengths(33, 1023), 128, true) && !by_index(lengths(33, 1024), 128, true));
     for (int32_t keys : {500, 800, 1300})                                                  // another tile behind a long one
         for (int n_long : {1, 8})
             for (bool fp8 : {false, true})
                 for (int D : {64, 128}) {
                     CHECK(!by_index(lengths(64, keys, n_long, 4 * keys), D, fp8));
-                    CHECK(by_index(lengths(64, keys, n_long, keys + 32), D, fp8));
+                    CHECK(by_index(lengths(64, keys, n_long, keys + 32), D, fp8) != (!fp8 && keys * D <= 640 * 128));  // (those run pipelined)
                 }
     CHECK(!by_index(lengths(52, 800, 14, 1600)));                                          // 16 long tiles of 112 would get one
     CHECK(by_index(lengths(52, 800, 12, 1600)));                                           // none of 96 would
