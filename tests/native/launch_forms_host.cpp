@@ -209,6 +209,15 @@ static void on_waves() {
     CHECK(unit(lengths(256, 440)) == 4 && unit(lengths(257, 440)) == 0 && unit(lengths(511, 440)) == 0 && unit(lengths(512, 440)) == 4);  // rounds of the waves
     CHECK(unit(even) == 4 && unit(even, 128, true) == 4 && unit(even, 64) == 4);
     CHECK(unit(lengths(256, 3500)) == 0 && unit(lengths(64, 2000)) == 0);
+    auto longer = [&](int count, int32_t low, int32_t high, int D, bool fp8) {  // test_long_decode_tiles_on_single_waves
+        std::vector<int32_t> keys;
+        for (int32_t end : {2049, 2048, 2047, 2046, 1025, 1024, 1023, 1022, 15, 1})
+            if (end <= high) keys.push_back(end);
+        while ((int)keys.size() < count) keys.push_back(low + (int32_t)keys.size() * 37 % (high - low + 1));
+        return unit(keys, D, fp8);
+    };
+    CHECK(longer(256, 1900, 2049, 64, false) == 4 && longer(256, 800, 1100, 128, false) == 4);
+    CHECK(longer(128, 1900, 2100, 128, true) == 2 && longer(160, 1900, 2100, 64, true) == 2);
 }
 
 // Where no order could make single waves win, the planner finds that out without laying the tiles out on the waves: the plan takes the memory
@@ -254,6 +263,14 @@ static void pipelined() {
     CHECK(runs(lengths(40, 400, 4, 700)) && !runs(lengths(40, 400, 4, 800)) && runs(lengths(40, 200, 4, 600)) && !runs(lengths(40, 200, 4, 800)));
     CHECK(runs(lengths(64, 200, 1, 590)) && runs(lengths(65, 200, 1, 490)) && !runs(lengths(65, 200, 1, 500)));  // a long tile and two more behind it
     CHECK(!runs(lengths(64, 5000)) && !runs(lengths(256, 100)) && !runs(lengths(256, 440)));
+    auto split = [&](int count, int D, int64_t chunk, int64_t grid) {  // test_pipelined_tiles_of_split_ranges
+        std::vector<int32_t> keys;
+        for (int i = 0; i < count; ++i) keys.push_back(256 + i * 389 % 1024);
+        const Step s = step(keys, D, false, chunk, grid);
+        CHECK(g_params.pipelined && !s.merges_itself && s.merge_launched);
+        return s.groups;
+    };
+    CHECK(split(39, 128, 0, 0) == 144 && split(40, 64, 256, 48) == 312 && split(37, 128, 256, 100) == 288);
 }
 
 // The list of a launch of the mixed kernel with a workgroup for every entry is in the order of its workgroups: every tile once, workgroup b

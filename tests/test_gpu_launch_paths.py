@@ -540,3 +540,86 @@ def test_rounds_of_short_tiles_run_pipelined(B, Hkv, D, grid):
         torch.cuda.synchronize()
         assert np.array_equal(from_dev_u16(got).reshape(out.shape), out)
     ctx.close()
+
+
+@pytest.mark.parametrize("B,D,G,options,groups", [(39, 128, 4, {}, 144), (40, 64, 4, {"narrow_chunk": 256, "grid": 48}, 312), (37, 128, 8, {"narrow_chunk": 256, "grid": 100}, 288)])
+def test_pipelined_tiles_of_split_ranges(B, D, G, options, groups):
+    """Split ranges in pipelined launches, by the automatic split size and by a given one, in two rounds and in more: tiles that begin
+    and end inside their sequence, whole ones beside them, multi-row tiles, partials that stay in the L2 and (more than 3 MiB) that do not.  The oracle's result, bit for bit the mixed kernel's, and
+    again on one context, its static entry point among them."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    keys = 256 + np.arange(B) * 389 % 1024  # tests/native/launch_forms_host.cpp, pipelined(): these launches are pipelined ones
+    n = np.where(np.arange(B) % 7 == 6, 16 // G, 1)
+    b = si.make_batch("split", L=keys - n, n=n, Hq=8 * G, Hkv=8, D=D, seed=B, slack_pages=3)
+    pool, out, stats = gpu_step(b, options=options)
+    assert stats["n_mfma"] == 0 and stats["n_narrow"] > stats["grid"] and stats["n_groups"] == groups
+    assert (stats["partial_floats"] * 4 >= 3 << 20) == (G == 8)
+    check_close(bits_to_f32(out), oracle_out(b))
+    _, mixed, _ = gpu_step(b, options=dict(options, narrow_kernel=0))
+    assert np.array_equal(out, mixed)
+    dev = torch.device("cuda:0")
+    ctx = ppd.Context(8 * G, 8, D, b.num_pages)
+    for key, value in options.items():
+        ctx.set_option(key, value)
+    dpool, q, pt = to_dev_u16(pool, torch, dev), to_dev_u16(b.q, torch, dev), torch.from_numpy(b.page_tables).to(dev)
+    for call in (ctx.mixed_attention, ctx.mixed_attention, ctx.mixed_attention_static, ctx.mixed_attention):
+        got = torch.zeros((b.T, b.Hq, D), dtype=torch.int16, device=dev)
+        call(q, dpool, pt, b.L, b.n, b.scale, got)
+        torch.cuda.synchronize()
+        assert np.array_equal(from_dev_u16(got).reshape(out.shape), out)
+    ctx.close()
+
+
+@pytest.mark.parametrize("fp8,D,B,low,high", [(False, 64, 256, 1900, 2049), (False, 128, 256, 800, 1100), (True, 128, 128, 1900, 2100), (True, 64, 160, 1900, 2100)])
+def test_long_decode_tiles_on_single_waves(fp8, D, B, low, high):
+    """Tiles of more pages than a wave holds page ids of, around 64 and 128 pages, each on one wave (sequences that share two sequences'
+    pages, 8 KV heads, every seventh with two rows): the oracle's result, with less error than on whole workgroups, as short tiles."""
+    import torch
+    import paper_2603_13358_amd as ppd
+
+    Hq, Hkv = 16, 8
+    rng = np.random.default_rng(B + D)
+    keys = low + np.arange(B) * 37 % (high - low + 1)  # launch_forms_host.cpp, on_waves(): these launches run on single waves
+    ends = [e for e in (2049, 2048, 2047, 2046, 1025, 1024, 1023, 1022, 15, 1) if e <= high]
+    keys[:len(ends)] = ends
+    n = np.where((np.arange(B) % 7 == 6) & (keys > 1), 2, 1).astype(np.int32)
+    L = (keys - n).astype(np.int32)
+    base = si.make_batch("long", L=[high, high], n=[1, 1], Hq=8, Hkv=Hkv, D=D, seed=B, slack_pages=2)
+    tables = np.ascontiguousarray(base.page_tables[np.arange(B) % 2])
+    q = (rng.standard_normal((int(n.sum()), Hq, D)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    scale = 1.0 / np.sqrt(D)
+    # The results over 15 and 1 keys are 10 to 40 times as large as those over 1000 and more, so the rounding of a few of them to bf16, which
+    # both forms share, would outweigh what the forms differ by in all the others.
+    averages = np.repeat(keys > 15, n)
+    dev = torch.device("cuda:0")
+    if fp8:
+        pool, _, _ = gpu_step_fp8(base, 0.0173, 0.0421)
+        want = oracle.mixed_attention_fp8(q, pool, 0.0173, 0.0421, tables, L, n, Hq, Hkv, D, 16, base.num_pages, scale)
+        dpool = torch.from_numpy(pool).to(dev)
+    else:
+        pool, _, _ = gpu_step(base)
+        want = oracle.mixed_attention(q, pool, tables, L, n, Hq, Hkv, D, 16, base.num_pages, scale)
+        dpool = to_dev_u16(pool, torch, dev)
+    dq, dt = to_dev_u16(q, torch, dev), torch.from_numpy(tables).to(dev)
+    errors = []
+    for wave_tiles in (-1, 0):
+        ctx = ppd.Context(Hq, Hkv, D, base.num_pages)
+        if fp8:
+            ctx.set_kv_format(ppd.PPD_KV_FP8_E4M3, 0.0173, 0.0421)
+        ctx.set_option("wave_tiles", wave_tiles)
+        outs = []
+        for _ in range(2):
+            out = torch.zeros((len(q), Hq, D), dtype=torch.int16, device=dev)
+            ctx.mixed_attention(dq, dpool, dt, L, n, scale, out)
+            torch.cuda.synchronize()
+            outs.append(from_dev_u16(out))
+        stats = ctx.plan_stats()
+        assert stats.n_narrow == B * Hkv and stats.n_mfma == 0 and stats.n_groups == 0 and ctx.device_error_flags() == 0
+        assert np.array_equal(outs[0], outs[1])
+        got = bits_to_f32(outs[0]).reshape(want.shape)
+        check_close(got, want)
+        errors.append(np.linalg.norm((got.astype(np.float64) - want)[averages]))
+        ctx.close()
+    assert errors[0] <= 0.875 * errors[1], errors
