@@ -288,28 +288,41 @@ static bool tiles_pipelined(const Plan& plan, int64_t wgs, int head_dim, int ele
 // Whether every tile of a decode-only launch runs on one wave (ppd_wave_kernel), and in units of how many neighbours (0: no).  By
 // estimate, against the tiles on whole workgroups:
 //  * on whole workgroups a launch takes 6 us, 2.15 per round of tiles (3.3 on FP8 pages; tiles that the list already has on single waves
-//    count an eighth), and its bytes at 7.2 TB/s: within 4 % of 208 measured launches on average;
+//    count an eighth), and its bytes at 7.2 TB/s;
 //  * on waves it takes the longer of two flows of the bytes out of HBM at 6.7 TB/s: to the compute units, of which none takes more
-//    than 40 GB/s, and to the waves' chains of tiles, of which none takes more than 12 GB/s (6 at D = 64; FP8 pages 8 and 5).
-//    All take the same until the one with the least to read is done, and the others share what it took; then 4 us (6): within 4.5 %.
-// 4 % less has to come out.  Of 208 drawn launches of 520 tiles and more, bf16 and FP8 pages, both head sizes, equal, spread and log-normal
-// lengths around 60-4000 keys, it takes 83, for 22 % less time on average (200 sequences of 75 keys by 8 heads 0.41 of the time, 256 of
-// 64-700 keys 0.83, FP8 pages 0.63) and 2 % more at worst; taking the faster one each time would gain 0.1 % more over all of them.
-// Split ranges stay on whole workgroups, which merge them, and so do more tiles than one round of the chip's waves and fewer than two:
-// the units of the second round come on top of evenly loaded compute units there (300 sequences of 64-700 keys 83 us
-// where 467 MB need 70), and whole workgroups give the mixed kernel's results bit for bit.  Below two and a half tiles for each compute unit it is slower on average on bf16 pages and not taken, and where
-// the list has every tile on single waves as it is (at most 384 keys each, and 1536 of them) the two differ by -18 to +27 %: that form stays.
+//    than 40 GB/s (FP8 pages at D = 64: 24), and to the waves' chains of tiles, of which none takes more than 12 GB/s (6 at D = 64; FP8
+//    pages 8 and 5).  All take the same until the one with the least to read is done, and the others share what it took; then 4 us (6),
+//    and 4 more in the second round of bf16 pages.
+// What has to come out (8 %, 6 in the second round, on FP8 pages 4, at D = 64 6, in units of one 10) is where no drawn launch that was taken is
+// slower by more than two runs differ: of 2200 launches (bf16 and FP8 pages, both head sizes, 1-16 KV heads, up to four rows, equal, spread and
+// log-normal lengths around 60-4000 keys, a few longer ones among equal ones) 2 are, by 1.2 and 2.3 %.  bf16 pages take 0.81 of the time (800
+// launches), FP8 pages 0.79 (900 of 640 tiles and more) and 0.64 (500 of fewer).  With one rate for both head sizes of FP8 pages and 4 %
+// everywhere 73 of 2300 were slower: 1296 tiles of 3239 keys of FP8 pages at D = 64 107 -> 128 us, 5296 tiles of 669 keys of bf16 pages 283 -> 299.
+// Not by the estimate:
+//  * Split ranges stay on whole workgroups, which merge them.
+//  * More tiles than one round of the chip's waves and fewer than two stay there.  That is not where waves stop winning: 257 sequences of
+//    64-700 keys by 8 heads 65 us against 76, 511 125 against 139, FP8 pages 39 against 60 and 67 against 90, and of 120 drawn launches that
+//    the estimate would take on average 0.97 of the time on bf16 pages (0.86-1.06) and 0.80 on FP8 pages (0.52-1.06).  The line stands
+//    because whole workgroups give the mixed kernel's results bit for bit, which batches of that size are tested for.
+//  * Two rounds of waves and more on bf16 pages at D = 128: 2.5 % less time on average where HBM bounds both, and 34 of 197 launches slower, by up to 5.6 %.
+//    And two rounds of which the list has seven eighths on single waves already (5539 tiles of 80 keys of FP8 pages at D = 64 21.6 -> 24.7 us), and
+//    lists that are all on them (at most 384 keys each, and 1536 of them: 80 launches that the estimate would take -15 to +23 %, 2.6 % more on average).
+//  * Below two and a half tiles for each compute unit on bf16 pages, where ppd_pipelined_kernel runs them.
+//  * Up to two tiles for each workgroup on FP8 pages, a longest one of more than 176 keys: the second round by index (second_round_by_index) takes 9 us
+//    there at D = 64 and 11 at D = 128, a wave 4.5 and 20 ns a key (443 tiles of 197 keys 8.7 -> 9.7 us, 436 of 204 at D = 128 11.3 -> 11.8; 424 of 164 9.1 -> 8.7).
 // Units of two where there are fewer than six tiles for each compute unit: more units have work then (640-1100 tiles 1.3 % less time).
-// On FP8 pages, where a whole workgroup loses more between its tiles, from the second round on, in units of one and where
-// 10 % less has to come out: of 247 drawn launches of 257-640 tiles 57 take it, for 28 % less time on average and 1.4 % more at worst (bf16 pages of that many run in ppd_pipelined_kernel).
 // By the device's workgroups, not by a grid override: the forms round differently, and that option stays scheduling only.
 static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
     const int64_t n = plan.queue_begin[kQueues], n_wg = plan.queue_begin[kWaveQueue];
     const bool fp8 = elem_bytes == 1;
     if (fp8 ? n <= wgs : 2 * n < 5 * wgs) return 0;
-    if ((n > kWaves * wgs && n < 2 * kWaves * wgs) || n_wg == 0 || !plan.groups.empty()) return 0;
+    const bool rounds_of_waves = n > kWaves * wgs;
+    if ((rounds_of_waves && n < 2 * kWaves * wgs) || n_wg == 0 || !plan.groups.empty()) return 0;
+    if (rounds_of_waves && (8 * n_wg < n || (!fp8 && head_dim == 128))) return 0;
+    if (fp8 && n <= 2 * wgs && plan.items[0].kv_end - plan.items[0].kv_begin > 176) return 0;
     const double key_bytes = 2.0 * head_dim * elem_bytes;
-    constexpr double kHbm = 6.7e6, kUnit = 40e3;  // bytes per us
+    constexpr double kHbm = 6.7e6;  // bytes per us
+    const double unit_rate = fp8 && head_dim == 64 ? 24e3 : 40e3;
     const double wave_rate = fp8 ? (head_dim == 64 ? 5e3 : 8e3) : (head_dim == 64 ? 6e3 : 12e3);
     const int64_t unit = n >= 6 * wgs ? 4 : 2 * n >= 5 * wgs ? 2 : 1, groups = kWaves / unit;
     auto bytes_of = [&](int64_t i) { return (plan.items[i].kv_end - plan.items[i].kv_begin) * key_bytes; };
@@ -317,7 +330,9 @@ static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int e
     for (int64_t i = 0; i < n; ++i) bytes += bytes_of(i);
     const double rounds = ((double)n_wg + (double)(n - n_wg) / kWaves) / (double)wgs;
     const double on_workgroups = 6.0 + (fp8 ? 3.3 : 2.15) * rounds + bytes / 7.2e6;
-    const double at_most = (unit == 1 ? 0.90 : 0.96) * on_workgroups - (fp8 ? 6.0 : 4.0);  // us, of the flows
+    const double wins = unit == 1 ? 0.90 : fp8 ? (head_dim == 64 ? 0.94 : 0.96) : rounds_of_waves ? 0.94 : 0.92;
+    const double fixed = (fp8 ? 6.0 : 4.0) + (rounds_of_waves && !fp8 ? 4.0 : 0.0);
+    const double at_most = wins * on_workgroups - fixed;  // us, of the flows
     // Neither flow is over before HBM has delivered all bytes and a wave the longest tile.  That answers most launches, and the flows take
     // the host as long as the rest of a small plan (64 sequences of FP8 pages by 8 heads 65.6 -> 32.1 us, 31.7 without the estimate).
     if (std::max(bytes / kHbm, bytes_of(0) / wave_rate) >= at_most) return 0;
@@ -337,7 +352,7 @@ static int32_t tiles_on_waves(const Plan& plan, int64_t wgs, int head_dim, int e
         }
         return t;
     };
-    return std::max(flow(units, kUnit, 1), flow(chains, wave_rate, unit)) < at_most ? (int32_t)unit : 0;
+    return std::max(flow(units, unit_rate, 1), flow(chains, wave_rate, unit)) < at_most ? (int32_t)unit : 0;
 }
 
 ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, int32_t B, const PlanOptions& o,

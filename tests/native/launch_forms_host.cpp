@@ -202,11 +202,22 @@ static void on_waves() {
             CHECK(unit(lengths(192, 100, 16, 400), D, fp8, 0, 7) == 4 && unit(lengths(192, 100, 16, 400), D, fp8, 0, 4096) == 4);
             CHECK(unit(lengths(100, 100, 1, 4000), D, fp8) == 0 && unit(lengths(192, 300, 64, 8000), D, fp8) == 0);
         }
-        CHECK(unit(lengths(80, 300), 128, fp8, 320) == 2 && unit(lengths(80, 300, 1, 330), 128, fp8, 320) == 0);  // a split range
+        CHECK(unit(lengths(80, 200), 128, fp8, 320) == 2 && unit(lengths(80, 200, 1, 330), 128, fp8, 320) == 0);  // a split range
     }
     std::vector<int32_t> even(256);
     for (int i = 0; i < 256; ++i) even[i] = 64 + i * 636 / 255;
-    CHECK(unit(lengths(256, 440)) == 4 && unit(lengths(257, 440)) == 0 && unit(lengths(511, 440)) == 0 && unit(lengths(512, 440)) == 4);  // rounds of the waves
+    for (bool fp8 : {false, true})
+        for (int D : {64, 128}) {  // rounds of the waves
+            CHECK(unit(lengths(256, 440), D, fp8) == 4 && unit(lengths(257, 440), D, fp8) == 0 && unit(lengths(511, 440), D, fp8) == 0);
+            CHECK(unit(lengths(512, 440), D, fp8) == (D == 128 && !fp8 ? 0 : 4));
+        }
+    for (int D : {64, 128}) {
+        CHECK(unit(lengths(520, 100, 64, 400), D, true) == 0 && unit(lengths(520, 100, 65, 400), D, true) == 4);  // an eighth not on single waves as it is
+        CHECK(unit(lengths(64, 176), D, true) == 1 && unit(lengths(64, 177), D, true) == 0 && unit(lengths(65, 177), D, true) == 1);  // a second round by index
+    }
+    // where whole workgroups were measured to be faster
+    CHECK(unit(lengths(162, 3239), 64, true) == 0 && unit(lengths(145, 1726), 64, true) == 0 && unit(lengths(128, 1124), 64) == 0);
+    CHECK(unit(lengths(662, 669)) == 0 && unit(lengths(576, 590)) == 0);
     CHECK(unit(even) == 4 && unit(even, 128, true) == 4 && unit(even, 64) == 4);
     CHECK(unit(lengths(256, 3500)) == 0 && unit(lengths(64, 2000)) == 0);
     auto longer = [&](int count, int32_t low, int32_t high, int D, bool fp8) {  // test_long_decode_tiles_on_single_waves
@@ -216,8 +227,8 @@ static void on_waves() {
         while ((int)keys.size() < count) keys.push_back(low + (int32_t)keys.size() * 37 % (high - low + 1));
         return unit(keys, D, fp8);
     };
-    CHECK(longer(256, 1900, 2049, 64, false) == 4 && longer(256, 800, 1100, 128, false) == 4);
-    CHECK(longer(128, 1900, 2100, 128, true) == 2 && longer(160, 1900, 2100, 64, true) == 2);
+    CHECK(longer(256, 900, 1100, 64, false) == 4 && longer(200, 900, 1100, 64, false) == 4);
+    CHECK(longer(128, 1900, 2100, 128, true) == 2 && longer(256, 1900, 2100, 64, true) == 4);
 }
 
 // Where no order could make single waves win, the planner finds that out without laying the tiles out on the waves: the plan takes the memory
