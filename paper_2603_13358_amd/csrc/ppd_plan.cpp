@@ -267,22 +267,39 @@ static bool second_round_by_index(const Plan& plan, int64_t wgs, int head_dim, i
 
 // Whether the whole-workgroup tiles of a decode-only launch on bf16 pages run in ppd_pipelined_kernel where a workgroup gets more than one.
 // What it saves is the gap between two tiles, which counts while tiles are short; and it holds three tiles ahead, so that a workgroup
-// with one far longer than the others keeps what an idle one could have run.  Of 181 drawn launches of 257-2500 tiles, against tiles
-// one after the other (mean keys at D = 128, longest by mean): up to 300, up to 1.7 -13 %; up to 300, 1.7-3 -8; 300-600, up to 1.7 -3; 600-900 -2;
-// 900-2500 +1; 300-900, 1.7-2.2 +0.5; above 3 +11.  At D = 64 up to 300, 3.0 -8 %; 300-900, 1.7 -9; 900-1300 -7; above 3 +8.
-// 320 KiB are 625 keys at D = 128 and 1250 at D = 64.
-// In more than two rounds a workgroup's first three tiles go by index, the longest ones with two more behind them: not where the longest
-// is 1.2 times what a workgroup reads on average.  Of 283 drawn launches of more than two rounds, 6 beyond it 0.98 of the time on
-// average and 1.06 at worst (560 tiles around 298 keys, one sequence of 845, 21.1 -> 22.4 us), the others 0.85 and 1.005.
-static bool tiles_pipelined(const Plan& plan, int64_t wgs, int head_dim, int elem_bytes) {
+// with one far longer than the others keeps what an idle one could have run.  Not, against tiles one after the other:
+//  * above 320 KiB on average, 625 keys at D = 128 and 1250 at D = 64 (181 drawn launches of 257-2500 tiles: up to 300 keys 8-13 % less time,
+//    300-900 2-3, 900-2500 1 % more; at D = 64 300-900 9, 900-1300 7);
+//  * the longest above 3 times the average, from 150 KiB on 1.7 and from 200 on 1.5 (beyond 3 11 % more; 1000 tiles of 519 keys, the longest 1.66
+//    times that, 47.9 -> 50.5 us, 846 around 420 keys 38.7 -> 42.8);
+//  * a workgroup's first three tiles, which go by index (up, down and up the list, the longest ones with two more behind them), 96 KiB above what no
+//    order can undercut, a tile's fixed cost counted as 64 KiB (544 tiles of 263 keys, an eighth of them 2.3 times that, 20.7 -> 22.4 us, 576 20.5 -> 22.1; of 294
+//    drawn launches of two to three rounds 7 of 68 above it were slower by more than 1 %, by up to 8.3, and 3 of 226 below, by up to 2.8);
+//  * more than eight columns (of several rows) in a second round, or with split ranges: 3 and 1 % less time on average there, up to 3 and
+//    6.7 % more.
+// Of 1800 drawn launches that it takes (bf16 pages, both head sizes, 1-16 KV heads, up to four rows, 400 with split ranges) 7 are slower by
+// more than 1 %, by 2.8 at most; they take 0.91 of the time (0.95 with split ranges).
+static bool tiles_pipelined(const Plan& plan, int64_t wgs, int head_dim, int G, int elem_bytes) {
     const int64_t n = plan.queue_begin[kQueues];
     if (elem_bytes != 2 || n <= wgs || plan.queue_begin[kWaveQueue] != n) return false;
+    constexpr int64_t kFixed = 64 << 10, kAbove = 96 << 10, kLongest = 320 << 10, kEven = 200 << 10, kShort = 150 << 10;
+    const int64_t key_bytes = 2LL * head_dim * elem_bytes;
+    auto bytes = [&](int64_t i) { return (plan.items[i].kv_end - plan.items[i].kv_begin) * key_bytes; };
     int64_t sum = 0;
-    for (int64_t i = 0; i < n; ++i) sum += plan.items[i].kv_end - plan.items[i].kv_begin;
-    const int64_t longest = plan.items[0].kv_end - plan.items[0].kv_begin, mean_bytes = sum / n * 2 * head_dim * elem_bytes;
-    static_assert(kMaxPipelinedKeys >= 3 * (320 << 10) / (2 * 64 * 2), "a wave's share of the longest tile fits its page ids");
-    if (n > 2 * wgs && 5 * longest * wgs > 6 * sum) return false;
-    return mean_bytes <= 320 << 10 && longest * n * 10 <= sum * (mean_bytes <= 150 << 10 ? 30 : 17);
+    int32_t columns = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        sum += bytes(i);
+        columns = std::max(columns, plan.items[i].nrows * G);
+    }
+    static_assert(kMaxPipelinedKeys >= 3 * kLongest / (2 * 64 * 2), "a wave's share of the longest tile fits its page ids");
+    const int64_t mean = sum / n, tenths = mean <= kShort ? 30 : mean <= kEven ? 17 : 15;
+    if (mean > kLongest || bytes(0) * n * 10 > sum * tenths) return false;
+    if (columns > 8 && (n <= 2 * wgs || !plan.groups.empty())) return false;
+    auto cost = [&](int64_t i) { return i < n ? bytes(i) + kFixed : 0; };
+    const int64_t least = std::max({cost(0), sum / wgs + n * kFixed / wgs, cost(wgs - 1) + cost(wgs), cost(2 * wgs - 2) + cost(2 * wgs - 1) + cost(2 * wgs)});
+    for (int64_t b = 0; b < wgs; ++b)
+        if (cost(b) + cost(2 * wgs - 1 - b) + cost(2 * wgs + b) > least + kAbove) return false;
+    return true;
 }
 
 // Whether every tile of a decode-only launch runs on one wave (ppd_wave_kernel), and in units of how many neighbours (0: no).  By
@@ -595,7 +612,7 @@ ppd_status build_plan(const ppd_shape& s, const int32_t* L, const int32_t* n, in
     plan->four_waves = n_mfma == 0 && long_tiles_on_four_waves(*plan, kWgPerCu * o.num_cus, D, Hkv, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->wave_unit = n_mfma == 0 && !plan->four_waves && o.wave_tiles < 0 && o.force_kind != 1
                           ? tiles_on_waves(*plan, kWgPerCu * o.num_cus, D, o.kv_elem_bytes == 1 ? 1 : 2) : 0;
-    plan->pipelined = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && tiles_pipelined(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
+    plan->pipelined = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && tiles_pipelined(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, G, o.kv_elem_bytes == 1 ? 1 : 2);
     plan->by_index = n_mfma == 0 && !plan->four_waves && plan->wave_unit == 0 && !plan->pipelined && second_round_by_index(*plan, st.grid * (kWaves / kNarrowKernelWaves), D, o.kv_elem_bytes == 1 ? 1 : 2);
     return PPD_OK;
 }

@@ -271,17 +271,19 @@ static void pipelined() {
     };
     CHECK(!runs(lengths(32, 200)) && runs(lengths(33, 200)) && runs(lengths(79, 200)) && runs(lengths(20, 200), 128, false, 100));
     CHECK(!runs(lengths(33, 200), 128, true) && runs(lengths(33, 640)) && !runs(lengths(33, 641)) && runs(lengths(33, 1280), 64) && !runs(lengths(33, 1281), 64));
-    CHECK(runs(lengths(40, 400, 4, 700)) && !runs(lengths(40, 400, 4, 800)) && runs(lengths(40, 200, 4, 600)) && !runs(lengths(40, 200, 4, 800)));
-    CHECK(runs(lengths(64, 200, 1, 590)) && runs(lengths(65, 200, 1, 490)) && !runs(lengths(65, 200, 1, 500)));  // a long tile and two more behind it
+    CHECK(runs(lengths(40, 400, 4, 630)) && !runs(lengths(40, 400, 4, 640)) && runs(lengths(40, 300, 4, 540)) && !runs(lengths(40, 300, 4, 600)));
+    CHECK(runs(lengths(40, 200, 4, 600)) && !runs(lengths(40, 200, 4, 800)));
+    CHECK(runs(lengths(65, 200, 1, 390)) && !runs(lengths(65, 200, 1, 400)) && runs(lengths(72, 200, 9, 390)) && !runs(lengths(72, 200, 9, 400)));  // a long tile and two more behind it
+    CHECK(!runs(lengths(72, 220, 9, 520)) && !runs(lengths(125, 480, 12, 862)) && !runs(lengths(106, 417, 11, 700)));  // measured to be slower
     CHECK(!runs(lengths(64, 5000)) && !runs(lengths(256, 100)) && !runs(lengths(256, 440)));
     auto split = [&](int count, int D, int64_t chunk, int64_t grid) {  // test_pipelined_tiles_of_split_ranges
         std::vector<int32_t> keys;
-        for (int i = 0; i < count; ++i) keys.push_back(256 + i * 389 % 1024);
+        for (int i = 0; i < count; ++i) keys.push_back(300 + i * 389 % 700);
         const Step s = step(keys, D, false, chunk, grid);
         CHECK(g_params.pipelined && !s.merges_itself && s.merge_launched);
         return s.groups;
     };
-    CHECK(split(39, 128, 0, 0) == 144 && split(40, 64, 256, 48) == 312 && split(37, 128, 256, 100) == 288);
+    CHECK(split(34, 128, 0, 0) == 176 && split(40, 64, 256, 48) == 320 && split(37, 128, 256, 100) == 296);
 }
 
 // The list of a launch of the mixed kernel with a workgroup for every entry is in the order of its workgroups: every tile once, workgroup b
