@@ -95,7 +95,8 @@ typedef struct {
     int32_t kv_end;
     int32_t group;    /* merge group, or -1 when the tile covers the whole key range and writes `out` */
     int32_t queue;    /* work queue: 0..7 = MFMA tiles preferred by the workgroups of XCD `queue`, 8 = narrow tiles run by a
-                         whole workgroup, 9 = short narrow tiles run one per wave, eight to a claim */
+                         whole workgroup, 9 = short narrow tiles run one per wave, eight to a claim (a decode-only launch
+                         may run both one per wave: option "wave_tiles") */
     int64_t part_off; /* float offset of this tile's partial (o, m, l) in the workspace, or -1 */
 } ppd_work_item;
 
@@ -130,7 +131,8 @@ const char *ppd_last_error(const ppd_ctx *ctx);
  * 2 split by physical compute unit (default), 3 narrow tiles for all), "narrow_cus" (pref_mode 2: how many of
  * the 32 compute units of an XCD take narrow tiles first; -1 = sized by the planner's cost model so that both
  * kinds finish together), "wave_tiles" (-1 = narrow tiles of at most 384 keys run one per wave, eight to a claim, when the launch has at
- * least six such tiles per workgroup; 0 = never; 1 = whenever there is such a tile), "launch_mode" (0 = one kernel runs both kinds of tiles on separate compute units,
+ * least six such tiles per workgroup, and all tiles of a decode-only launch, whatever their length, where that is estimated to be
+ * faster (see below); 0 = never; 1 = tiles of at most 384 keys whenever there is one), "launch_mode" (0 = one kernel runs both kinds of tiles on separate compute units,
  * 1 = a step that holds both kinds runs as two kernels resident side by side on every compute unit -- row-block
  * tiles on the caller's stream, narrow tiles on a stream of the context's own, joined before the call's work ends
  * -- 2 = the two specialised kernels also for steps of one kind), "narrow_kernel" (1, the default = with launch_mode 0 a step
@@ -141,7 +143,8 @@ const char *ppd_last_error(const ppd_ctx *ctx);
  * waves: head_dim 128, bf16 pages, a multiple of 8 KV heads, no one-wave tiles, at least two tiles per compute unit, 3072 keys
  * or more per tile on average, and the last round of tiles nearly full (70 % of the units) or short (its longest tile at
  * most a seventh of a unit's mean load) -- and where it runs every tile on one wave: "wave_tiles" -1, no split ranges, at least
- * 2.5 tiles per compute unit (FP8 pages: more than one), not between one and two tiles per wave of the chip, and estimated to be
+ * 2.5 tiles per compute unit (FP8 pages: more than one), not between one and two tiles per wave of the chip (bf16 pages at head_dim
+ * 128: not more than one), at least one tile above 384 keys or fewer than six per workgroup, and estimated to be
  * faster by the tiles' lengths.  In both the results have less error (probabilities as two bf16 numbers; four partial
  * softmaxes per tile, or one, instead of eight), and so a row's rounding depends on the rest of its batch, as it does with the
  * automatic split sizes.  "grid" changes which workgroup runs what, not the results, as long as "narrow_chunk" and

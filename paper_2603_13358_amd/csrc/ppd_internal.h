@@ -151,7 +151,7 @@ struct KParams {
     int64_t pace_keys;       // ppd_narrow_kernel: the same, or the longest tile's keys over the launch's rounds where that is more
     int32_t four_waves;      // ppd_narrow_kernel: the four-wave form (long_tiles_on_four_waves), which leaves split ranges to ppd_merge_kernel
     int32_t pipelined;       // ppd_pipelined_kernel, which has at least as many slots as workgroups and no one-wave tiles
-    int32_t wave_unit;       // not 0: ppd_wave_kernel, which takes the tiles in units of this many (1, 2, 4 or 8)
+    int32_t wave_unit;       // not 0: ppd_wave_kernel, which takes the tiles in units of this many (1, 2 or 4)
     int32_t n_wg;         // whole-workgroup tiles, at the front of the work list
     int32_t by_block;     // ppd_mixed_kernel: a workgroup for every entry, the work list in their order (order_by_block)
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed

@@ -1609,12 +1609,13 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void ppd_narrow_kernel(const ppd_w
 // Decode-only launches of several rounds of short tiles (bf16 pages; whole-workgroup tiles).  A short tile streams for a few
 // microseconds, and the same again went by between its last load and the first one of the next tile: the combine, the claim, and
 // three reads that wait for one another (work item, page ids, K and V).  Here all of that happens ahead.  While a tile runs, the
-// workgroup holds the work item of the next two, page ids and queries of the next one, and a claim under way; the first kSets
+// workgroup holds the work item of the next two, page ids and queries of the next one, and a claim under way; the first kPipelinedSets
 // pages of the next tile are asked for as soon as a wave is through with its share of this one, before the waves' results meet in
 // LDS (two buffers, so that a tile needs one barrier, which leaves the loads in flight).
 // The first three slots of a workgroup go by index, up, down and up the list, longest tiles first; the others are claimed.  Bit for bit
-// the results of ppd_narrow_kernel.  A launch of 8 tiles of 100 keys to a workgroup 47.0 -> 37.5 us, of 8 of 382 79.3 -> 74.3, of 3 of 800-1600
-// 79.1 -> 75.5 (6.2 TB/s); two, three and four register sets, and the heads of a page on one XCD or on eight, are within 1 %.  What is left of a
+// the results of ppd_narrow_kernel.  A launch of 8 tiles of 100 keys to a workgroup 47.0 -> 37.5 us, of 8 of 382 79.3 -> 74.3 (both run on
+// single waves now), of 3 of 800-1600 79.1 -> 75.5 (6.2 TB/s); 90 decodes of 420-600 keys by 8 heads, 720 tiles, 33 us, 5.8 TB/s, and HBM reads 1.02 times
+// K, V and queries (64 of 100-300 keys 1.05); two, three and four register sets, and the heads of a page on one XCD or on eight, are within 1 %.  What is left of a
 // tile of 100 keys is 4 us: one trip of its loads, and its pages worked.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kPipelinedSets = 3, kByIndexSlots = 3;
@@ -1633,7 +1634,7 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_pipelined_kernel(const ppd_wo
     if (block >= slots) return;
     const float c = P.scale_log2e;
     const bool claims = slots > kByIndexSlots * grid;
-    typedef const __attribute__((address_space(4))) ppd_work_item* ItemPtr;  // read through the scalar cache: no kernel writes work items
+    typedef const __attribute__((address_space(4))) ppd_work_item* ItemPtr;  // read through the scalar cache: work items are written by the upload, an earlier launch on this stream, only
     // a tile as the workgroup holds it; one of no steps where the slot does not exist
     struct Tile {
         ppd_work_item it;
@@ -1760,11 +1761,13 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_pipelined_kernel(const ppd_wo
 // Decode-only launches of many tiles, each on one wave (tiles_on_waves decides, and says what it measured).  A wave goes from
 // tile to tile on its own -- no LDS, no barrier, no claim -- so that what a tile costs before and after its stream of loads passes
 // under the streams of the unit's other waves.  Tiles come longest first and are taken in units of neighbours, which read the heads'
-// pieces of the same pages: units go to the workgroups up, down, up the list (unit 0 and the 512th last meet on the first
-// workgroup), so that every compute unit has as many bytes to read, and to the 8 / unit groups of a workgroup's waves in turn.
-// A wave has one running reference for a whole tile where eight have eight, hence SPLIT_P.  Bound by HBM: 256 sequences of
+// pieces of the same pages: units go to the workgroups up, down, up the list (of 256, the first workgroup takes units 0, 511
+// and 512), so that every compute unit has as many bytes to read, and to the 8 / unit groups of a workgroup's waves in turn.
+// A wave has one running reference for a whole tile where eight have eight, hence SPLIT_P.  256 sequences of
 // 64-700 keys by 8 heads, 405 MB, 81 us on whole workgroups (5.0 TB/s), 75 with a tile to a wave in the list's order (the first units
-// have the longest tiles only and cannot stream faster than 55 GB/s), 67.5 this way (6.0 TB/s).  Two register sets, on FP8 pages two page
+// have the longest tiles only and cannot stream faster than 55 GB/s), 67.5 this way: 6.0 TB/s, where a plain read loop reaches 7.2.  HBM reads
+// 1.02 times K, V and queries.  What is missing are both ends: of 2048 tiles every wave has one, so nothing passes under the 4 us before its first loads,
+// nor under the last waves' tails.  FP8 pages 39 us (5.3 TB/s), D = 64 39 (5.2), both 26 (4.0: 4 KiB a wave in flight; the FP8 forms spill 54 scalars).  Two register sets, on FP8 pages two page
 // pairs: three and four of bf16 pages are 7 and 5 % slower on average over 260 drawn launches and one FP8 pair 8 %, single wave or full chip.
 // ---------------------------------------------------------------------------------------------------
 template <int HD, bool FP8>
