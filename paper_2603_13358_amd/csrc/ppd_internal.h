@@ -153,7 +153,7 @@ struct KParams {
     int32_t pipelined;       // ppd_pipelined_kernel, which has at least as many slots as workgroups and no one-wave tiles
     int32_t wave_unit;       // not 0: ppd_wave_kernel, which takes the tiles in units of this many (1, 2 or 4)
     int32_t n_wg;         // whole-workgroup tiles, at the front of the work list
-    int32_t by_block;     // ppd_mixed_kernel: a workgroup for every entry, the work list in their order (order_by_block)
+    int32_t by_block;     // ppd_mixed_by_block_kernel: a workgroup for every entry, the work list in their order (order_by_block)
     int32_t by_index;     // ppd_narrow_kernel: at most two rounds of slots, not claimed
     int32_t partials_past_l2;  // ppd_narrow_kernel: see store_partial
     int32_t n_items;

@@ -1347,6 +1347,28 @@ __device__ __forceinline__ void rearm_cursors(const KParams& P, int q0, int q1, 
     }
 }
 
+// The tile of the mixed kernels that stands at `idx` of the list; one-wave tiles, which are those from n_wg to `end`, kWaves at a time.
+template <int HD, bool FP8>
+__device__ __forceinline__ void mixed_tile(const KParams& P, int idx, int n_wg, int end, char* smem) {
+    if (idx >= n_wg) {
+        // wave w runs tile idx + w on its own
+        const int mine = idx + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (mine < end) {
+            const ppd_work_item it = P.items[mine];
+            if constexpr (FP8) narrow_item_wide<HD, 1, fp8_sets(HD), true, true>(P, it, smem);
+            else narrow_item<HD, 1, mixed_sets(HD), mixed_sets(HD), true>(P, it, smem);
+        }
+        return;
+    }
+    const ppd_work_item it = P.items[idx];
+    if (it.kind == 0) {
+        if constexpr (FP8) narrow_item_wide<HD, kWaves, fp8_sets(HD), false, true>(P, it, smem);
+        else narrow_item<HD, kWaves, mixed_sets(HD), mixed_sets(HD), false>(P, it, smem);
+    } else {
+        mfma_item<HD, false, FP8>(P, it, smem);
+    }
+}
+
 template <int HD, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P) {
     // Dynamic LDS: rings of kStages + 1 stages of 4 pages of K and as many of V, then the page ids of a tile's key
@@ -1384,11 +1406,9 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
     // others are, instead of one failing atomic (a round trip to the L2 each, one after the other) per queue --
     // that chain used to be the last ~10 us of every workgroup, and so of every launch.
     unsigned dry = 0;
-    if (!P.by_block) {
 #pragma unroll
-        for (int q = 0; q < kQueues; ++q)
-            if (P.queue_begin[q + 1] == P.queue_begin[q]) dry |= 1u << q;
-    }
+    for (int q = 0; q < kQueues; ++q)
+        if (P.queue_begin[q + 1] == P.queue_begin[q]) dry |= 1u << q;
     constexpr unsigned kAllDry = (1u << kQueues) - 1;
     auto look_at_cursors = [&]() {
         unsigned cur[kQueues];
@@ -1399,14 +1419,8 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
         for (int q = 0; q < kQueues; ++q)
             if ((int)(cur[q] * (q == kWaveQueue ? kWaves : 1)) >= P.queue_begin[q + 1] - P.queue_begin[q]) dry |= 1u << q;
     };
-    // A launch with a workgroup for every entry (a tile, or kWaves one-wave tiles) claims nothing: its list is in the order of the
-    // workgroups, the one-wave tiles behind the others.  A claim costs such a launch ~4 us of ~13: the first one, the one that finds the
-    // queues empty, and the re-arming of the cursors (small steps of 4 layers 233 -> 218, 59.3 -> 55.3 us); and with the order in the list
-    // the first read from memory is the work item, where the queues' bounds and a search in them came before it (steps of 8, 80 and 48 tiles 9.14 -> 8.57, 25.2 -> 23.4 and 12.1 -> 11.5 us).
-    const int block = (int)blockIdx.x;
-    const int own = !P.by_block ? -1 : block < P.n_wg ? block : P.n_wg + (block - P.n_wg) * kWaves;
     for (;;) {
-        if (own < 0 && tid == 0) {
+        if (tid == 0) {
             int idx = -1;
 #pragma unroll
             for (int attempt = 0; attempt < 2 && idx < 0; ++attempt) {
@@ -1435,34 +1449,27 @@ __global__ __launch_bounds__(kThreads, 2) void ppd_mixed_kernel(const KParams P)
             }
             *s_next = idx;
         }
-        int idx = own;
-        if (own < 0) {
-            __syncthreads();
-            idx = __builtin_amdgcn_readfirstlane(*s_next);
-            __syncthreads();  // everyone has read s_next, and the previous tile's LDS use is over
-        }
+        __syncthreads();
+        const int idx = __builtin_amdgcn_readfirstlane(*s_next);
+        __syncthreads();  // everyone has read s_next, and the previous tile's LDS use is over
         if (idx < 0) break;
-        if (idx >= P.n_wg) {
-            // a claim on the wave-tile queue: wave w runs tile idx + w on its own
-            const int mine = idx + __builtin_amdgcn_readfirstlane(tid >> 6);
-            if (mine < P.n_items) {
-                const ppd_work_item it = P.items[mine];
-                if constexpr (FP8) narrow_item_wide<HD, 1, fp8_sets(HD), true, true>(P, it, smem);
-                else narrow_item<HD, 1, mixed_sets(HD), mixed_sets(HD), true>(P, it, smem);
-            }
-            if (own >= 0) return;
-            continue;
-        }
-        const ppd_work_item it = P.items[idx];
-        if (it.kind == 0) {
-            if constexpr (FP8) narrow_item_wide<HD, kWaves, fp8_sets(HD), false, true>(P, it, smem);
-            else narrow_item<HD, kWaves, mixed_sets(HD), mixed_sets(HD), false>(P, it, smem);
-        } else {
-            mfma_item<HD, false, FP8>(P, it, smem);
-        }
-        if (own >= 0) return;
+        mixed_tile<HD, FP8>(P, idx, P.queue_begin[kWaveQueue], P.queue_begin[kQueues], smem);
     }
     if (tid == 0) rearm_cursors(P, 0, kCursors, 10);
+}
+
+// A launch of the mixed kernel with a workgroup for every entry (a tile, or kWaves one-wave tiles) claims nothing: its list is in the order
+// of the workgroups, the one-wave tiles behind the others.  A claim costs such a launch ~4 us of ~13: the first one, the one that finds the
+// queues empty, and the re-arming of the cursors (small steps of 4 layers 233 -> 218, 59.3 -> 55.3 us); and with the order in the list
+// the first read from memory is the work item, where the queues' bounds and a search in them came before it (steps of 8, 80 and 48 tiles 9.14 -> 8.57, 25.2 -> 23.4 and 12.1 -> 11.5 us).
+// A kernel of its own: with both in one, what this one knows (its tile, the list's bounds) was kept over the other's loop, 91 spilled scalars
+// on FP8 pages against 83 and 22 against 11 on bf16 pages.  66 decodes and turns of FP8 pages by 8 heads, 2176 tiles, 889 us in one kernel, 863 in
+// two; 110 drawn launches with claims of FP8 pages 0.98 of the time, 190 of bf16 pages equal; 600 drawn launches without 0.97.
+template <int HD, bool FP8>
+__global__ __launch_bounds__(kThreads, 2) void ppd_mixed_by_block_kernel(const KParams P) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int block = (int)blockIdx.x;
+    mixed_tile<HD, FP8>(P, block < P.n_wg ? block : P.n_wg + (block - P.n_wg) * kWaves, P.n_wg, P.n_items, smem);
 }
 
 // Merge of a split range by the last of its tiles, in the launch that made them: every tile of the group has counted itself in
@@ -2147,6 +2154,10 @@ int prepare_mixed_kernels() {
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, false>), mixed_lds_bytes(64));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<128, true>), mixed_lds_bytes(128));
     allow(reinterpret_cast<const void*>(&ppd_mixed_kernel<64, true>), mixed_lds_bytes(64));
+    allow(reinterpret_cast<const void*>(&ppd_mixed_by_block_kernel<128, false>), mixed_lds_bytes(128));
+    allow(reinterpret_cast<const void*>(&ppd_mixed_by_block_kernel<64, false>), mixed_lds_bytes(64));
+    allow(reinterpret_cast<const void*>(&ppd_mixed_by_block_kernel<128, true>), mixed_lds_bytes(128));
+    allow(reinterpret_cast<const void*>(&ppd_mixed_by_block_kernel<64, true>), mixed_lds_bytes(64));
     for (int form = 0; form < 8; ++form) {  // of the decode-only kernel eight waves at D = 128: page format, short and long tiles, merged in the launch or not
         const int64_t keys = form & 2 ? 1 << 20 : 0;
         const NarrowForm f = narrow_form(128, (form & 1) != 0, false, keys, keys, (form & 4) != 0);
@@ -2161,15 +2172,11 @@ int prepare_mixed_kernels() {
 }
 
 int launch_mixed(const KParams& p, int head_dim, int grid, void* stream, bool fp8_pages) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (head_dim == 128 && !fp8_pages)
-        hipLaunchKernelGGL((ppd_mixed_kernel<128, false>), dim3(grid), dim3(kThreads), mixed_lds_bytes(128), st, p);
-    else if (head_dim == 128)
-        hipLaunchKernelGGL((ppd_mixed_kernel<128, true>), dim3(grid), dim3(kThreads), mixed_lds_bytes(128), st, p);
-    else if (!fp8_pages)
-        hipLaunchKernelGGL((ppd_mixed_kernel<64, false>), dim3(grid), dim3(kThreads), mixed_lds_bytes(64), st, p);
-    else
-        hipLaunchKernelGGL((ppd_mixed_kernel<64, true>), dim3(grid), dim3(kThreads), mixed_lds_bytes(64), st, p);
+    auto* const kernel = head_dim == 128 ? (fp8_pages ? (p.by_block ? &ppd_mixed_by_block_kernel<128, true> : &ppd_mixed_kernel<128, true>)
+                                                      : (p.by_block ? &ppd_mixed_by_block_kernel<128, false> : &ppd_mixed_kernel<128, false>))
+                                         : (fp8_pages ? (p.by_block ? &ppd_mixed_by_block_kernel<64, true> : &ppd_mixed_kernel<64, true>)
+                                                      : (p.by_block ? &ppd_mixed_by_block_kernel<64, false> : &ppd_mixed_kernel<64, false>));
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), mixed_lds_bytes(head_dim), static_cast<hipStream_t>(stream), p);
     return (int)hipGetLastError();
 }
 
