@@ -371,6 +371,23 @@ static void modes_share_a_plan() {
         ppd_destroy(ctx);
     }
     CHECK(in_order > 100);
+    // a list that the fixed scratch array holds in one order only is claimed there
+    for (int decodes : {2200, 2400}) {
+        const ppd_shape s = {32, 8, 128, 16, 1 << 20};
+        std::vector<int32_t> L((size_t)decodes + 1, 99), n((size_t)decodes + 1, 1);
+        n[0] = 64;
+        for (bool use_static : {false, true}) {
+            ppd_ctx* ctx = nullptr;
+            CHECK(ppd_create(&s, 0, &ctx) == PPD_OK);
+            for (auto& o : std::vector<std::pair<const char*, int64_t>>{{"wave_tiles", 0}, {"grid", 65536}, {"mfma_chunk", 32768}, {"narrow_chunk", 8192}})
+                CHECK(ppd_set_option(ctx, o.first, o.second) == PPD_OK);
+            auto fn = use_static ? ppd_mixed_attention_static : ppd_mixed_attention;
+            CHECK(fn(ctx, device, device, reinterpret_cast<const int32_t*>(device), 1 << 16, L.data(), n.data(), (int32_t)L.size(), 1.f, device, nullptr) == PPD_OK);
+            sim.null_stream.run();
+            CHECK(ctx->plan.stats.n_items == 8 * (decodes + 1) && (g_params.by_block != 0) == (!use_static || decodes == 2200));
+            ppd_destroy(ctx);
+        }
+    }
 }
 
 int main(int argc, char** argv) {
